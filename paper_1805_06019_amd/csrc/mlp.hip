@@ -27,7 +27,7 @@ constexpr int oW1 = 0, oB1 = oW1 + kH * kIn, oW2 = oB1 + kH, oB2 = oW2 + kH * kH
 static_assert(kParams == LFC_MLP_PARAMS, "parameter count");
 constexpr int kThreads = 256;
 constexpr int kTile = 128;   // rows per gradient workgroup
-constexpr int kSplitWgs = 256;   // workgroups of the gradient that run at once (one per compute unit)
+constexpr int kCus = 256;    // compute units of the device
 
 __device__ __forceinline__ float bf16_to_f32(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
@@ -49,6 +49,7 @@ __global__ __launch_bounds__(kThreads) void k_mlp_unpack(const uint16_t *w, floa
 }
 
 struct InferArgs {
+  const uint16_t *w;
   const float *wf;   // the parameters as float32 (k_mlp_unpack)
   const float *x;
   int64_t n;
@@ -129,126 +130,203 @@ __global__ __launch_bounds__(kThreads) void k_mlp_infer(InferArgs a) {
 // ---------------------------------------------------------------------------
 // inference on the matrix cores: bf16 operands, fp32 accumulation
 // ---------------------------------------------------------------------------
-// Each wave runs tiles of 32 rows through v_mfma_f32_32x32x16_bf16: lane l
-// supplies row l%32 of A with K elements 8*(l/32)..+7, column l%32 of B with
-// the same K elements, and receives D[8*(r/4) + 4*(l/32) + r%4][l%32] in its
-// register r.  The weights (as B operands) stay in registers for the wave's
-// life; each layer's output goes through the wave's LDS (bias, ReLU, rounded
-// to bf16) to become the next layer's A operand.
+// What bounds it: vector issue beside the matrix cores (the bias, ReLU and
+// rounding of 128 hidden values a row, the two heads), with the rows' 70 bytes
+// from and to HBM close behind.  Each wave runs tiles of 32 rows through
+// v_mfma_f32_32x32x16_bf16 with the weights as the first operand (units x
+// rows): lane l supplies unit l%32 with K elements 8 (l/32)..+7 and row l%32
+// with the same K elements, and receives units 8 (r/4) + 4 (l/32) + r%4 of row
+// l%32 in its register r.  A row's values thus stay in its two lanes l and
+// l+32: after the bias and the ReLU they are rounded and packed, and one
+// exchange of register halves between the two lanes per pair of packed words
+// (v_permlane32_swap) gives the next layer's operand with its K elements in
+// their order, so no layer goes through LDS.  The weights stay in registers
+// for the wave's life, the biases are read from LDS, and the next tile's
+// features are requested before this tile's layers.
+// Measured over 18.2 M rows: @BF16@
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 constexpr int kMfmaWaves = 4;
+constexpr int kMfmaWgs = 3;   // workgroups per compute unit that the registers allow
 
 __device__ __forceinline__ bf16x8 load_bf16x8(const uint16_t *p) {
-  const uint4 v = *reinterpret_cast<const uint4 *>(p);
-  bf16x8 r;
-  __builtin_memcpy(&r, &v, sizeof r);
-  return r;
+  return __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(p));
 }
 
-__global__ __launch_bounds__(64 * kMfmaWaves) void k_mlp_infer_mfma(InferArgs a, const uint16_t *w) {
-  __shared__ __attribute__((aligned(16))) __bf16 sh[kMfmaWaves][2][32][kH];   // layer outputs
-  __shared__ float sz[kMfmaWaves][32][kOut + 3];   // logits
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, col = lane & 31, kh = lane >> 5;
-  // B operands: W1 (K 16) as 2 column tiles; W2, W3 (K 64) as 4 K steps x 2 tiles
-  bf16x8 b1[2], b2[4][2], b3[4][2];
-  float bias1[2], bias2[2], bias3[2];
+// A head's running argmax.  A later unit wins only with a larger logit, so
+// ties go to the lower class; where lanes hold parts of a row, the lane of the
+// head's first unit starts from that unit's logit and the others from -inf, as
+// one pass over the units in order would.
+struct Best {
+  float v;
+  int i;
+  __device__ __forceinline__ void take(float z, int k) {
+    const bool g = z > v;
+    v = g ? z : v;
+    i = g ? k : i;
+  }
+  // the other lane's part: the larger logit, on equality the lower class
+  __device__ __forceinline__ void join(int mask) {
+    const float ov = __shfl_xor(v, mask);
+    const int oi = __shfl_xor(i, mask);
+    const bool g = ov > v || (ov == v && oi < i);
+    v = g ? ov : v;
+    i = g ? oi : i;
+  }
+};
+
+// The biases as float32 in LDS, zero past the last unit of a layer.
+__device__ __forceinline__ void load_biases(const uint16_t *w, float (*sb)[kH]) {
+  for (int i = threadIdx.x; i < 3 * kH; i += 64 * kMfmaWaves) {
+    const int l = i / kH, j = i % kH;
+    sb[l][j] = l == 0 ? bf16_to_f32(w[oB1 + j]) : (l == 1 ? bf16_to_f32(w[oB2 + j]) : (j < kOut ? bf16_to_f32(w[oB3 + j]) : 0.0f));
+  }
+  __syncthreads();
+}
+
+// The wave's 32 x 37 logits, staged in LDS as the output holds them.
+__device__ __forceinline__ void put_logits(const float *sz, float *out, int rows, int lane) {
+  __builtin_amdgcn_s_waitcnt(0xc07f);   // this wave's LDS writes are done
+  __builtin_amdgcn_wave_barrier();
+  for (int i = lane; i < rows * kOut; i += 64) out[i] = sz[i];
+  __builtin_amdgcn_wave_barrier();
+}
+
+template <bool LOGITS>
+__global__ __launch_bounds__(64 * kMfmaWaves, kMfmaWgs) void k_mlp_infer_mfma(InferArgs a) {
+  __shared__ __attribute__((aligned(16))) float sb[3][kH];
+  __shared__ float sz[LOGITS ? kMfmaWaves : 1][LOGITS ? 32 * kOut : 1];
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int col = lane & 31, h = lane >> 5;
+  load_biases(a.w, sb);
+  // weights: W1 (K 16) as 2 unit tiles; W2, W3 (K 64) as 4 K steps x 2 tiles
+  // (units from 37 on are zero)
+  bf16x8 w1[2], w2[4][2], w3[4][2];
   const bf16x8 zero8 = {};
 #pragma unroll
   for (int t = 0; t < 2; t++) {
     const int j = t * 32 + col;
-    b1[t] = load_bf16x8(w + oW1 + j * kIn + kh * 8);
-    bias1[t] = bf16_to_f32(w[oB1 + j]);
-    bias2[t] = bf16_to_f32(w[oB2 + j]);
-    bias3[t] = j < kOut ? bf16_to_f32(w[oB3 + j]) : 0.0f;
+    w1[t] = load_bf16x8(a.w + oW1 + j * kIn + h * 8);
 #pragma unroll
     for (int ks = 0; ks < 4; ks++) {
-      b2[ks][t] = load_bf16x8(w + oW2 + j * kH + ks * 16 + kh * 8);
-      b3[ks][t] = j < kOut ? load_bf16x8(w + oW3 + j * kH + ks * 16 + kh * 8) : zero8;
+      w2[ks][t] = load_bf16x8(a.w + oW2 + j * kH + ks * 16 + h * 8);
+      w3[ks][t] = j < kOut ? load_bf16x8(a.w + oW3 + j * kH + ks * 16 + h * 8) : zero8;
     }
   }
-  const int64_t tiles = (a.n + 31) / 32;
-  for (int64_t tile = (int64_t)blockIdx.x * kMfmaWaves + wv; tile < tiles; tile += (int64_t)gridDim.x * kMfmaWaves) {
-    const int64_t r0 = tile * 32, row = r0 + col;
-    // layer 1: A = this lane's row, features 8*kh..+7, rounded to bf16
-    bf16x8 a1;
+  // bias, ReLU, rounding to bf16, and the next layer's operand of each K step
+  auto next_operand = [&](const f32x16 (&d)[2], const float *b, bf16x8 (&o)[4]) {
+#pragma unroll
+    for (int ks = 0; ks < 4; ks++) {
+      uint32_t pk[4];   // units 16 ks + 4 h ..+3, then 16 ks + 8 + 4 h ..+3
+#pragma unroll
+      for (int g = 0; g < 2; g++) {
+        const f32x4 bb = *reinterpret_cast<const f32x4 *>(b + 16 * ks + 8 * g);
+#pragma unroll
+        for (int p = 0; p < 2; p++) {
+          typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+          const int r = 8 * (ks & 1) + 4 * g + 2 * p;
+          const bf16x2 v = {(__bf16)fmaxf(d[ks >> 1][r] + bb[2 * p], 0.0f), (__bf16)fmaxf(d[ks >> 1][r + 1] + bb[2 * p + 1], 0.0f)};
+          pk[2 * g + p] = __builtin_bit_cast(uint32_t, v);
+        }
+      }
+      // lane l keeps units 16 ks ..+7, lane l + 32 units 16 ks + 8 ..+7
+      const auto s0 = __builtin_amdgcn_permlane32_swap(pk[0], pk[2], false, false);
+      const auto s1 = __builtin_amdgcn_permlane32_swap(pk[1], pk[3], false, false);
+      const u32x4 q = {s0[0], s1[0], s0[1], s1[1]};
+      o[ks] = __builtin_bit_cast(bf16x8, q);
+    }
+  };
+  const int64_t tiles = (a.n + 31) / 32, stride = (int64_t)gridDim.x * kMfmaWaves;
+  f32x4 xu = {}, xv = {};   // this lane's half of its row, requested a tile ahead
+  auto request = [&](int64_t tile) {
+    const int64_t row = tile * 32 + col;
     if (row < a.n) {
-      const float4 u = *reinterpret_cast<const float4 *>(a.x + row * kIn + kh * 8);
-      const float4 v = *reinterpret_cast<const float4 *>(a.x + row * kIn + kh * 8 + 4);
-      a1[0] = (__bf16)u.x, a1[1] = (__bf16)u.y, a1[2] = (__bf16)u.z, a1[3] = (__bf16)u.w;
-      a1[4] = (__bf16)v.x, a1[5] = (__bf16)v.y, a1[6] = (__bf16)v.z, a1[7] = (__bf16)v.w;
-    } else {
-      a1 = zero8;
+      xu = *reinterpret_cast<const f32x4 *>(a.x + row * kIn + h * 8);
+      xv = *reinterpret_cast<const f32x4 *>(a.x + row * kIn + h * 8 + 4);
     }
-    // d -> bias, ReLU, bf16 into the wave's LDS rows
-    auto store_act = [&](const f32x16 &d, float bias, int t, int buf) {
+  };
+  int64_t tile = (int64_t)blockIdx.x * kMfmaWaves + wv;
+  request(tile);
+  for (; tile < tiles; tile += stride) {
+    bf16x8 x;
 #pragma unroll
-      for (int r = 0; r < 16; r++) sh[wv][buf][8 * (r / 4) + 4 * kh + (r % 4)][t * 32 + col] = (__bf16)fmaxf(d[r] + bias, 0.0f);
-    };
+    for (int k = 0; k < 4; k++) x[k] = (__bf16)xu[k], x[4 + k] = (__bf16)xv[k];
+    request(tile + stride);
+    // (the biases are read anew for each tile: kept in registers, their 160
+    // values would halve the waves per SIMD)
+    int hb = 4 * h;
+    asm volatile("" : "+v"(hb));
+    const float *bias = &sb[0][0] + hb;
+    f32x16 d[2] = {{}, {}};
+    bf16x8 o[4];
 #pragma unroll
-    for (int t = 0; t < 2; t++) {
-      f32x16 d = {};
-      d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, b1[t], d, 0, 0, 0);
-      store_act(d, bias1[t], t, 0);
+    for (int t = 0; t < 2; t++) d[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w1[t], x, d[t], 0, 0, 0);
+    next_operand(d, bias, o);
+    d[0] = d[1] = f32x16{};
+#pragma unroll
+    for (int ks = 0; ks < 4; ks++)
+#pragma unroll
+      for (int t = 0; t < 2; t++) d[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w2[ks][t], o[ks], d[t], 0, 0, 0);
+    next_operand(d, bias + kH, o);
+    d[0] = d[1] = f32x16{};
+#pragma unroll
+    for (int ks = 0; ks < 4; ks++)
+#pragma unroll
+      for (int t = 0; t < 2; t++) d[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w3[ks][t], o[ks], d[t], 0, 0, 0);
+    // this lane's logits of its row: units 8 g + 4 h + j (z[4 g + j]), g = 0..4; past unit 36 none
+    float z[20];
+#pragma unroll
+    for (int g = 0; g < 5; g++) {
+      const f32x4 bb = *reinterpret_cast<const f32x4 *>(bias + 2 * kH + 8 * g);
+#pragma unroll
+      for (int j = 0; j < 4; j++) z[4 * g + j] = d[g >> 2][(4 * g + j) & 15] + bb[j];
     }
-    __builtin_amdgcn_s_waitcnt(0xc07f);   // LDS writes of this wave done before its reads
-    __builtin_amdgcn_wave_barrier();
-    // layer 2
-    f32x16 d2[2] = {{}, {}};
+    const int64_t r0 = tile * 32;
+    const int rows = (int)min((int64_t)32, a.n - r0);
+    const float ninf = -__builtin_inff();
+    // threshold head: units 0..9 (lane l: 0-3, 8, 9; lane l + 32: 4-7)
+    Best c = {h ? ninf : z[0], 0};
 #pragma unroll
-    for (int ks = 0; ks < 4; ks++) {
-      const bf16x8 a2 = *reinterpret_cast<const bf16x8 *>(&sh[wv][0][col][ks * 16 + kh * 8]);
+    for (int j = 0; j < 4; j++) c.take(z[j], 4 * h + j);
 #pragma unroll
-      for (int t = 0; t < 2; t++) d2[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a2, b2[ks][t], d2[t], 0, 0, 0);
+    for (int j = 4; j < 6; j++) c.take(h ? ninf : z[j], 4 + j);
+    // range head: units 10..36 (lane l: 10, 11, then groups of four; lane l + 32: 12-15, ..., 36)
+    Best q = {h ? ninf : z[6], 0};
+#pragma unroll
+    for (int j = 4; j < 6; j++) q.take(h ? z[j] : ninf, j - 2);
+#pragma unroll
+    for (int j = 6; j < 8; j++) q.take(z[j], 4 * h + j - 6);
+#pragma unroll
+    for (int j = 8; j < 16; j++) q.take(z[j], (j / 4) * 8 + j % 4 + 4 * h - kCls);
+    q.take(z[16], 32 + 4 * h - kCls);
+#pragma unroll
+    for (int j = 17; j < 20; j++) q.take(h ? ninf : z[j], 32 + j - 16 - kCls);
+    c.join(32);
+    q.join(32);
+    if (a.conf) {
+      float den = 0.0f;
+#pragma unroll
+      for (int j = 0; j < 4; j++) den += expf(z[j] - c.v);
+#pragma unroll
+      for (int j = 4; j < 6; j++) den += expf((h ? ninf : z[j]) - c.v);
+      den += __shfl_xor(den, 32);
+      if (!h && col < rows) a.conf[r0 + col] = 1.0f / den;
     }
-#pragma unroll
-    for (int t = 0; t < 2; t++) store_act(d2[t], bias2[t], t, 1);
-    __builtin_amdgcn_s_waitcnt(0xc07f);
-    __builtin_amdgcn_wave_barrier();
-    // layer 3 (columns 37..63 are zero weights)
-    f32x16 d3[2] = {{}, {}};
-#pragma unroll
-    for (int ks = 0; ks < 4; ks++) {
-      const bf16x8 a3 = *reinterpret_cast<const bf16x8 *>(&sh[wv][1][col][ks * 16 + kh * 8]);
-#pragma unroll
-      for (int t = 0; t < 2; t++) d3[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a3, b3[ks][t], d3[t], 0, 0, 0);
+    if (!h && col < rows) {
+      a.cls[r0 + col] = (int8_t)c.i;
+      a.rng[r0 + col] = (int8_t)q.i;
     }
+    if constexpr (LOGITS) {
+      float *sw = sz[wv];
 #pragma unroll
-    for (int t = 0; t < 2; t++)
-#pragma unroll
-      for (int r = 0; r < 16; r++) {
-        const int j = t * 32 + col;
-        if (j < kOut) sz[wv][8 * (r / 4) + 4 * kh + (r % 4)][j] = d3[t][r] + bias3[t];
+      for (int k = 0; k < 20; k++) {
+        const int u = 8 * (k / 4) + 4 * h + k % 4;
+        if (u < kOut) sw[col * kOut + u] = z[k];
       }
-    __builtin_amdgcn_s_waitcnt(0xc07f);
-    __builtin_amdgcn_wave_barrier();
-    // heads: lane i < 32 takes row i
-    if (lane < 32 && r0 + lane < a.n) {
-      const float *z = sz[wv][lane];
-      const int64_t rr = r0 + lane;
-      float bt = z[0], br = z[kCls];
-      int ct = 0, cr = 0;
-      for (int o = 1; o < kCls; o++)
-        if (z[o] > bt) {
-          bt = z[o];
-          ct = o;
-        }
-      for (int o = 1; o < kRng; o++)
-        if (z[kCls + o] > br) {
-          br = z[kCls + o];
-          cr = o;
-        }
-      a.cls[rr] = (int8_t)ct;
-      a.rng[rr] = (int8_t)cr;
-      if (a.conf) {
-        float den = 0.0f;
-        for (int o = 0; o < kCls; o++) den += expf(z[o] - bt);
-        a.conf[rr] = 1.0f / den;
-      }
-      if (a.logits)
-        for (int o = 0; o < kOut; o++) a.logits[rr * kOut + o] = z[o];
+      put_logits(sw, a.logits + r0 * kOut, rows, lane);
     }
-    __builtin_amdgcn_wave_barrier();
   }
 }
 
@@ -284,8 +362,6 @@ struct GradArgs {
   float *part;   // [ceil(n/128)][kParams + 1]: partial gradient sums, then the partial loss
   int split;     // blockIdx.y computes one layer's gradient (else every workgroup all three)
 };
-
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ f32x4 lds4(const float *p) { return *reinterpret_cast<const f32x4 *>(p); }
 
@@ -659,7 +735,7 @@ lfc_status infer_launch(const uint16_t *w, const float *x, int64_t n, int8_t *cl
   lfc_status st = mlp_launched("lfc_mlp_infer");
   if (st == LFC_OK) {
     const int64_t blocks = (n + kThreads - 1) / kThreads;   // n < 2^31 * 256, checked by the callers
-    InferArgs a{wf, x, n, cls, rng, conf, logits};
+    InferArgs a{w, wf, x, n, cls, rng, conf, logits};
     hipLaunchKernelGGL(k_mlp_infer, dim3((unsigned)blocks), dim3(kThreads), 0, s, a);
     st = mlp_launched("lfc_mlp_infer");
   }
@@ -693,9 +769,10 @@ extern "C" lfc_status lfc_mlp_infer_ex(const uint16_t *d_w, const float *d_x, in
   if (reinterpret_cast<uintptr_t>(d_w) % 16)
     return lfc::fail(LFC_E_INVALID, "lfc_mlp_infer: bf16 inference needs 16-byte aligned weights");
   const int64_t tiles = (n + 31) / 32;
-  const int64_t blocks = std::min<int64_t>((tiles + kMfmaWaves - 1) / kMfmaWaves, 4096);
-  InferArgs a{nullptr, d_x, n, d_cls, d_rng, d_conf, d_logits};
-  hipLaunchKernelGGL(k_mlp_infer_mfma, dim3((unsigned)blocks), dim3(64 * kMfmaWaves), 0, s, a, d_w);
+  const int64_t blocks = std::min<int64_t>((tiles + kMfmaWaves - 1) / kMfmaWaves, (int64_t)kMfmaWgs * kCus);
+  InferArgs a{d_w, nullptr, d_x, n, d_cls, d_rng, d_conf, d_logits};
+  hipLaunchKernelGGL(d_logits ? k_mlp_infer_mfma<true> : k_mlp_infer_mfma<false>, dim3((unsigned)blocks),
+                     dim3(64 * kMfmaWaves), 0, s, a);
   return mlp_launched(who);
 }
 
@@ -716,7 +793,7 @@ extern "C" lfc_status lfc_mlp_grad(const uint16_t *d_w, const float *d_x, const 
   // is what a small batch waits for (1,024 rows: 18.1 us split, 24.2 not;
   // 10,880: 21.0, 26.9).  Beyond that the repeated work costs throughput
   // (10,881 rows: 32.4 us split, 26.7 not; 60,000: 103, 61).
-  const bool split = 3 * nwg <= kSplitWgs;
+  const bool split = 3 * nwg <= kCus;
   GradArgs a{d_w, d_x, d_cls, d_rng, n, d_part, split};
   hipLaunchKernelGGL(k_mlp_grad, dim3(nwg, split ? 3 : 1), dim3(kGradThreads), kGradLds, s, a);
   if (lfc_status st = mlp_launched(who)) return st;

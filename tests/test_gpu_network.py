@@ -46,3 +46,68 @@ def test_gradient_at_tile_and_split_edges(gpu, n, offset):
     assert np.abs(got - g64).max() <= 1e-4 * max(1e-3, np.abs(g64).max())
     assert np.linalg.norm(got - g64) <= 1e-4 * np.linalg.norm(g64)
     assert (part[tiles * (lfc.MLP_PARAMS + 1):] == 7.0).all()      # the scratch past the tiles' partials is untouched
+
+
+# one row, a tile of 32 rows less / exact / more, a workgroup's 128, and counts
+# past one pass of the grid; with and without logits, with a view of the rows
+# that starts inside an allocation.  Tolerances: the bf16 path's of
+# test_gpu_control.py (2e-2 of the logits' scale at most, 1e-3 for 99 %); the
+# float32 path's there (1e-4).
+@pytest.mark.parametrize("n", [1, 31, 32, 33, 127, 129, 4097, 100_001])
+@pytest.mark.parametrize("bf16", [False, True])
+def test_inference_at_tile_edges(gpu, n, bf16):
+    say("mlp infer", n, bf16)
+    wt, w = net(21, 8)
+    x = np.random.default_rng(22).uniform(0, 1, (n, 16)).astype(np.float32)
+    buf = torch.from_numpy(np.concatenate([np.full((3, 16), 9.0, np.float32), x])).cuda()
+    prec = lfc.MLP_BF16 if bf16 else lfc.MLP_FP32
+    cls, rng, conf, z = lfc.mlp_infer(wt, buf[3:], logits=True, precision=prec)
+    cls2, rng2, conf2 = lfc.mlp_infer(wt, buf[3:], precision=prec)
+    assert torch.equal(cls, cls2) and torch.equal(rng, rng2) and torch.equal(conf, conf2)
+    z = z.cpu().numpy()
+    z64 = omlp.forward_bf16(w, x) if bf16 else omlp.forward(w, x)[0]
+    scale = max(1.0, float(np.abs(z64).max()))
+    err = np.abs(z - z64) / scale
+    if bf16:
+        assert err.max() <= 2e-2 and np.quantile(err, 0.99) <= 1e-3
+    else:
+        assert err.max() <= 1e-4
+    # the heads follow the kernel's own logits: ties to the lower class
+    assert np.array_equal(cls.cpu().numpy(), np.argmax(z[:, :10], axis=1))
+    assert np.array_equal(rng.cpu().numpy(), np.argmax(z[:, 10:], axis=1))
+    e = np.exp(z[:, :10].astype(np.float64) - z[:, :10].max(1, keepdims=True))
+    assert np.abs(conf.cpu().numpy() - 1.0 / e.sum(1)).max() <= 1e-5
+
+
+def in_order_argmax(z):
+    """One pass over the units: a later one wins only if it is greater."""
+    best = 0
+    for k in range(1, len(z)):
+        if z[k] > z[best]:
+            best = k
+    return best
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("special", [float("nan"), float("inf"), float("-inf")])
+def test_heads_take_units_in_order(gpu, bf16, special):
+    """Logits given by the last biases alone: all equal, one raised, or one of
+    them not finite; the decisions are those of one pass over the units."""
+    x = torch.rand(70, 16, device="cuda")
+    prec = lfc.MLP_BF16 if bf16 else lfc.MLP_FP32
+    pairs = [(None, None)] + [(None, k) for k in range(37)] + [(s, k) for s in range(37) for k in (0, 3, 4, 9, 10, 12, 31, 36)]
+    for s, k in pairs:
+        w = np.zeros(lfc.MLP_PARAMS, dtype=np.float32)
+        z = w[lfc.MLP_PARAMS - 37:]
+        if k is not None:
+            z[k] = 0.5
+        bits = control.to_bf16_bits(w)
+        if s is not None:
+            z[s] = special
+            bits[lfc.MLP_PARAMS - 37 + s] = {"nan": 0x7FC0, "inf": 0x7F80, "-inf": 0xFF80}[str(special)]
+        cls, rng, conf = lfc.mlp_infer(torch.from_numpy(bits.view(np.int16)).cuda(), x, precision=prec)
+        assert (cls == in_order_argmax(z[:10])).all() and (rng == in_order_argmax(z[10:])).all(), (s, k)
+        with np.errstate(invalid="ignore"):
+            want = 1.0 / np.exp(z[:10].astype(np.float64) - z[in_order_argmax(z[:10])]).sum()
+        got = conf.cpu().numpy()
+        assert np.isnan(got).all() if np.isnan(want) else np.abs(got - want).max() <= 1e-6, (s, k)
