@@ -5,17 +5,16 @@
 // range classes).  Parameters W1[64][16], b1[64], W2[64][64], b2[64],
 // W3[37][64], b3[37]; inference and gradients read them as bfloat16 and
 // accumulate in float32.  The network is tiny (7,653 parameters).
-// Inference runs one row per lane with the parameters, unpacked once per
-// call to float32, read through the scalar unit (they are the same for every
-// lane), so each multiply-add takes its weight from a scalar register; the
-// gradient kernel keeps all parameters and a tile of 128 rows' activations
-// in LDS and runs every contraction on the matrix cores.
+// Every contraction runs on the matrix cores: inference keeps the weights in
+// registers and takes 32 rows at a time, the gradient kernel keeps a tile of
+// 128 rows' activations in LDS.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <string>
+#include <type_traits>
 
 #include "internal.h"
 
@@ -38,112 +37,36 @@ __device__ __forceinline__ uint16_t f32_to_bf16(float f) {
   return (uint16_t)((u + 0x7FFFu + ((u >> 16) & 1u)) >> 16);
 }
 
-// ---------------------------------------------------------------------------
-// inference: one row per lane, parameters through the scalar unit
-// ---------------------------------------------------------------------------
-typedef const __attribute__((address_space(4))) float *uniform_f32;
-
-__global__ __launch_bounds__(kThreads) void k_mlp_unpack(const uint16_t *w, float *wf) {
-  const int i = blockIdx.x * kThreads + threadIdx.x;
-  if (i < kParams) wf[i] = bf16_to_f32(w[i]);
-}
-
 struct InferArgs {
   const uint16_t *w;
-  const float *wf;   // the parameters as float32 (k_mlp_unpack)
   const float *x;
   int64_t n;
   int8_t *cls, *rng;
   float *conf, *logits;
 };
 
-__global__ __launch_bounds__(kThreads) void k_mlp_infer(InferArgs a) {
-  const uniform_f32 sw = (uniform_f32)a.wf;
-  {
-    // one row per lane and no loop over rows, so that the parameter loads stay
-    // at their uses instead of being hoisted out of a loop into registers
-    const int64_t r = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (r >= a.n) return;
-    float x[kIn];
-    const float4 *xr = reinterpret_cast<const float4 *>(a.x + r * kIn);
-#pragma unroll
-    for (int k = 0; k < kIn / 4; k++) {
-      const float4 t = xr[k];
-      x[4 * k] = t.x;
-      x[4 * k + 1] = t.y;
-      x[4 * k + 2] = t.z;
-      x[4 * k + 3] = t.w;
-    }
-    float h1[kH];
-#pragma unroll
-    for (int j = 0; j < kH; j++) {
-      float acc = sw[oB1 + j];
-#pragma unroll
-      for (int k = 0; k < kIn; k++) acc += sw[oW1 + j * kIn + k] * x[k];
-      h1[j] = fmaxf(acc, 0.0f);
-    }
-    float h2[kH];
-#pragma unroll
-    for (int j = 0; j < kH; j++) {
-      float acc = sw[oB2 + j];
-#pragma unroll
-      for (int k = 0; k < kH; k++) acc += sw[oW2 + j * kH + k] * h1[k];
-      h2[j] = fmaxf(acc, 0.0f);
-    }
-    float z[kOut];
-#pragma unroll
-    for (int o = 0; o < kOut; o++) {
-      float acc = sw[oB3 + o];
-#pragma unroll
-      for (int k = 0; k < kH; k++) acc += sw[oW3 + o * kH + k] * h2[k];
-      z[o] = acc;
-    }
-    if (a.logits)
-#pragma unroll
-      for (int o = 0; o < kOut; o++) a.logits[r * kOut + o] = z[o];
-    // heads: argmax (ties to the lower class)
-    float best_t = z[0], best_r = z[kCls];
-    int ct = 0, cr = 0;
-#pragma unroll
-    for (int o = 1; o < kCls; o++)
-      if (z[o] > best_t) {
-        best_t = z[o];
-        ct = o;
-      }
-#pragma unroll
-    for (int o = 1; o < kRng; o++)
-      if (z[kCls + o] > best_r) {
-        best_r = z[kCls + o];
-        cr = o;
-      }
-    a.cls[r] = (int8_t)ct;
-    a.rng[r] = (int8_t)cr;
-    if (a.conf) {
-      float den = 0.0f;
-#pragma unroll
-      for (int o = 0; o < kCls; o++) den += expf(z[o] - best_t);
-      a.conf[r] = 1.0f / den;
-    }
-  }
-}
-
 // ---------------------------------------------------------------------------
 // inference on the matrix cores: bf16 operands, fp32 accumulation
 // ---------------------------------------------------------------------------
-// What bounds it: vector issue beside the matrix cores (the bias, ReLU and
-// rounding of 128 hidden values a row, the two heads), with the rows' 70 bytes
-// from and to HBM close behind.  Each wave runs tiles of 32 rows through
+// What bounds it: vector issue (the bias, ReLU and rounding of 128 hidden
+// values a row, the two heads), which overlaps the matrix products of other
+// waves only in part; the rows' 70 bytes from and to HBM would allow twice
+// the rate.  Each wave runs tiles of 32 rows through
 // v_mfma_f32_32x32x16_bf16 with the weights as the first operand (units x
 // rows): lane l supplies unit l%32 with K elements 8 (l/32)..+7 and row l%32
 // with the same K elements, and receives units 8 (r/4) + 4 (l/32) + r%4 of row
 // l%32 in its register r.  A row's values thus stay in its two lanes l and
-// l+32: after the bias and the ReLU they are rounded and packed, and one
-// exchange of register halves between the two lanes per pair of packed words
-// (v_permlane32_swap) gives the next layer's operand with its K elements in
-// their order, so no layer goes through LDS.  The weights stay in registers
-// for the wave's life, the biases are read from LDS, and the next tile's
-// features are requested before this tile's layers.
-// Measured over 18.2 M rows: @BF16@
+// l+32: after the bias they are rounded and packed, clamped at zero two at a
+// time, and one exchange of register halves between the two lanes per pair of
+// packed words (v_permlane32_swap) gives the next layer's operand with its K
+// elements in their order, so no layer goes through LDS.  The weights stay in
+// registers for the wave's life, the biases are read from LDS, and the next
+// tile's features are requested before this tile's layers.  (The bias as a
+// product with one, in an fp32 MFMA, costs more than the additions: those
+// share the vector unit.)
+// Measured over 18.2 M rows: 456 us, 2.8 TB/s of rows (936 us with each layer's
+// output exchanged through LDS and the heads on half of the lanes); four waves
+// per SIMD with part of the weights in LDS 504 us, two 490 us.
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -155,27 +78,55 @@ __device__ __forceinline__ bf16x8 load_bf16x8(const uint16_t *p) {
   return __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(p));
 }
 
-// A head's running argmax.  A later unit wins only with a larger logit, so
-// ties go to the lower class; where lanes hold parts of a row, the lane of the
-// head's first unit starts from that unit's logit and the others from -inf, as
-// one pass over the units in order would.
-struct Best {
-  float v;
-  int i;
-  __device__ __forceinline__ void take(float z, int k) {
-    const bool g = z > v;
-    v = g ? z : v;
-    i = g ? k : i;
-  }
-  // the other lane's part: the larger logit, on equality the lower class
-  __device__ __forceinline__ void join(int mask) {
-    const float ov = __shfl_xor(v, mask);
-    const int oi = __shfl_xor(i, mask);
-    const bool g = ov > v || (ov == v && oi < i);
-    v = g ? ov : v;
-    i = g ? oi : i;
-  }
-};
+// op of a value over the lanes whose numbers differ in the bits from LOW up
+// (through LDS: the register exchanges between halves cost more issue).
+template <int LOW, typename T, typename Op>
+__device__ __forceinline__ T across(T v, Op op) {
+#pragma unroll
+  for (int d = 32; d >= LOW; d >>= 1) v = op(v, __shfl_xor(v, d));
+  return v;
+}
+
+// Argmax of a head whose logits are spread over the lanes of a row (which
+// differ in the bits from LOW up), as one pass over its units in order gives
+// it: a unit wins only with a larger logit, so ties go to the lower class and
+// a NaN loses, unless it is the first unit's.  z: this lane's logits, -inf
+// where it has none; at: each one's class less shift, rising.  holds: this
+// lane has the head's first unit, z[first].  m: the row's largest logit.
+template <int N, int LOW>
+__device__ __forceinline__ int head_argmax(const float (&z)[N], const int (&at)[N], int shift, int first, bool holds,
+                                           float &m) {
+  m = z[0];
+#pragma unroll
+  for (int k = 1; k + 1 < N; k += 2) m = fmaxf(fmaxf(z[k], z[k + 1]), m);
+  if constexpr (N % 2 == 0) m = fmaxf(m, z[N - 1]);
+  m = across<LOW>(m, [](float u, float v) { return fmaxf(u, v); });
+  int i = 64;
+#pragma unroll
+  for (int k = N - 1; k >= 0; k--) i = z[k] == m ? at[k] : i;
+  if (holds && z[first] != z[first]) i = -64;
+  i = across<LOW>(i + shift, [](int u, int v) { return min(u, v); });
+  return max(i, 0);   // (below 0: the first unit's NaN, or no logit above -inf)
+}
+
+// 1 / x for 1 <= x <= 10 (a softmax denominator): the hardware reciprocal and
+// one Newton step.
+__device__ __forceinline__ float recip(float x) {
+  const float r = __builtin_amdgcn_rcpf(x);
+  return __builtin_fmaf(__builtin_fmaf(-x, r, 1.0f), r, r);
+}
+
+// e^x for x <= 0 as 2^(x log2 e): the product's rounding moves the result by
+// at most |x| e^x 2^-24, below 3e-8 of a softmax sum.
+__device__ __forceinline__ float exp_neg(float x) { return __builtin_amdgcn_exp2f(x * 1.44269504f); }
+
+// The wave's 32 x 37 logits, staged in LDS as the output holds them.
+__device__ __forceinline__ void put_logits(const float *sz, float *out, int rows, int lane) {
+  __builtin_amdgcn_s_waitcnt(0xc07f);   // this wave's LDS writes are done
+  __builtin_amdgcn_wave_barrier();
+  for (int i = lane; i < rows * kOut; i += 64) out[i] = sz[i];
+  __builtin_amdgcn_wave_barrier();
+}
 
 // The biases as float32 in LDS, zero past the last unit of a layer.
 __device__ __forceinline__ void load_biases(const uint16_t *w, float (*sb)[kH]) {
@@ -184,14 +135,6 @@ __device__ __forceinline__ void load_biases(const uint16_t *w, float (*sb)[kH]) 
     sb[l][j] = l == 0 ? bf16_to_f32(w[oB1 + j]) : (l == 1 ? bf16_to_f32(w[oB2 + j]) : (j < kOut ? bf16_to_f32(w[oB3 + j]) : 0.0f));
   }
   __syncthreads();
-}
-
-// The wave's 32 x 37 logits, staged in LDS as the output holds them.
-__device__ __forceinline__ void put_logits(const float *sz, float *out, int rows, int lane) {
-  __builtin_amdgcn_s_waitcnt(0xc07f);   // this wave's LDS writes are done
-  __builtin_amdgcn_wave_barrier();
-  for (int i = lane; i < rows * kOut; i += 64) out[i] = sz[i];
-  __builtin_amdgcn_wave_barrier();
 }
 
 template <bool LOGITS>
@@ -215,8 +158,21 @@ __global__ __launch_bounds__(64 * kMfmaWaves, kMfmaWgs) void k_mlp_infer_mfma(In
       w3[ks][t] = j < kOut ? load_bf16x8(a.w + oW3 + j * kH + ks * 16 + h * 8) : zero8;
     }
   }
-  // bias, ReLU, rounding to bf16, and the next layer's operand of each K step
-  auto next_operand = [&](const f32x16 (&d)[2], const float *b, bf16x8 (&o)[4]) {
+  auto products = [&](const bf16x8 (&w)[4][2], const bf16x8 (&x)[4], f32x16 (&d)[2]) {
+    d[0] = d[1] = f32x16{};
+#pragma unroll
+    for (int ks = 0; ks < 4; ks++)
+#pragma unroll
+      for (int t = 0; t < 2; t++) d[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[ks][t], x[ks], d[t], 0, 0, 0);
+  };
+  // bias, ReLU, rounding to bf16, and the next layer's operand of each K
+  // step.  The ReLU takes a NaN to 0.  FAST clamps the rounded pairs as signed
+  // 16-bit numbers instead, which keeps a positive NaN: it makes every logit of
+  // its row NaN, and the tile is then done again without FAST.
+  auto next_operand = [&](auto fast, const f32x16 (&d)[2], const float *b, bf16x8 (&o)[4]) {
+    constexpr bool FAST = decltype(fast)::value;
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    typedef short i16x2 __attribute__((ext_vector_type(2)));
 #pragma unroll
     for (int ks = 0; ks < 4; ks++) {
       uint32_t pk[4];   // units 16 ks + 4 h ..+3, then 16 ks + 8 + 4 h ..+3
@@ -225,10 +181,16 @@ __global__ __launch_bounds__(64 * kMfmaWaves, kMfmaWgs) void k_mlp_infer_mfma(In
         const f32x4 bb = *reinterpret_cast<const f32x4 *>(b + 16 * ks + 8 * g);
 #pragma unroll
         for (int p = 0; p < 2; p++) {
-          typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
           const int r = 8 * (ks & 1) + 4 * g + 2 * p;
-          const bf16x2 v = {(__bf16)fmaxf(d[ks >> 1][r] + bb[2 * p], 0.0f), (__bf16)fmaxf(d[ks >> 1][r + 1] + bb[2 * p + 1], 0.0f)};
-          pk[2 * g + p] = __builtin_bit_cast(uint32_t, v);
+          float v0 = d[ks >> 1][r] + bb[2 * p], v1 = d[ks >> 1][r + 1] + bb[2 * p + 1];
+          if constexpr (!FAST) v0 = fmaxf(v0, 0.0f), v1 = fmaxf(v1, 0.0f);
+          const bf16x2 v = {(__bf16)v0, (__bf16)v1};
+          uint32_t w = __builtin_bit_cast(uint32_t, v);
+          if constexpr (FAST) {
+            asm("" : "+v"(w));   // (keeps the two conversions one packed one)
+            w = __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(i16x2, w), i16x2{0, 0}));
+          }
+          pk[2 * g + p] = w;
         }
       }
       // lane l keeps units 16 ks ..+7, lane l + 32 units 16 ks + 8 ..+7
@@ -247,85 +209,292 @@ __global__ __launch_bounds__(64 * kMfmaWaves, kMfmaWgs) void k_mlp_infer_mfma(In
       xv = *reinterpret_cast<const f32x4 *>(a.x + row * kIn + h * 8 + 4);
     }
   };
-  int64_t tile = (int64_t)blockIdx.x * kMfmaWaves + wv;
-  request(tile);
-  for (; tile < tiles; tile += stride) {
-    bf16x8 x;
+  bf16x8 x;
+  auto take_request = [&] {
 #pragma unroll
     for (int k = 0; k < 4; k++) x[k] = (__bf16)xu[k], x[4 + k] = (__bf16)xv[k];
+  };
+  int64_t tile = (int64_t)blockIdx.x * kMfmaWaves + wv;
+  request(tile);
+  take_request();
+  for (; tile < tiles; tile += stride) {
     request(tile + stride);
-    // (the biases are read anew for each tile: kept in registers, their 160
-    // values would halve the waves per SIMD)
-    int hb = 4 * h;
-    asm volatile("" : "+v"(hb));
-    const float *bias = &sb[0][0] + hb;
-    f32x16 d[2] = {{}, {}};
-    bf16x8 o[4];
+    f32x16 d[2];
+    auto layers = [&](auto fast) {
+      // (the biases are read anew for each tile: kept in registers, their 160
+      // values would halve the waves per SIMD)
+      int hb = 4 * h;
+      asm volatile("" : "+v"(hb));
+      const float *bias = &sb[0][0] + hb;
+      bf16x8 o[4];
 #pragma unroll
-    for (int t = 0; t < 2; t++) d[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w1[t], x, d[t], 0, 0, 0);
-    next_operand(d, bias, o);
-    d[0] = d[1] = f32x16{};
+      for (int t = 0; t < 2; t++) d[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w1[t], x, f32x16{}, 0, 0, 0);
+      next_operand(fast, d, bias, o);
+      products(w2, o, d);
+      next_operand(fast, d, bias + kH, o);
+      products(w3, o, d);
 #pragma unroll
-    for (int ks = 0; ks < 4; ks++)
+      for (int g = 0; g < 5; g++) {
+        const f32x4 bb = *reinterpret_cast<const f32x4 *>(bias + 2 * kH + 8 * g);
 #pragma unroll
-      for (int t = 0; t < 2; t++) d[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w2[ks][t], o[ks], d[t], 0, 0, 0);
-    next_operand(d, bias + kH, o);
-    d[0] = d[1] = f32x16{};
-#pragma unroll
-    for (int ks = 0; ks < 4; ks++)
-#pragma unroll
-      for (int t = 0; t < 2; t++) d[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w3[ks][t], o[ks], d[t], 0, 0, 0);
-    // this lane's logits of its row: units 8 g + 4 h + j (z[4 g + j]), g = 0..4; past unit 36 none
-    float z[20];
-#pragma unroll
-    for (int g = 0; g < 5; g++) {
-      const f32x4 bb = *reinterpret_cast<const f32x4 *>(bias + 2 * kH + 8 * g);
-#pragma unroll
-      for (int j = 0; j < 4; j++) z[4 * g + j] = d[g >> 2][(4 * g + j) & 15] + bb[j];
-    }
+        for (int j = 0; j < 4; j++) d[g >> 2][(4 * g + j) & 15] += bb[j];
+      }
+    };
+    layers(std::true_type{});
+    if (__builtin_expect(__any(d[0][0] != d[0][0]), 0)) layers(std::false_type{});
+    // this lane's logits of its row: units 8 g + 4 h + j (d[0][4 g + j]), g = 0..3, and 32 + 4 h + j
     const int64_t r0 = tile * 32;
     const int rows = (int)min((int64_t)32, a.n - r0);
     const float ninf = -__builtin_inff();
     // threshold head: units 0..9 (lane l: 0-3, 8, 9; lane l + 32: 4-7)
-    Best c = {h ? ninf : z[0], 0};
+    const float zc[6] = {d[0][0], d[0][1], d[0][2], d[0][3], h ? ninf : d[0][4], h ? ninf : d[0][5]};
+    constexpr int ic[6] = {0, 1, 2, 3, 8, 9};
+    float mc, mr;
+    const int c = head_argmax<6, 32>(zc, ic, 4 * h, 0, !h, mc);
+    // range head: units 10..36 (lane l: 10, 11, 16-19, 24-27, 32-35; lane l + 32: 12-15, 20-23, 28-31, 36)
+    const float zr[16] = {h ? d[0][4] : ninf, h ? d[0][5] : ninf, d[0][6], d[0][7], d[0][8], d[0][9], d[0][10], d[0][11],
+                          d[0][12], d[0][13], d[0][14], d[0][15], d[1][0], h ? ninf : d[1][1], h ? ninf : d[1][2],
+                          h ? ninf : d[1][3]};
+    constexpr int ir[16] = {-2, -1, 0, 1, 6, 7, 8, 9, 14, 15, 16, 17, 22, 23, 24, 25};
+    const int q = head_argmax<16, 32>(zr, ir, 4 * h, 2, !h, mr);
+    float den = 0.0f;
 #pragma unroll
-    for (int j = 0; j < 4; j++) c.take(z[j], 4 * h + j);
-#pragma unroll
-    for (int j = 4; j < 6; j++) c.take(h ? ninf : z[j], 4 + j);
-    // range head: units 10..36 (lane l: 10, 11, then groups of four; lane l + 32: 12-15, ..., 36)
-    Best q = {h ? ninf : z[6], 0};
-#pragma unroll
-    for (int j = 4; j < 6; j++) q.take(h ? z[j] : ninf, j - 2);
-#pragma unroll
-    for (int j = 6; j < 8; j++) q.take(z[j], 4 * h + j - 6);
-#pragma unroll
-    for (int j = 8; j < 16; j++) q.take(z[j], (j / 4) * 8 + j % 4 + 4 * h - kCls);
-    q.take(z[16], 32 + 4 * h - kCls);
-#pragma unroll
-    for (int j = 17; j < 20; j++) q.take(h ? ninf : z[j], 32 + j - 16 - kCls);
-    c.join(32);
-    q.join(32);
-    if (a.conf) {
-      float den = 0.0f;
-#pragma unroll
-      for (int j = 0; j < 4; j++) den += expf(z[j] - c.v);
-#pragma unroll
-      for (int j = 4; j < 6; j++) den += expf((h ? ninf : z[j]) - c.v);
-      den += __shfl_xor(den, 32);
-      if (!h && col < rows) a.conf[r0 + col] = 1.0f / den;
-    }
+    for (int j = 0; j < 6; j++) den += exp_neg(zc[j] - mc);
+    den = across<32>(den, [](float u, float v) { return u + v; });
+    // the next tile's features are taken before this tile's stores: a wait for
+    // loads also waits for every store issued before it is reached
+    take_request();
+    __builtin_amdgcn_sched_barrier(0);
+    if (a.conf && !h && col < rows) a.conf[r0 + col] = recip(den);
     if (!h && col < rows) {
-      a.cls[r0 + col] = (int8_t)c.i;
-      a.rng[r0 + col] = (int8_t)q.i;
+      a.cls[r0 + col] = (int8_t)c;
+      a.rng[r0 + col] = (int8_t)q;
     }
     if constexpr (LOGITS) {
       float *sw = sz[wv];
 #pragma unroll
       for (int k = 0; k < 20; k++) {
         const int u = 8 * (k / 4) + 4 * h + k % 4;
-        if (u < kOut) sw[col * kOut + u] = z[k];
+        if (u < kOut) sw[col * kOut + u] = d[k >> 4][k & 15];
       }
       put_logits(sw, a.logits + r0 * kOut, rows, lane);
+    }
+  }
+}
+
+// The parameters as bf16 in LDS.  The weights' row strides put the rows of an
+// operand in different banks.
+constexpr int kLdW1 = kIn + 4, kLdW = kH + 4;
+constexpr int kLdsW = kH * kLdW1 + (kH + kOut) * kLdW + 2 * kH + kOut + 1;
+struct LdsWeights {
+  uint16_t *w1, *w2, *w3, *b1, *b2, *b3;   // [kH][kLdW1], [kH][kLdW], [kOut][kLdW], biases
+  __device__ explicit LdsWeights(uint16_t *p)
+      : w1(p), w2(w1 + kH * kLdW1), w3(w2 + kH * kLdW), b1(w3 + kOut * kLdW), b2(b1 + kH), b3(b2 + kH) {}
+  // two parameters at a time (every part starts at an even offset); T threads
+  template <int T>
+  __device__ __forceinline__ void fill(const uint16_t *w, int t) const {
+    const bool words = reinterpret_cast<uintptr_t>(w) % 4 == 0;
+    auto copy2 = [&](uint16_t *dst, int o) {
+      *reinterpret_cast<uint32_t *>(dst) =
+          words ? *reinterpret_cast<const uint32_t *>(w + o) : (uint32_t)w[o] | (uint32_t)w[o + 1] << 16;
+    };
+#pragma unroll
+    for (int i = t; i < kH * kIn / 2; i += T) copy2(w1 + i / (kIn / 2) * kLdW1 + i % (kIn / 2) * 2, oW1 + 2 * i);
+#pragma unroll
+    for (int i = t; i < kH * kH / 2; i += T) copy2(w2 + i / (kH / 2) * kLdW + i % (kH / 2) * 2, oW2 + 2 * i);
+#pragma unroll
+    for (int i = t; i < kOut * kH / 2; i += T) copy2(w3 + i / (kH / 2) * kLdW + i % (kH / 2) * 2, oW3 + 2 * i);
+    if (t < kH / 2) copy2(b1 + 2 * t, oB1 + 2 * t);
+    else if (t < kH) copy2(b2 + 2 * (t - kH / 2), oB2 + 2 * (t - kH / 2));
+    else if (t < kH + kOut) b3[t - kH] = w[oB3 + t - kH];
+  }
+};
+
+// ---------------------------------------------------------------------------
+// inference in float32
+// ---------------------------------------------------------------------------
+// What bounds it: the fp32 matrix rate (the fp32 MFMAs share the vector unit,
+// so the heads and the ReLU add to it).  Each wave runs tiles of 32 rows with
+// the weights, widened to float32, as the first operand: layers 1 and 2 through
+// v_mfma_f32_32x32x2_f32, layer 3 (37 units) through v_mfma_f32_16x16x4_f32,
+// which pads it to 48 units instead of 64.  An fp32 MFMA accumulates its K
+// elements as a chain of fused multiply-adds, so with the bias as the initial
+// value and K in order a logit has the bits of a loop of fmas over the units.
+// As in the bf16 kernel a row's values stay in its lanes; exchanges of register
+// halves and quarters put the K elements where the next product wants them.
+// The 128 weight registers allow two waves per SIMD, which fill the unit.
+// Measured over 1.57 M rows: 229 us, 103 TFLOP/s (394 us with one row per lane
+// and the weights through the scalar unit: unpacked fp32 fmas reach half of
+// the matrix rate).
+constexpr int kF32Wgs = 2;   // workgroups per compute unit that the registers allow
+
+// max(x, 0), a NaN to 0, as one operation: the median of x, 0 and infinity
+// (fmaxf of a matrix product is canonicalised by a second operation first, as
+// is a median whose infinity the compiler can see)
+__device__ __forceinline__ float opaque_inf() {
+  float v = __builtin_inff();
+  asm("" : "+s"(v));
+  return v;
+}
+__device__ __forceinline__ void swap32(float &u, float &v) {
+  const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(u), __float_as_uint(v), false, false);
+  u = __uint_as_float(s[0]);
+  v = __uint_as_float(s[1]);
+}
+__device__ __forceinline__ void swap16(float &u, float &v) {
+  const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(u), __float_as_uint(v), false, false);
+  u = __uint_as_float(s[0]);
+  v = __uint_as_float(s[1]);
+}
+
+template <bool LOGITS>
+__global__ __launch_bounds__(64 * kMfmaWaves, kF32Wgs) void k_mlp_infer(InferArgs a) {
+  __shared__ __attribute__((aligned(16))) uint16_t sw[kLdsW];
+  __shared__ __attribute__((aligned(16))) float sb[3][kH];
+  __shared__ float sz[LOGITS ? kMfmaWaves : 1][LOGITS ? 32 * kOut : 1];
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int col = lane & 31, h = lane >> 5, c16 = lane & 15, kq = lane >> 4;
+  const float inf = opaque_inf(), ninf = -inf;
+  const LdsWeights lw(sw);
+  lw.fill<64 * kMfmaWaves>(a.w, threadIdx.x);
+  load_biases(a.w, sb);
+  float w1[2][kIn / 2], w2[2][kH / 2], w3[3][kH / 4];
+#pragma unroll
+  for (int t = 0; t < 2; t++) {
+#pragma unroll
+    for (int s = 0; s < kIn / 2; s++) w1[t][s] = bf16_to_f32(lw.w1[(t * 32 + col) * kLdW1 + 2 * s + h]);
+#pragma unroll
+    for (int s = 0; s < kH / 2; s++) w2[t][s] = bf16_to_f32(lw.w2[(t * 32 + col) * kLdW + 2 * s + h]);
+  }
+#pragma unroll
+  for (int t = 0; t < 3; t++)
+#pragma unroll
+    for (int s = 0; s < kH / 4; s++)
+      w3[t][s] = t * 16 + c16 < kOut ? bf16_to_f32(lw.w3[min(t * 16 + c16, kOut - 1) * kLdW + 4 * s + kq]) : 0.0f;
+  const int64_t tiles = (a.n + 31) / 32, stride = (int64_t)gridDim.x * kMfmaWaves;
+  f32x4 xu = {}, xv = {};   // this lane's half of its row, requested a tile ahead
+  auto request = [&](int64_t tile) {
+    const int64_t row = tile * 32 + col;
+    if (row < a.n) {
+      xu = *reinterpret_cast<const f32x4 *>(a.x + row * kIn + h * 8);
+      xv = *reinterpret_cast<const f32x4 *>(a.x + row * kIn + h * 8 + 4);
+    }
+  };
+  float x[kIn / 2];   // features 2 s + h of row col
+  auto take_request = [&] {
+    float u[8] = {xu[0], xu[1], xu[2], xu[3], xv[0], xv[1], xv[2], xv[3]};
+#pragma unroll
+    for (int p = 0; p < 4; p++) {
+      swap32(u[2 * p], u[2 * p + 1]);
+      x[p] = u[2 * p];
+      x[4 + p] = u[2 * p + 1];
+    }
+  };
+  int64_t tile = (int64_t)blockIdx.x * kMfmaWaves + wv;
+  request(tile);
+  take_request();
+  for (; tile < tiles; tile += stride) {
+    request(tile + stride);
+    int hb = 4 * h, kb = 4 * kq;   // (the biases are read anew for each tile, not kept in registers)
+    asm volatile("" : "+v"(hb), "+v"(kb));
+    auto bias_tile = [&](int l, int t) {
+      f32x16 d;
+#pragma unroll
+      for (int g = 0; g < 4; g++) {
+        const f32x4 b = *reinterpret_cast<const f32x4 *>(&sb[l][0] + hb + t * 32 + 8 * g);
+#pragma unroll
+        for (int j = 0; j < 4; j++) d[4 * g + j] = b[j];
+      }
+      return d;
+    };
+    f32x16 d[2] = {bias_tile(0, 0), bias_tile(0, 1)};
+#pragma unroll
+    for (int s = 0; s < kIn / 2; s++)
+#pragma unroll
+      for (int t = 0; t < 2; t++) d[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(w1[t][s], x[s], d[t], 0, 0, 0);
+    f32x16 e[2] = {bias_tile(1, 0), bias_tile(1, 1)};
+    float v[kH / 2];   // units 2 s + h of row col
+#pragma unroll
+    for (int t = 0; t < 2; t++)
+#pragma unroll
+      for (int g = 0; g < 4; g++) {
+        float u[4];
+#pragma unroll
+        for (int j = 0; j < 4; j++) u[j] = __builtin_amdgcn_fmed3f(d[t][4 * g + j], 0.0f, inf);
+        swap32(u[0], u[1]);
+        swap32(u[2], u[3]);
+        float *o = v + 16 * t + 4 * g;
+        o[0] = u[0], o[1] = u[2], o[2] = u[1], o[3] = u[3];
+      }
+#pragma unroll
+    for (int s = 0; s < kH / 2; s++)
+#pragma unroll
+      for (int t = 0; t < 2; t++) e[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(w2[t][s], v[s], e[t], 0, 0, 0);
+    // layer 3: rows 16 nt..+15, unit tile t; lane = row c16, K quarter kq
+    f32x4 z[2][3];
+#pragma unroll
+    for (int t = 0; t < 3; t++) z[0][t] = z[1][t] = *reinterpret_cast<const f32x4 *>(&sb[2][0] + kb + 16 * t);
+#pragma unroll
+    for (int g = 0; g < 8; g++) {
+      float u[4];
+#pragma unroll
+      for (int j = 0; j < 4; j++) u[j] = __builtin_amdgcn_fmed3f(e[g >> 2][4 * (g & 3) + j], 0.0f, inf);
+      swap32(u[0], u[2]);
+      swap32(u[1], u[3]);
+      swap16(u[0], u[1]);
+      swap16(u[2], u[3]);
+#pragma unroll
+      for (int k = 0; k < 2; k++)
+#pragma unroll
+        for (int t = 0; t < 3; t++)
+#pragma unroll
+          for (int nt = 0; nt < 2; nt++)
+            z[nt][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(w3[t][2 * g + k], u[2 * k + nt], z[nt][t], 0, 0, 0);
+    }
+    // heads: this lane's logits of rows c16 and 16 + c16 are units 16 t + 4 kq + r
+    const int64_t r0 = tile * 32;
+    const int rows = (int)min((int64_t)32, a.n - r0);
+    int cls[2], rng[2];
+    float den[2];
+#pragma unroll
+    for (int nt = 0; nt < 2; nt++) {
+      float zc[4], zr[12];
+#pragma unroll
+      for (int r = 0; r < 4; r++) {
+        const bool is_cls = 4 * kq + r < kCls;
+        zc[r] = is_cls ? z[nt][0][r] : ninf;
+        zr[r] = is_cls ? ninf : z[nt][0][r];
+        zr[4 + r] = z[nt][1][r];
+        zr[8 + r] = 32 + 4 * kq + r < kOut ? z[nt][2][r] : ninf;
+      }
+      constexpr int ic[4] = {0, 1, 2, 3}, ir[12] = {-10, -9, -8, -7, 6, 7, 8, 9, 22, 23, 24, 25};
+      float mc, mr;
+      cls[nt] = head_argmax<4, 16>(zc, ic, 4 * kq, 0, kq == 0, mc);
+      rng[nt] = head_argmax<12, 16>(zr, ir, 4 * kq, 2, kq == 2, mr);
+      float s = 0.0f;
+#pragma unroll
+      for (int r = 0; r < 4; r++) s += exp_neg(zc[r] - mc);
+      den[nt] = across<16>(s, [](float p, float q) { return p + q; });
+    }
+    // the next tile's features are taken before this tile's stores: a wait for
+    // loads also waits for every store issued before it is reached
+    take_request();
+    __builtin_amdgcn_sched_barrier(0);
+    if (lane < rows) {   // (lane < 32: row lane, of half kq)
+      a.cls[r0 + lane] = (int8_t)(kq ? cls[1] : cls[0]);
+      a.rng[r0 + lane] = (int8_t)(kq ? rng[1] : rng[0]);
+      if (a.conf) a.conf[r0 + lane] = recip(kq ? den[1] : den[0]);
+    }
+    if constexpr (LOGITS) {
+      float *so = sz[wv];
+#pragma unroll
+      for (int nt = 0; nt < 2; nt++)
+#pragma unroll
+        for (int t = 0; t < 3; t++)
+#pragma unroll
+          for (int r = 0; r < 4; r++)
+            if (16 * t + 4 * kq + r < kOut) so[(16 * nt + c16) * kOut + 16 * t + 4 * kq + r] = z[nt][t][r];
+      put_logits(so, a.logits + r0 * kOut, rows, lane);
     }
   }
 }
@@ -350,8 +519,6 @@ __global__ __launch_bounds__(64 * kMfmaWaves, kMfmaWgs) void k_mlp_infer_mfma(In
 constexpr int kGradThreads = 512;
 constexpr int kLd = kH + 4;     // row stride of the activations and deltas
 constexpr int kLdX = kIn + 4;   // row stride of the features
-constexpr int kLdW1 = kIn + 4, kLdW = kH + 4;   // row strides of the bf16 weights in LDS (an operand's 32 rows in 32 bank pairs)
-constexpr int kLdsW = kH * kLdW1 + (kH + kOut) * kLdW + 2 * kH + kOut + 1;   // bf16 parameters in LDS
 constexpr int kRedTile = 16 * 64 + 64;      // one wave's tile and its column sums
 
 struct GradArgs {
@@ -415,29 +582,13 @@ __global__ __launch_bounds__(kGradThreads) void k_mlp_grad(GradArgs a) {
   float *Z = H2 + kTile * kLd;           // [kTile][kLd], dL/dz, zero from column 37
   float *red = Z + kTile * kLd;          // [4][kRedTile] tiles of the second row halves
   float *rloss = red + 4 * kRedTile;     // [8] loss of each wave's rows
-  uint16_t *sw1 = reinterpret_cast<uint16_t *>(rloss + 8);   // the parameters: [kH][kLdW1], [kH][kLdW], [kOut][kLdW]
-  uint16_t *sw2 = sw1 + kH * kLdW1, *sw3 = sw2 + kH * kLdW, *sb1 = sw3 + kOut * kLdW, *sb2 = sb1 + kH, *sb3 = sb2 + kH;
+  uint16_t *sw = reinterpret_cast<uint16_t *>(rloss + 8);   // the parameters
   const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int r0 = blockIdx.x * kTile, rows = min(kTile, a.n - r0);
   const int roles = a.split ? 1 << blockIdx.y : 7;   // 1: layer 3 and the loss, 2: layer 2, 4: layer 1
   const float inv_n = 1.0f / (float)a.n;
-  {
-    // two parameters at a time (every part starts at an even offset)
-    const bool words = reinterpret_cast<uintptr_t>(a.w) % 4 == 0;
-    auto copy2 = [&](uint16_t *dst, int o) {
-      *reinterpret_cast<uint32_t *>(dst) =
-          words ? *reinterpret_cast<const uint32_t *>(a.w + o) : (uint32_t)a.w[o] | (uint32_t)a.w[o + 1] << 16;
-    };
-#pragma unroll
-    for (int i = t; i < kH * kIn / 2; i += kGradThreads) copy2(sw1 + i / (kIn / 2) * kLdW1 + i % (kIn / 2) * 2, oW1 + 2 * i);
-#pragma unroll
-    for (int i = t; i < kH * kH / 2; i += kGradThreads) copy2(sw2 + i / (kH / 2) * kLdW + i % (kH / 2) * 2, oW2 + 2 * i);
-#pragma unroll
-    for (int i = t; i < kOut * kH / 2; i += kGradThreads) copy2(sw3 + i / (kH / 2) * kLdW + i % (kH / 2) * 2, oW3 + 2 * i);
-    if (t < kH / 2) copy2(sb1 + 2 * t, oB1 + 2 * t);
-    else if (t < kH) copy2(sb2 + 2 * (t - kH / 2), oB2 + 2 * (t - kH / 2));
-    else if (t < kH + kOut) sb3[t - kH] = a.w[oB3 + t - kH];
-  }
+  const LdsWeights lw(sw);
+  lw.fill<kGradThreads>(a.w, t);
 #pragma unroll
   for (int i = t; i < kTile * kIn; i += kGradThreads) {
     const int r = i / kIn;
@@ -469,26 +620,26 @@ __global__ __launch_bounds__(kGradThreads) void k_mlp_grad(GradArgs a) {
     return d;
   };
   {
-    f32x16 d = bias_units(sb1);
+    f32x16 d = bias_units(lw.b1);
 #pragma unroll
     for (int c = 0; c < kIn / 8; c++) {
       const f32x4 b = lds4(X + row * kLdX + 8 * c + 4 * h);
 #pragma unroll
       for (int j = 0; j < 4; j++)
-        d = __builtin_amdgcn_mfma_f32_32x32x2f32(bf16_to_f32(sw1[(ut * 32 + col) * kLdW1 + 8 * c + 4 * h + j]), b[j],
+        d = __builtin_amdgcn_mfma_f32_32x32x2f32(bf16_to_f32(lw.w1[(ut * 32 + col) * kLdW1 + 8 * c + 4 * h + j]), b[j],
                                                  d, 0, 0, 0);
     }
     store_units(H1, d);
   }
   __syncthreads();
   {
-    f32x16 d = bias_units(sb2);
+    f32x16 d = bias_units(lw.b2);
 #pragma unroll
     for (int c = 0; c < kH / 8; c++) {
       const f32x4 b = lds4(H1 + row * kLd + 8 * c + 4 * h);
 #pragma unroll
       for (int j = 0; j < 4; j++)
-        d = __builtin_amdgcn_mfma_f32_32x32x2f32(bf16_to_f32(sw2[(ut * 32 + col) * kLdW + 8 * c + 4 * h + j]), b[j],
+        d = __builtin_amdgcn_mfma_f32_32x32x2f32(bf16_to_f32(lw.w2[(ut * 32 + col) * kLdW + 8 * c + 4 * h + j]), b[j],
                                                  d, 0, 0, 0);
     }
     store_units(H2, d);
@@ -504,7 +655,7 @@ __global__ __launch_bounds__(kGradThreads) void k_mlp_grad(GradArgs a) {
 #pragma unroll
       for (int r = 0; r < 4; r++) {
         const int o = 16 * tt + 4 * kq + r;
-        z[tt][r] = o < kOut ? bf16_to_f32(sb3[o]) : 0.0f;
+        z[tt][r] = o < kOut ? bf16_to_f32(lw.b3[o]) : 0.0f;
       }
 #pragma unroll
     for (int c = 0; c < kH / 16; c++) {
@@ -514,15 +665,11 @@ __global__ __launch_bounds__(kGradThreads) void k_mlp_grad(GradArgs a) {
 #pragma unroll
         for (int tt = 0; tt < 3; tt++) {
           const int o = 16 * tt + c16;
-          const float w = o < kOut ? bf16_to_f32(sw3[o * kLdW + 16 * c + 4 * kq + j]) : 0.0f;
+          const float w = o < kOut ? bf16_to_f32(lw.w3[o * kLdW + 16 * c + 4 * kq + j]) : 0.0f;
           z[tt] = __builtin_amdgcn_mfma_f32_16x16x4f32(w, b[j], z[tt], 0, 0, 0);
         }
     }
-    // a row's 37 logits are spread over the four lanes c16 + 16 kq
-    auto across = [&](float v, auto op) {
-      v = op(v, __shfl_xor(v, 16));
-      return op(v, __shfl_xor(v, 32));
-    };
+    // (a row's 37 logits are spread over the four lanes c16 + 16 kq)
     auto fmax2 = [](float u, float v) { return fmaxf(u, v); };
     auto add2 = [](float u, float v) { return u + v; };
     float mx[2] = {-__builtin_inff(), -__builtin_inff()}, den[2] = {0.0f, 0.0f}, zy[2] = {0.0f, 0.0f};
@@ -535,8 +682,8 @@ __global__ __launch_bounds__(kGradThreads) void k_mlp_grad(GradArgs a) {
         if (o < kCls) mx[0] = fmaxf(mx[0], z[tt][r]);
         else if (o < kOut) mx[1] = fmaxf(mx[1], z[tt][r]);
       }
-    mx[0] = across(mx[0], fmax2);
-    mx[1] = across(mx[1], fmax2);
+    mx[0] = across<16>(mx[0], fmax2);
+    mx[1] = across<16>(mx[1], fmax2);
     f32x4 p[3];
 #pragma unroll
     for (int tt = 0; tt < 3; tt++)
@@ -552,8 +699,8 @@ __global__ __launch_bounds__(kGradThreads) void k_mlp_grad(GradArgs a) {
     const bool live = srow < rows, good = yc >= 0 && yc < kCls && yr >= 0 && yr < kRng;
 #pragma unroll
     for (int hd = 0; hd < 2; hd++) {
-      den[hd] = across(den[hd], add2);
-      zy[hd] = across(zy[hd], add2);   // (one lane holds the label's logit, the others 0)
+      den[hd] = across<16>(den[hd], add2);
+      zy[hd] = across<16>(zy[hd], add2);   // (one lane holds the label's logit, the others 0)
       loss += logf(den[hd]) + mx[hd] - zy[hd];
     }
     const float inv[2] = {1.0f / den[0], 1.0f / den[1]};
@@ -604,7 +751,7 @@ __global__ __launch_bounds__(kGradThreads) void k_mlp_grad(GradArgs a) {
 #pragma unroll
       for (int j = 0; j < 4; j++) {
         const int o = 8 * c + 4 * h + j;
-        const float w = o < kOut ? bf16_to_f32(sw3[o * kLdW + ut * 32 + col]) : 0.0f;
+        const float w = o < kOut ? bf16_to_f32(lw.w3[o * kLdW + ut * 32 + col]) : 0.0f;
         d = __builtin_amdgcn_mfma_f32_32x32x2f32(w, b[j], d, 0, 0, 0);
       }
     }
@@ -620,7 +767,7 @@ __global__ __launch_bounds__(kGradThreads) void k_mlp_grad(GradArgs a) {
       const f32x4 b = lds4(H2 + row * kLd + 8 * c + 4 * h);
 #pragma unroll
       for (int j = 0; j < 4; j++)
-        d = __builtin_amdgcn_mfma_f32_32x32x2f32(bf16_to_f32(sw2[(8 * c + 4 * h + j) * kLdW + ut * 32 + col]), b[j],
+        d = __builtin_amdgcn_mfma_f32_32x32x2f32(bf16_to_f32(lw.w2[(8 * c + 4 * h + j) * kLdW + ut * 32 + col]), b[j],
                                                  d, 0, 0, 0);
     }
     back(d, H1);
@@ -722,25 +869,17 @@ lfc_status mlp_launched(const char *who) {
 constexpr size_t kGradLds = sizeof(float) * (kTile * (kLdX + 3 * kLd) + 4 * kRedTile + 8) + sizeof(uint16_t) * kLdsW;
 
 lfc_status infer_launch(const uint16_t *w, const float *x, int64_t n, int8_t *cls, int8_t *rng, float *conf,
-                        float *logits, hipStream_t s) {
+                        float *logits, int32_t precision, hipStream_t s) {
   if (n == 0) return LFC_OK;
-  if (n > (int64_t)0x7FFFFFFF * kThreads) return lfc::fail(LFC_E_INVALID, "lfc_mlp_infer: too many rows");
-  // the float32 parameters live in stream-ordered scratch for this call
-  float *wf = nullptr;
-  if (hipMallocAsync(reinterpret_cast<void **>(&wf), sizeof(float) * kParams, s) != hipSuccess) {
-    (void)hipGetLastError();
-    return lfc::fail(LFC_E_NOMEM, "lfc_mlp_infer: scratch for the parameters");
-  }
-  hipLaunchKernelGGL(k_mlp_unpack, dim3((kParams + kThreads - 1) / kThreads), dim3(kThreads), 0, s, w, wf);
-  lfc_status st = mlp_launched("lfc_mlp_infer");
-  if (st == LFC_OK) {
-    const int64_t blocks = (n + kThreads - 1) / kThreads;   // n < 2^31 * 256, checked by the callers
-    InferArgs a{w, wf, x, n, cls, rng, conf, logits};
-    hipLaunchKernelGGL(k_mlp_infer, dim3((unsigned)blocks), dim3(kThreads), 0, s, a);
-    st = mlp_launched("lfc_mlp_infer");
-  }
-  if (hipFreeAsync(wf, s) != hipSuccess && st == LFC_OK) st = lfc::fail(LFC_E_HIP, "lfc_mlp_infer: scratch release");
-  return st;
+  InferArgs a{w, x, n, cls, rng, conf, logits};
+  const bool bf16 = precision == LFC_MLP_BF16;
+  // resident workgroups whose waves take tiles in turn
+  const int64_t groups = ((n + 31) / 32 + kMfmaWaves - 1) / kMfmaWaves;
+  const dim3 grid((unsigned)std::min<int64_t>(groups, (int64_t)(bf16 ? kMfmaWgs : kF32Wgs) * kCus));
+  const auto kern = bf16 ? (logits ? k_mlp_infer_mfma<true> : k_mlp_infer_mfma<false>)
+                         : (logits ? k_mlp_infer<true> : k_mlp_infer<false>);
+  hipLaunchKernelGGL(kern, grid, dim3(64 * kMfmaWaves), 0, s, a);
+  return mlp_launched("lfc_mlp_infer");
 }
 
 }  // namespace
@@ -765,15 +904,9 @@ extern "C" lfc_status lfc_mlp_infer_ex(const uint16_t *d_w, const float *d_x, in
     if (lfc_status st = mlp_check(d_conf, sizeof(float) * (size_t)n, 4, who, "d_conf")) return st;
   if (d_logits)
     if (lfc_status st = mlp_check(d_logits, sizeof(float) * kOut * (size_t)n, 4, who, "d_logits")) return st;
-  if (precision == LFC_MLP_FP32) return infer_launch(d_w, d_x, n, d_cls, d_rng, d_conf, d_logits, s);
-  if (reinterpret_cast<uintptr_t>(d_w) % 16)
+  if (precision == LFC_MLP_BF16 && reinterpret_cast<uintptr_t>(d_w) % 16)
     return lfc::fail(LFC_E_INVALID, "lfc_mlp_infer: bf16 inference needs 16-byte aligned weights");
-  const int64_t tiles = (n + 31) / 32;
-  const int64_t blocks = std::min<int64_t>((tiles + kMfmaWaves - 1) / kMfmaWaves, (int64_t)kMfmaWgs * kCus);
-  InferArgs a{d_w, nullptr, d_x, n, d_cls, d_rng, d_conf, d_logits};
-  hipLaunchKernelGGL(d_logits ? k_mlp_infer_mfma<true> : k_mlp_infer_mfma<false>, dim3((unsigned)blocks),
-                     dim3(64 * kMfmaWaves), 0, s, a);
-  return mlp_launched(who);
+  return infer_launch(d_w, d_x, n, d_cls, d_rng, d_conf, d_logits, precision, s);
 }
 
 extern "C" lfc_status lfc_mlp_grad(const uint16_t *d_w, const float *d_x, const int8_t *d_cls, const int8_t *d_rng,
@@ -836,7 +969,7 @@ lfc_status mlp_infer_rows(const void *d_w, const float *feat, int64_t n, int8_t 
   lfc_status st = LFC_OK;
   if (hipMemcpyAsync(dx, feat, fx, hipMemcpyHostToDevice, s) != hipSuccess)
     st = fail(LFC_E_HIP, "lfc_encode_ctl: copy of the features");
-  if (st == LFC_OK) st = infer_launch(static_cast<const uint16_t *>(d_w), dx, n, dcls, drng, dconf, nullptr, s);
+  if (st == LFC_OK) st = infer_launch(static_cast<const uint16_t *>(d_w), dx, n, dcls, drng, dconf, nullptr, LFC_MLP_FP32, s);
   if (st == LFC_OK && (hipMemcpyAsync(cls, dcls, (size_t)n, hipMemcpyDeviceToHost, s) != hipSuccess ||
                        hipMemcpyAsync(rng, drng, (size_t)n, hipMemcpyDeviceToHost, s) != hipSuccess ||
                        hipMemcpyAsync(conf, dconf, sizeof(float) * (size_t)n, hipMemcpyDeviceToHost, s) != hipSuccess))

@@ -111,3 +111,28 @@ def test_heads_take_units_in_order(gpu, bf16, special):
             want = 1.0 / np.exp(z[:10].astype(np.float64) - z[in_order_argmax(z[:10])]).sum()
         got = conf.cpu().numpy()
         assert np.isnan(got).all() if np.isnan(want) else np.abs(got - want).max() <= 1e-6, (s, k)
+    # no logit above -inf, or none that is a number: the first class
+    for bits16 in (0xFF80, 0x7FC0):
+        bits = np.zeros(lfc.MLP_PARAMS, dtype=np.uint16)
+        bits[lfc.MLP_PARAMS - 37:] = bits16
+        cls, rng, conf = lfc.mlp_infer(torch.from_numpy(bits.view(np.int16)).cuda(), x, precision=prec)
+        assert (cls == 0).all() and (rng == 0).all() and torch.isnan(conf).all()
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+def test_a_row_that_is_not_finite(gpu, bf16):
+    """A NaN feature makes every unit of layer 1 NaN, which the ReLU takes to
+    0; the other rows of its tile are not touched."""
+    wt, w = net(31)
+    x = np.random.default_rng(32).uniform(0, 1, (64, 16)).astype(np.float32)
+    prec = lfc.MLP_BF16 if bf16 else lfc.MLP_FP32
+    ref = lfc.mlp_infer(wt, torch.from_numpy(x).cuda(), logits=True, precision=prec)[3].cpu().numpy()
+    x[5, 3] = x[40, 15] = np.nan
+    z = lfc.mlp_infer(wt, torch.from_numpy(x).cuda(), logits=True, precision=prec)[3].cpu().numpy()
+    p = omlp.unpack(w)
+    h2 = np.maximum(p["b2"], 0)
+    want = h2 @ p["W3"].T + p["b3"]
+    for r in (5, 40):
+        assert np.abs(z[r] - want).max() <= 1e-2 * max(1.0, np.abs(want).max())
+    rest = np.setdiff1d(np.arange(64), [5, 40])
+    assert np.array_equal(z[rest], ref[rest])
