@@ -961,9 +961,8 @@ __device__ __forceinline__ uint32_t rgb_pack(int32_t yv, int32_t co, int32_t cg)
   return (uint32_t)min(max(R, 0), 255) | ((uint32_t)min(max(G, 0), 255) << 8) | ((uint32_t)min(max(Bc, 0), 255) << 16);
 }
 
-// The quadrilinear interpolation of one output pixel from its 16 taps
-// P[k][0..3] = (y0,x0), (y0,x1), (y1,x0), (y1,x1) of view k = 0: (u0, v0),
-// 1: (u1, v0), 2: (u0, v1), 3: (u1, v1); lerps in s, t, v, u order.
+// Source views of an output pixel: k = 0: (u0, v0), 1: (u1, v0), 2: (u0, v1),
+// 3: (u1, v1); its taps in each are (y0,x0), (y0,x1), (y1,x0), (y1,x1).
 // Camera-plane position (clamped to the grid) and the image-plane shift of
 // source view k (0: lower column/row, 1: upper) for focal disparity d: a
 // novel camera focused at disparity d samples source camera (iu, jv) at
@@ -984,32 +983,79 @@ __device__ __forceinline__ float src_pos(float s, int X, float scale) {
   return s + ((float)X + 0.5f) * scale - 0.5f;
 }
 
-// x / 255 for 0 <= x <= 255, rounded as the IEEE quotient: the product with
-// the rounded reciprocal, corrected by one fused residual step (equal to the
-// division for every float of the range, checked on the host by
-// tests/arith_identities.c; negative inputs mirror it); three VALU operations
-// instead of a full division.
+// The interpolation works on taps scaled by 2^-24 (exact throughout: a power
+// of two): a byte in the low half of a 16-bit lane is the fp16 number byte x
+// 2^-24, so a byte permute makes two taps into packed fp16, their differences
+// are exact there, and a mixed-precision fma lerps them in fp32.  Five
+// operations for two taps pairs against eight with conversions.
+typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ f16x2 tap_pair(uint32_t hi, uint32_t lo, uint32_t sel) {
+  return __builtin_bit_cast(f16x2, __builtin_amdgcn_perm(hi, lo, sel));
+}
+
+// lerp along s of the tap pairs (a[k], b[k]) of the four source views, at that
+// view's fraction fs[k % NS]: h[view][channel]
+template <int NS>
+__device__ __forceinline__ void slerp_taps(const uint32_t (&a)[4], const uint32_t (&b)[4], const float (&fs)[NS],
+                                           float (&h)[4][3]) {
+#pragma unroll
+  for (int k = 0; k < 4; k++) {   // red and green
+    const f16x2 p = tap_pair(a[k], a[k], 0x0c010c00u), d = tap_pair(b[k], b[k], 0x0c010c00u) - p;
+    h[k][0] = __builtin_fmaf((float)d.x, fs[k % NS], (float)p.x);
+    h[k][1] = __builtin_fmaf((float)d.y, fs[k % NS], (float)p.y);
+  }
+#pragma unroll
+  for (int k = 0; k < 4; k += 2) {   // blue, of two views
+    const f16x2 p = tap_pair(a[k + 1], a[k], 0x0c060c02u), d = tap_pair(b[k + 1], b[k], 0x0c060c02u) - p;
+    h[k][2] = __builtin_fmaf((float)d.x, fs[k % NS], (float)p.x);
+    h[k + 1][2] = __builtin_fmaf((float)d.y, fs[(k + 1) % NS], (float)p.y);
+  }
+}
+
+// lerp along v, then u, of the four views' values
+__device__ __forceinline__ void blend_views(const float (&h)[4][3], float fu, float fv, float (&r)[3]) {
+#pragma unroll
+  for (int ch = 0; ch < 3; ch++) r[ch] = lerpf(lerpf(h[0][ch], h[2][ch], fv), lerpf(h[1][ch], h[3][ch], fv), fu);
+}
+
+// x / 255 for 0 <= x <= 255 given x 2^-24, rounded as the IEEE quotient: the
+// product with the rounded reciprocal, corrected by one fused residual step
+// (equal to the division for every float of the range, checked on the host by
+// tests/arith_identities.c, where the powers of two are left out; negative
+// inputs mirror it); three VALU operations instead of a full division.
 __device__ __forceinline__ float div255(float x) {
-  constexpr float r = 1.0f / 255.0f;
+  constexpr float r = 1.0f / 255.0f * 16777216.0f, k = 255.0f / 16777216.0f;
   const float q = x * r;
-  return __builtin_fmaf(__builtin_fmaf(-q, 255.0f, x), r, q);
+  return __builtin_fmaf(__builtin_fmaf(-q, k, x), r, q);
 }
 
 // quadrilinear interpolation of the 16 RGB taps P[view][tap] (taps 00, 01,
-// 10, 11 of each view, at that view's fractions fs[k], ft[k])
+// 10, 11 of each view, at that view's fractions fs[k], ft[k]).  The lerps go
+// along s, v, u and t: the first three depend on the source row only, so
+// consecutive output rows can share them; with a focal shift, where the views
+// have fractions of their own, along s, t, v and u.
+template <bool FOCAL>
 __device__ __forceinline__ void interp_store(const uint32_t P[4][4], const float fs[4], const float ft[4], float fu,
                                              float fv, float *o, size_t plane) {
+  const float f[4] = {fs[0], fs[1], fs[2], fs[3]};
+  const uint32_t t0[4] = {P[0][0], P[1][0], P[2][0], P[3][0]}, t1[4] = {P[0][1], P[1][1], P[2][1], P[3][1]};
+  const uint32_t b0[4] = {P[0][2], P[1][2], P[2][2], P[3][2]}, b1[4] = {P[0][3], P[1][3], P[2][3], P[3][3]};
+  float top[4][3], bot[4][3], r[2][3];
+  slerp_taps<4>(t0, t1, f, top);
+  slerp_taps<4>(b0, b1, f, bot);
+  if constexpr (FOCAL) {
 #pragma unroll
-  for (int ch = 0; ch < 3; ch++) {
-    float lt[4];
+    for (int k = 0; k < 4; k++)
 #pragma unroll
-    for (int k = 0; k < 4; k++) {
-      const float p00 = (float)((P[k][0] >> (8 * ch)) & 255u), p01 = (float)((P[k][1] >> (8 * ch)) & 255u);
-      const float p10 = (float)((P[k][2] >> (8 * ch)) & 255u), p11 = (float)((P[k][3] >> (8 * ch)) & 255u);
-      lt[k] = lerpf(lerpf(p00, p01, fs[k]), lerpf(p10, p11, fs[k]), ft[k]);
-    }
-    const float lv0 = lerpf(lt[0], lt[2], fv), lv1 = lerpf(lt[1], lt[3], fv);
-    o[ch * plane] = div255(lerpf(lv0, lv1, fu));
+      for (int ch = 0; ch < 3; ch++) top[k][ch] = lerpf(top[k][ch], bot[k][ch], ft[k]);
+    blend_views(top, fu, fv, r[0]);
+#pragma unroll
+    for (int ch = 0; ch < 3; ch++) o[ch * plane] = div255(r[0][ch]);
+  } else {
+    blend_views(top, fu, fv, r[0]);
+    blend_views(bot, fu, fv, r[1]);
+#pragma unroll
+    for (int ch = 0; ch < 3; ch++) o[ch * plane] = div255(lerpf(r[0][ch], r[1][ch], ft[0]));
   }
 }
 
@@ -1149,7 +1195,7 @@ __device__ __forceinline__ void render_tile(const RenderArgs &a, const lfc_view 
       P[k][2] = img[((ly1 / B) * FBX[k] + lx0 / B) * SLOT + (ly1 % B) * B + lx0 % B];
       P[k][3] = img[((ly1 / B) * FBX[k] + lx1 / B) * SLOT + (ly1 % B) * B + lx1 % B];
     }
-    interp_store(P, fs, ft, fu, fv, outn + (size_t)Yp * a.wo + X, plane);
+    interp_store<FOCAL>(P, fs, ft, fu, fv, outn + (size_t)Yp * a.wo + X, plane);
   }
 }
 
@@ -1557,9 +1603,22 @@ __global__ __launch_bounds__(kLFThreads) void k_decode_rgb_multi(RGBMultiArgs m)
 }
 
 // Novel views from fully decoded 8-bit RGB source views ([nv][hp][wp]): one
-// thread per output pixel, its 16 taps one word each, the same lerps as
+// thread per output column and R consecutive output rows, the same lerps as
 // render_tile.  Used when a batch of views needs about as many source blocks
 // as the whole light field holds.
+// What bounds it: the traffic of the taps (four source views of 4 bytes a
+// pixel) and of the output.  The lerps along s, v and u depend on the column
+// and the source row only, and consecutive output rows mostly share a source
+// row, so a thread keeps the blended values of two source rows and takes a new
+// one when the output row moves on: at equal scale half of the tap reads and
+// lerps.  Taps are read as pairs (x1 = x0 + 1) in one 8-byte read, all of a
+// thread's before its first store: a load issued after stores waits for them
+// too (a loop over the rows, each with its own reads, took as long as one row
+// per thread).
+// Measured, 64 views of 512 x 512 from 17 x 17 x 512 x 512 (167 MB of decoded
+// views, 201 MB out): 82 us, 5.1 TB/s of what the counters see, about the rate
+// of a copy (112 us with one row per thread and conversions); one row per
+// thread 129 us, two 106, eight 81.
 struct InterpRGBArgs {
   const uint32_t *rgb;
   uint32_t rgb_bytes;   // bytes of the decoded views (below 4 GiB)
@@ -1568,73 +1627,189 @@ struct InterpRGBArgs {
   int wo, ho, U, V, W, H, wp, hp;
   float disp;       // focal disparity (as RenderArgs)
   float sxs, tys;   // W / wo and H / ho, rounded once on the host as the other renderers round them
+  int stream_out;   // store the output with the non-temporal hint
 };
 
-// Output pixel (X, Yp) of view vw into o (its view's [3][ho][wo] planes).
-template <bool FOCAL>
-__device__ __forceinline__ void interp_rgb_pixel(const InterpRGBArgs &a, const lfc_view &vw, float *o, int X,
-                                                 int Yp) {
-  int iu0, iu1, jv0, jv1, x0, x1, y0, y1;
+// Output pixels (X, Yb..Yb + R - 1) of view vw into o (its view's [3][ho][wo]
+// planes), as far as they are inside.
+template <bool FOCAL, int R>
+__device__ __forceinline__ void interp_rgb_rows(const InterpRGBArgs &a, const lfc_view &vw, float *o, int X, int Yb) {
+  constexpr int NS = FOCAL ? 4 : 1;   // source positions: of each view, or shared
+  int iu0, iu1, jv0, jv1, x0, x1;
   float fu, fv;
   cell(vw.u, a.U, iu0, iu1, fu);
   cell(vw.v, a.V, jv0, jv1, fv);
-  const float sx = src_pos(vw.s, X, a.sxs), ty = src_pos(vw.t, Yp, a.tys);
+  // (lanes past the row's end, in its last wave, follow the last column: the
+  // row positions below come from the wave's first lanes, whatever they hold)
+  const float sx = src_pos(vw.s, min(X, a.wo - 1), a.sxs);
   // taps through a buffer resource: 32-bit byte offsets from one base (the
-  // decoded views take less than 4 GiB)
+  // decoded views take less than 4 GiB); a row's offset goes in the load's
+  // scalar offset, the column in the per-lane one, and the hardware adds them;
+  // the stores likewise (a view's planes take at most 3 GiB)
   const __amdgpu_buffer_rsrc_t rs =
       __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t *>(a.rgb), 0, a.rgb_bytes, 0x00020000);
+  const uint32_t plane = (uint32_t)a.ho * (uint32_t)a.wo;
+  const __amdgpu_buffer_rsrc_t ro = __builtin_amdgcn_make_buffer_rsrc(o, 0, 12u * plane, 0x00020000);
   const uint32_t vbytes = 4u * (uint32_t)a.hp * (uint32_t)a.wp, rbytes = 4u * (uint32_t)a.wp;
   const uint32_t vis[4] = {(uint32_t)(jv0 * a.U + iu0), (uint32_t)(jv0 * a.U + iu1), (uint32_t)(jv1 * a.U + iu0),
                            (uint32_t)(jv1 * a.U + iu1)};
-  uint32_t P[4][4];
-  float fs[4], ft[4];
+  uint32_t vo[4], c0[NS];
+  float fs[NS];
 #pragma unroll
-  for (int k = 0; k < 4; k++) {
+  for (int k = 0; k < 4; k++) vo[k] = __builtin_amdgcn_readfirstlane(vis[k] * vbytes);
+#pragma unroll
+  for (int k = 0; k < NS; k++) {
+    // (the pair's second pixel is x0 + 1; where the image is one pixel wide,
+    // the padding's, at fraction zero)
     cell(sx + focal_shift<FOCAL>(a.disp, vw.u, a.U, (k & 1) ? iu1 : iu0), a.W, x0, x1, fs[k]);
-    cell(ty + focal_shift<FOCAL>(a.disp, vw.v, a.V, (k & 2) ? jv1 : jv0), a.H, y0, y1, ft[k]);
-    // a row's offset goes in the load's scalar offset, the column in the
-    // per-lane one, and the hardware adds them
-    if constexpr (FOCAL) {   // (the shifted row is computed per lane otherwise)
-      y0 = __builtin_amdgcn_readfirstlane(y0);
-      y1 = __builtin_amdgcn_readfirstlane(y1);
-    }
-    const uint32_t r0 = __builtin_amdgcn_readfirstlane(vis[k] * vbytes + (uint32_t)y0 * rbytes);
-    const uint32_t r1 = __builtin_amdgcn_readfirstlane(vis[k] * vbytes + (uint32_t)y1 * rbytes);
-    const uint32_t c0 = 4u * (uint32_t)x0, c1 = 4u * (uint32_t)x1;
-    P[k][0] = __builtin_amdgcn_raw_buffer_load_b32(rs, c0, r0, 0);
-    P[k][1] = __builtin_amdgcn_raw_buffer_load_b32(rs, c1, r0, 0);
-    P[k][2] = __builtin_amdgcn_raw_buffer_load_b32(rs, c0, r1, 0);
-    P[k][3] = __builtin_amdgcn_raw_buffer_load_b32(rs, c1, r1, 0);
+    c0[k] = 4u * (uint32_t)x0;
   }
-  interp_store(P, fs, ft, fu, fv, o + (size_t)Yp * a.wo + X, (size_t)a.ho * a.wo);
+  // the rows' source positions, the same for the whole wave: lane l finds row
+  // l % R's, and they go to scalar registers
+  int y0[R][NS], y1[R][NS];
+  float ft[R][NS];
+  {
+    const int l = R == 1 ? 0 : (int)(threadIdx.x & 63) % R;
+    const float ty = src_pos(vw.t, min(Yb + l, a.ho - 1), a.tys);
+#pragma unroll
+    for (int k = 0; k < NS; k++) {
+      int u0, u1;
+      float f;
+      cell(ty + focal_shift<FOCAL>(a.disp, vw.v, a.V, (k & 2) ? jv1 : jv0), a.H, u0, u1, f);
+#pragma unroll
+      for (int i = 0; i < R; i++) {
+        y0[i][k] = R == 1 ? __builtin_amdgcn_readfirstlane(u0) : __builtin_amdgcn_readlane(u0, i);
+        y1[i][k] = R == 1 ? __builtin_amdgcn_readfirstlane(u1) : __builtin_amdgcn_readlane(u1, i);
+        ft[i][k] = __uint_as_float(R == 1 ? __builtin_amdgcn_readfirstlane(__float_as_uint(f))
+                                          : __builtin_amdgcn_readlane(__float_as_uint(f), i));
+      }
+    }
+  }
+  // which rows to read: a row's upper source row is read if the row above has
+  // it neither as its upper nor as its lower one, the lower unless the row
+  // above has it in the same part
+  bool nu[R], nl[R];
+  u32x2_t wu[R][4], wl[R][4];
+  auto read = [&](u32x2_t (&w)[4], const int (&y)[NS]) {
+#pragma unroll
+    for (int k = 0; k < 4; k++)
+      w[k] = __builtin_amdgcn_raw_buffer_load_b64(rs, c0[k % NS], vo[k] + (uint32_t)y[k % NS] * rbytes, 0);
+  };
+#pragma unroll
+  for (int i = 0; i < R; i++) {
+    nu[i] = i == 0 || (y0[i][0] != y0[i - 1][0] && y0[i][0] != y1[i - 1][0]);
+    nl[i] = i == 0 || y0[i][0] != y0[i - 1][0] || y1[i][0] != y1[i - 1][0];
+    if (nu[i]) read(wu[i], y0[i]);
+    if (nl[i]) read(wl[i], y1[i]);
+  }
+  auto slerp = [&](const u32x2_t (&w)[4], float (&h)[4][3]) {
+    const uint32_t p[4] = {w[0].x, w[1].x, w[2].x, w[3].x}, q[4] = {w[0].y, w[1].y, w[2].y, w[3].y};
+    slerp_taps<NS>(p, q, fs, h);
+  };
+  auto put = [&](int i, const float (&x)[3]) {
+    if (Yb + i >= a.ho || X >= a.wo) return;
+    const uint32_t at = 4u * (uint32_t)X, row = 4u * (uint32_t)(Yb + i) * (uint32_t)a.wo;
+    if (a.stream_out)
+#pragma unroll
+      for (uint32_t ch = 0; ch < 3; ch++)
+        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(div255(x[ch])), ro, at, 4u * ch * plane + row, 2 /* nt */);
+    else
+#pragma unroll
+      for (uint32_t ch = 0; ch < 3; ch++)
+        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(div255(x[ch])), ro, at, 4u * ch * plane + row, 0);
+  };
+  float h[4][3];
+  if constexpr (FOCAL) {
+    static_assert(R == 1, "the source rows of a refocused pixel are each view's own");
+    float g[4][3], x[3];
+    slerp(wu[0], h);
+    slerp(wl[0], g);
+#pragma unroll
+    for (int k = 0; k < 4; k++)
+#pragma unroll
+      for (int ch = 0; ch < 3; ch++) h[k][ch] = lerpf(h[k][ch], g[k][ch], ft[0][k]);
+    blend_views(h, fu, fv, x);
+    put(0, x);
+  } else {
+    // the blended source rows: row i's upper one in place i % 2, its lower one
+    // in the other, so that moving on by one source row moves no value
+    float row[2][3];
+#pragma unroll
+    for (int i = 0; i < R; i++) {
+      const int U = i & 1;
+      if (nu[i]) {
+        slerp(wu[i], h);
+        blend_views(h, fu, fv, row[U]);
+      } else if (i > 0 && y0[i][0] == y0[i - 1][0]) {   // (magnified: the same upper row again)
+#pragma unroll
+        for (int ch = 0; ch < 3; ch++) {
+          const float t = row[U][ch];
+          row[U][ch] = row[1 - U][ch];
+          row[1 - U][ch] = t;
+        }
+      }
+      if (nl[i]) {
+        slerp(wl[i], h);
+        blend_views(h, fu, fv, row[1 - U]);
+      }
+      float x[3];
+#pragma unroll
+      for (int ch = 0; ch < 3; ch++) x[ch] = lerpf(row[U][ch], row[1 - U][ch], ft[i][0]);
+      put(i, x);
+    }
+  }
 }
 
-template <bool FOCAL>
-__global__ __launch_bounds__(kThreads) void k_interp_rgb(InterpRGBArgs a) {
-  // grid (row pieces, view, row): the workgroups that run together render one
-  // output row of every view, whose taps come from nearby rows of the same
-  // few source views, so the caches serve those rows once for all views
-  // (a grid that gave each of the eight dies its own band of rows measured
-  // no faster)
-  const int X = blockIdx.x * kThreads + threadIdx.x, n = blockIdx.y, Yp = blockIdx.z;
-  if (X >= a.wo) return;
-  interp_rgb_pixel<FOCAL>(a, a.views[n], a.out + (size_t)n * 3 * a.ho * a.wo, X, Yp);
+// The grid of the interpolation: workgroups go to the eight dies in turn, and
+// the bands of R output rows with them, so that all views' workgroups of a
+// band run on one die about together and its L2 serves a source row once for
+// every view that reads it (64 views of 512 x 512: 82 us; bands in launch
+// order 85; an eighth of the rows per die in one run 86).
+struct InterpGrid {
+  int pieces, n;   // workgroups per output row, views
+  __device__ __forceinline__ void at(int &x, int &view, int &band) const {
+    const uint32_t id = blockIdx.y * gridDim.x + blockIdx.x;
+    const int j = (int)(id / 8u), per = pieces * n;
+    band = j / per * 8 + (int)(id % 8u);
+    x = (j % per % pieces) * kThreads + (int)threadIdx.x;
+    view = j % per / pieces;
+  }
+  // (a grid dimension holds fewer than 2^32 threads; bands past the last exit)
+  dim3 grid(int bands) const {
+    const uint64_t blocks = (uint64_t)8 * ((bands + 7) / 8) * pieces * n;
+    const uint32_t x = (uint32_t)std::min<uint64_t>(blocks, 1u << 23);
+    return dim3(x, (uint32_t)((blocks + x - 1) / x));
+  }
+};
+
+template <bool FOCAL, int R>
+__global__ __launch_bounds__(kThreads) void k_interp_rgb(InterpRGBArgs a, InterpGrid g) {
+  int X, n, band;
+  g.at(X, n, band);
+  if (band * R >= a.ho || X - (int)(threadIdx.x & 63) >= a.wo) return;   // (whole waves)
+  interp_rgb_rows<FOCAL, R>(a, a.views[n], a.out + (size_t)n * 3 * a.ho * a.wo, X, band * R);
 }
+
+// Output rows per thread of the plain interpolation.  Small batches gain too:
+// 4 views of 128 x 128 from 8 x 8 x 256 x 256 take 26 us with the decode, 32 us
+// with one row per thread; 64 of 512 x 512 take 66, 112.
+constexpr int kInterpRows = 4;
 
 // Requests of several light fields and output sizes interpolated in one
-// launch: workgroup (piece, request, row) exits when the request's output is
-// smaller.  A request's record carries its light field's decoded views
-// (views unused; the camera is in the record).
+// launch: a workgroup exits when its request's output is smaller.  A request's
+// record carries its light field's decoded views (views unused; the camera is
+// in the record).
 struct InterpReq {
   InterpRGBArgs a;
   lfc_view view;
 };
 
-__global__ __launch_bounds__(kThreads) void k_interp_multi(const InterpReq *reqs) {
-  const InterpReq r = reqs[blockIdx.y];
-  const int X = blockIdx.x * kThreads + threadIdx.x, Yp = blockIdx.z;
-  if (X >= r.a.wo || Yp >= r.a.ho) return;
-  interp_rgb_pixel<false>(r.a, r.view, r.a.out, X, Yp);
+__global__ __launch_bounds__(kThreads) void k_interp_multi(const InterpReq *reqs, InterpGrid g) {
+  int X, n, band;
+  g.at(X, n, band);
+  const InterpReq r = reqs[n];
+  if (band * kInterpRows >= r.a.ho || X - (int)(threadIdx.x & 63) >= r.a.wo) return;   // (whole waves)
+  interp_rgb_rows<false, kInterpRows>(r.a, r.view, r.a.out, X, band * kInterpRows);
 }
 
 // ---------------------------------------------------------------------------
@@ -1910,6 +2085,13 @@ lfc_status choose_render(const lfc_lf *lf, int32_t n, int32_t wo, int32_t ho, co
 size_t rgb_bytes(const lfc::Geometry &g) { return (size_t)g.nv() * g.hp * g.wp * sizeof(uint32_t); }
 size_t decoded_bytes(const lfc::Geometry &g) { return rgb_bytes(g); }
 
+// Whether a decoded render's output is stored with the non-temporal hint: when
+// it and the decoded views do not fit the Infinity Cache together, stored
+// normally it would push out the views that are still to be read and the
+// compressed input of the next call (64 views of 512 x 512 from 17 x 17 x 512
+// x 512: interpolation 82 us, 96 without; the next decode 122, 129).
+int stream_render(uint64_t decoded, uint64_t out) { return decoded + out > kStreamOutBytes; }
+
 // One render with a resolved choice.  The decoded path decodes into ws when
 // given, else into stream-ordered scratch from the library's pool.
 template <int B>
@@ -1926,12 +2108,14 @@ lfc_status render_with(const lfc_lf *lf, const lfc_view *views, int32_t n, int32
     lfc_status st = decode_rgb<B>(lf, rgb, nullptr, s, "lfc_render_views", views, n);
     if (st == LFC_OK) {
       InterpRGBArgs ia{rgb, (uint32_t)rgb_bytes(g), views, out, wo, ho, g.U, g.V, g.W, g.H, g.wp, g.hp, rc.disp,
-                       (float)g.W / (float)wo, (float)g.H / (float)ho};
-      const dim3 grid((wo + kThreads - 1) / kThreads, n, ho);
+                       (float)g.W / (float)wo, (float)g.H / (float)ho,
+                       stream_render(decoded_bytes(g), (uint64_t)12 * n * wo * ho)};
+      const InterpGrid gr{(wo + kThreads - 1) / kThreads, n};
       if (rc.disp != 0.0f)
-        hipLaunchKernelGGL(k_interp_rgb<true>, grid, dim3(kThreads), 0, s, ia);
+        hipLaunchKernelGGL((k_interp_rgb<true, 1>), gr.grid(ho), dim3(kThreads), 0, s, ia, gr);
       else
-        hipLaunchKernelGGL(k_interp_rgb<false>, grid, dim3(kThreads), 0, s, ia);
+        hipLaunchKernelGGL((k_interp_rgb<false, kInterpRows>), gr.grid((ho + kInterpRows - 1) / kInterpRows),
+                           dim3(kThreads), 0, s, ia, gr);
       st = launched("lfc_render_views");
     }
     if (!ws && hipFreeAsync(dec, s) != hipSuccess && st == LFC_OK)
@@ -2404,11 +2588,11 @@ void need_mask_host(const lfc_lf *lf, const lfc_view &v, uint32_t *mask) {
 size_t interp_req_bytes() { return sizeof(InterpReq); }
 
 void interp_req_fill(const lfc_lf *lf, const uint32_t *d_rgb, const lfc_view &v, int wo, int ho, float *out,
-                     void *dst) {
+                     uint64_t call_bytes, void *dst) {
   const Geometry &g = lf->geo;
   InterpReq r{};
   r.a = InterpRGBArgs{d_rgb, (uint32_t)rgb_bytes(g), nullptr, out, wo, ho, g.U, g.V, g.W, g.H, g.wp, g.hp, 0.0f,
-                      (float)g.W / (float)wo, (float)g.H / (float)ho};
+                      (float)g.W / (float)wo, (float)g.H / (float)ho, call_bytes > kStreamOutBytes};
   r.view = v;
   std::memcpy(dst, &r, sizeof r);
 }
@@ -2441,8 +2625,9 @@ lfc_status rgb_multi_launch(int block, bool keys, const void *d_args, const int3
 lfc_status interp_multi_launch(const void *d_reqs, int n, int max_wo, int max_ho, hipStream_t s) {
   if (n <= 0) return LFC_OK;
   if (n > 65535) return fail(LFC_E_INVALID, "lfc_batch_render: at most 65535 interpolated requests per batch");
-  const dim3 grid((unsigned)((max_wo + kThreads - 1) / kThreads), (unsigned)n, (unsigned)max_ho);
-  hipLaunchKernelGGL(k_interp_multi, grid, dim3(kThreads), 0, s, static_cast<const InterpReq *>(d_reqs));
+  const InterpGrid gr{(max_wo + kThreads - 1) / kThreads, n};
+  hipLaunchKernelGGL(k_interp_multi, gr.grid((max_ho + kInterpRows - 1) / kInterpRows), dim3(kThreads), 0, s,
+                     static_cast<const InterpReq *>(d_reqs), gr);
   return launched("lfc_batch_render");
 }
 

@@ -200,6 +200,7 @@ struct BatchLayout {
   std::vector<size_t> at_mask;
   size_t at_interp = 0, bytes = 0;
   int n_interp = 0, max_wo = 0, max_ho = 0;
+  uint64_t interp_bytes = 0;        // decoded views and outputs of the interpolated requests
 };
 
 // Validates a batch and lays out its table (see BatchLayout); with
@@ -237,7 +238,7 @@ lfc_status plan_batch(lfc_batch *b, const lfc_lf *const *lfs, int32_t n_lf, cons
   L.scr.assign((size_t)n_lf, nullptr);
   for (int l = 0; l < n_lf; l++)
     if (px[(size_t)l] > 0.0 && (!allow_rgb || allow_rgb[l]) && lfc::lf_rgb_batchable(lfs[l], px[(size_t)l]))
-      L.scr[(size_t)l] = get_scratch(b, lfs[l]);
+      if ((L.scr[(size_t)l] = get_scratch(b, lfs[l]))) L.interp_bytes += lfc::lf_rgb_bytes(lfs[l]);
   const size_t rb = lfc::render_req_bytes(), ab = lfc::rgb_args_bytes(), ib = lfc::interp_req_bytes();
   std::vector<char> packed((size_t)n * rb);
   std::vector<int> bs(n, 0);
@@ -245,6 +246,7 @@ lfc_status plan_batch(lfc_batch *b, const lfc_lf *const *lfs, int32_t n_lf, cons
     const lfc_render_request &r = reqs[i];
     if (L.scr[(size_t)r.lf]) {
       L.n_interp++;
+      L.interp_bytes += (uint64_t)12 * r.out_w * r.out_h;
       L.max_wo = std::max(L.max_wo, r.out_w);
       L.max_ho = std::max(L.max_ho, r.out_h);
       continue;
@@ -324,7 +326,7 @@ void fill_batch(const BatchLayout &L, const lfc_lf *const *lfs, int32_t n_lf, co
     if (!L.scr[(size_t)r.lf]) continue;
     lfc::need_mask_host(lfs[r.lf], r.view, reinterpret_cast<uint32_t *>(host + L.at_mask[(size_t)r.lf]));
     lfc::interp_req_fill(lfs[r.lf], static_cast<uint32_t *>(L.scr[(size_t)r.lf]->buf), r.view, r.out_w, r.out_h,
-                         d_outs[i], host + L.at_interp + (size_t)k * ib);
+                         d_outs[i], L.interp_bytes, host + L.at_interp + (size_t)k * ib);
     k++;
   }
   (void)n_lf;
