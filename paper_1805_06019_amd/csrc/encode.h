@@ -2,6 +2,7 @@
 // encoder (encode_gpu.hip), so that both write the same stream.
 #pragma once
 
+#include <cstddef>
 #include <cstdint>
 #include <vector>
 
@@ -16,5 +17,9 @@ void put_stream_header(uint8_t *h, const Geometry &g, const lfc_params &p, uint3
 // PSNR statistics (eq. 5 per view and channel, eq. 4, means over views) from
 // the squared error of every (view, channel) on the unpadded area.
 void encode_stats_from_sse(const std::vector<double> &se, int nv, int W, int H, lfc_encode_stats *stats);
+
+// Memory of an encoded stream (lfc_free returns it); nullptr if there is none.
+void *stream_alloc(size_t bytes) noexcept;
+void stream_free(void *p) noexcept;
 
 }  // namespace lfc

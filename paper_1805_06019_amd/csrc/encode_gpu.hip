@@ -13,12 +13,14 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <new>
 #include <string>
 #include <type_traits>
 #include <vector>
 
 #include "encode.h"
 #include "internal.h"
+#include "serve.h"
 
 namespace {
 
@@ -408,15 +410,17 @@ __device__ __forceinline__ void put_block(BitPut &out, const uint32_t (&z)[S / 2
 
 template <int B>
 __global__ __launch_bounds__(kT) void k_enc_pack(const int8_t *code_tab, const uint16_t *zv, const uint32_t *offsets,
-                                                 uint32_t *srv, EncGeo g) {
+                                                 uint32_t *off_out, uint32_t *srv, EncGeo g) {
   constexpr int S = B * B;
   __shared__ PackLds<S> lds[kT / 64];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, gi = blockIdx.x * (kT / 64) + wv;
   if (gi >= g.ng) {
     if (gi == g.ng && lane < 2) srv[offsets[g.ng] + lane] = 0;   // the section's spare words
+    if (gi == g.ng && lane == 0) off_out[gi] = offsets[gi];
     return;
   }
   const uint32_t o0 = offsets[gi];
+  if (lane == 0) off_out[gi] = o0;   // (the stream's copy)
   if (o0 == offsets[gi + 1]) return;
   PackLds<S> &sm = lds[wv];
   uint32_t *w = srv + o0;
@@ -513,29 +517,36 @@ lfc_status launched(const char *what) {
   return LFC_OK;
 }
 
-// device buffers of one encode, freed on every path
-struct DevBufs {
-  std::vector<void *> ptrs;
-  ~DevBufs() {
-    for (void *p : ptrs) (void)hipFree(p);
+// Device scratch of one encode, given back on every path (and on its stream, so
+// after the work that uses it).
+struct Scratch {
+  hipStream_t s;
+  void *p = nullptr;
+  explicit Scratch(hipStream_t stream) : s(stream) {}
+  ~Scratch() {
+    if (p) (void)hipFreeAsync(p, s);
   }
-  template <typename T>
-  lfc_status alloc(T **p, size_t n) {
-    void *q = nullptr;
-    if (hipMalloc(&q, std::max<size_t>(n, 1) * sizeof(T)) != hipSuccess) {
-      (void)hipGetLastError();
+  Scratch(const Scratch &) = delete;
+  lfc_status alloc(size_t bytes) {
+    if (lfc::scratch_alloc(&p, std::max<size_t>(bytes, 256), s) != LFC_OK)
       return lfc::fail(LFC_E_NOMEM, "lfc_encode_gpu: device memory");
-    }
-    ptrs.push_back(q);
-    *p = static_cast<T *>(q);
     return LFC_OK;
   }
 };
 
-}  // namespace
+// Parts of one allocation, 256-byte aligned.
+struct Parts {
+  size_t bytes = 0;
+  template <typename T>
+  size_t add(size_t n) {
+    const size_t at = bytes;
+    bytes = (at + n * sizeof(T) + 255) & ~(size_t)255;
+    return at;
+  }
+};
 
-extern "C" lfc_status lfc_encode_gpu(const uint8_t *d_rgb, const lfc_params *p, void **stream_out, size_t *bytes_out,
-                                     lfc_encode_stats *stats, hipStream_t s) {
+lfc_status encode_gpu(const uint8_t *d_rgb, const lfc_params *p, void **stream_out, size_t *bytes_out,
+                      lfc_encode_stats *stats, hipStream_t s) {
   using namespace lfc;
   if (!d_rgb || !p || (!stream_out) != (!bytes_out)) return fail(LFC_E_INVALID, "lfc_encode_gpu: null argument");
   if (stream_out) {
@@ -579,44 +590,52 @@ extern "C" lfc_status lfc_encode_gpu(const uint8_t *d_rgb, const lfc_params *p, 
     }
   }
   TreeTables tt;
-  try {
-    build_tree_tables(geo, tt);
-  } catch (const std::bad_alloc &) {
-    return fail(LFC_E_NOMEM, "lfc_encode_gpu: out of host memory");
-  }
+  build_tree_tables(geo, tt);
   const size_t plane = (size_t)geo.hp * geo.wp, img = 3 * plane;
   const size_t nsg = (size_t)geo.ng * geo.n_srv;
-  DevBufs db;
-  std::vector<int16_t *> lvl(L, nullptr), rec(L, nullptr);
-  std::vector<int32_t *> serial(L, nullptr);
-  int8_t *code_tab = nullptr;
-  uint16_t *zv = nullptr;
-  uint32_t *gw = nullptr, *d_off = nullptr;
-  // small results, copied to the host together: the offsets' total, the stored
-  // blocks per code, the error flags, the squared errors
-  unsigned long long *small = nullptr;
-  const size_t at_hist = 1, at_err = at_hist + kHistCopies * kHistStride, at_sse = at_err + 1, n_small = at_sse + (size_t)nv * 3;
+  // one scratch: the levels, the reconstructions between the top and level 0,
+  // the tables; and the small results, copied to the host together: the
+  // offsets' total, the stored blocks per code, the error flags, the squared
+  // errors
+  const size_t at_hist = 1, at_err = at_hist + kHistCopies * kHistStride, at_sse = at_err + 1,
+               n_small = at_sse + (size_t)nv * 3;
+  Parts parts;
+  std::vector<size_t> p_lvl(L), p_rec(L), p_serial(L);
+  size_t n_serial = 0;
   for (int l = 0; l < L; l++) {
     const size_t nodes = (size_t)geo.lu[l] * geo.lv[l];
-    if (lfc_status st = db.alloc(&lvl[l], nodes * img)) return st;
+    p_lvl[l] = parts.add<int16_t>(nodes * img);
+    if (l > 0 && l < L - 1) p_rec[l] = parts.add<int16_t>(nodes * img);
+    if (l < L - 1) p_serial[l] = n_serial, n_serial += nodes;
+  }
+  const size_t p_code = parts.add<int8_t>(nsg), p_zv = parts.add<uint16_t>(nsg * S), p_gw = parts.add<uint32_t>(geo.ng),
+               p_off = parts.add<uint32_t>((size_t)geo.ng + 1), p_small = parts.add<unsigned long long>(n_small),
+               p_host = parts.add<char>(sizeof(RangeTab) + 4 * n_serial);
+  Scratch ws(s);
+  if (lfc_status st = ws.alloc(parts.bytes)) return st;
+  char *base = static_cast<char *>(ws.p);
+  std::vector<int16_t *> lvl(L), rec(L, nullptr);
+  std::vector<const int32_t *> serial(L, nullptr);
+  // the host's tables in one copy: the range table, the serial numbers
+  std::vector<char> host(sizeof(RangeTab) + 4 * n_serial);
+  std::memcpy(host.data(), &rt, sizeof rt);
+  for (int l = 0; l < L; l++) {
+    lvl[l] = reinterpret_cast<int16_t *>(base + p_lvl[l]);
+    if (l > 0 && l < L - 1) rec[l] = reinterpret_cast<int16_t *>(base + p_rec[l]);
     if (l < L - 1) {
-      if (l > 0)
-        if (lfc_status st = db.alloc(&rec[l], nodes * img)) return st;
-      if (lfc_status st = db.alloc(&serial[l], nodes)) return st;
-      if (hipMemcpyAsync(serial[l], tt.serial[l].data(), 4 * nodes, hipMemcpyHostToDevice, s) != hipSuccess)
-        return fail(LFC_E_HIP, "lfc_encode_gpu: copy of the tree tables");
+      const size_t at = sizeof(RangeTab) + 4 * p_serial[l];
+      std::memcpy(host.data() + at, tt.serial[l].data(), 4 * tt.serial[l].size());
+      serial[l] = reinterpret_cast<const int32_t *>(base + p_host + at);
     }
   }
+  if (hipMemcpyAsync(base + p_host, host.data(), host.size(), hipMemcpyHostToDevice, s) != hipSuccess)
+    return fail(LFC_E_HIP, "lfc_encode_gpu: copy of the tables");
+  const RangeTab *d_rt = reinterpret_cast<const RangeTab *>(base + p_host);
+  int8_t *code_tab = reinterpret_cast<int8_t *>(base + p_code);
+  uint16_t *zv = reinterpret_cast<uint16_t *>(base + p_zv);
+  uint32_t *gw = reinterpret_cast<uint32_t *>(base + p_gw), *d_off = reinterpret_cast<uint32_t *>(base + p_off);
+  unsigned long long *small = reinterpret_cast<unsigned long long *>(base + p_small);
   rec[L - 1] = lvl[L - 1];   // the top level is stored losslessly
-  if (lfc_status st = db.alloc(&code_tab, nsg)) return st;
-  if (lfc_status st = db.alloc(&zv, nsg * S)) return st;
-  if (lfc_status st = db.alloc(&gw, (size_t)geo.ng)) return st;
-  if (lfc_status st = db.alloc(&d_off, (size_t)geo.ng + 1)) return st;
-  if (lfc_status st = db.alloc(&small, n_small)) return st;
-  RangeTab *d_rt = nullptr;
-  if (lfc_status st = db.alloc(&d_rt, 1)) return st;
-  if (hipMemcpyAsync(d_rt, &rt, sizeof rt, hipMemcpyHostToDevice, s) != hipSuccess)
-    return fail(LFC_E_HIP, "lfc_encode_gpu: copy of the range table");
   if (hipMemsetAsync(small, 0, 8 * n_small, s) != hipSuccess ||
       hipMemsetAsync(code_tab, 0xFF, std::max<size_t>(nsg, 1), s) != hipSuccess)
     return fail(LFC_E_HIP, "lfc_encode_gpu: clearing tables");
@@ -654,8 +673,7 @@ extern "C" lfc_status lfc_encode_gpu(const uint8_t *d_rgb, const lfc_params *p, 
       constexpr int B = decltype(n)::value;
       hipLaunchKernelGGL(k_enc_residual<B>, dim3((unsigned)((geo.nb + kT - 1) / kT), 3, geo.lu[l + 1] * geo.lv[l + 1]),
                          dim3(kT), 0, s, (const int16_t *)lvl[l], (const int16_t *)rec[l + 1], rec[l],
-                         (const int32_t *)serial[l], code_tab, zv, stats && l == 0 ? small + at_sse : nullptr, err, g,
-                         (const RangeTab *)d_rt, l);
+                         serial[l], code_tab, zv, stats && l == 0 ? small + at_sse : nullptr, err, g, d_rt, l);
     });
     if (lfc_status st = launched("residuals")) return st;
   }
@@ -695,36 +713,43 @@ extern "C" lfc_status lfc_encode_gpu(const uint8_t *d_rgb, const lfc_params *p, 
   const uint64_t rkv_off = kHeaderBytes, off_off = rkv_off + rkv_bytes, srv_off = off_off + 4ull * (geo.ng + 1);
   if (stats) stats->stream_bytes = srv_off + 4 * srv_words;
   if (!stream_out) return LFC_OK;
-  uint32_t *d_srv = nullptr;
-  int16_t *d_top = nullptr;
-  if (lfc_status st = db.alloc(&d_srv, srv_words)) return st;
-  if (lfc_status st = db.alloc(&d_top, rkv_bytes / 2)) return st;
+  // the whole stream is laid out on the device and copied once
+  const size_t bytes = srv_off + 4 * srv_words;
+  Scratch ds(s);
+  if (lfc_status st = ds.alloc(bytes)) return st;
+  char *stream = static_cast<char *>(ds.p);
   by_block([&](auto n) {
     constexpr int B = decltype(n)::value;
-    // (one wave more than groups: it writes the section's two spare words)
+    // (one wave more than groups: it writes the last offset and the section's two spare words)
     hipLaunchKernelGGL(k_enc_pack<B>, dim3((unsigned)((geo.ng + kT / 64) / (kT / 64))), dim3(kT), 0, s,
-                       (const int8_t *)code_tab, (const uint16_t *)zv, (const uint32_t *)d_off, d_srv, g);
+                       (const int8_t *)code_tab, (const uint16_t *)zv, (const uint32_t *)d_off,
+                       reinterpret_cast<uint32_t *>(stream + off_off), reinterpret_cast<uint32_t *>(stream + srv_off), g);
     const int64_t rows = (int64_t)geo.n_top * geo.nb * 3 * B;
     hipLaunchKernelGGL(k_enc_top_blocks<B>, dim3((unsigned)((rows + kT - 1) / kT)), dim3(kT), 0, s,
-                       (const int16_t *)lvl[L - 1], d_top, g, geo.n_top);
+                       (const int16_t *)lvl[L - 1], reinterpret_cast<int16_t *>(stream + rkv_off), g, geo.n_top);
   });
   if (lfc_status st = launched("packing")) return st;
-  std::vector<uint8_t> out;
-  try {
-    out.assign(srv_off + 4 * srv_words, 0);
-  } catch (const std::bad_alloc &) {
-    return fail(LFC_E_NOMEM, "lfc_encode_gpu: out of host memory");
-  }
-  put_stream_header(out.data(), geo, *p, mask, rkv_off, off_off, srv_off);
-  if (hipMemcpyAsync(out.data() + off_off, d_off, 4ull * (geo.ng + 1), hipMemcpyDeviceToHost, s) != hipSuccess ||
-      hipMemcpyAsync(out.data() + rkv_off, d_top, rkv_bytes, hipMemcpyDeviceToHost, s) != hipSuccess ||
-      hipMemcpyAsync(out.data() + srv_off, d_srv, 4 * srv_words, hipMemcpyDeviceToHost, s) != hipSuccess ||
-      hipStreamSynchronize(s) != hipSuccess)
+  uint8_t *out = static_cast<uint8_t *>(stream_alloc(bytes));
+  if (!out) return fail(LFC_E_NOMEM, "lfc_encode_gpu: out of host memory");
+  put_stream_header(out, geo, *p, mask, rkv_off, off_off, srv_off);
+  if (hipMemcpyAsync(out + kHeaderBytes, stream + kHeaderBytes, bytes - kHeaderBytes, hipMemcpyDeviceToHost, s) !=
+          hipSuccess ||
+      hipStreamSynchronize(s) != hipSuccess) {
+    stream_free(out);
     return fail(LFC_E_HIP, "lfc_encode_gpu: copy of the stream");
-  void *mem = std::malloc(out.size());
-  if (!mem) return fail(LFC_E_NOMEM, "lfc_encode_gpu: out of host memory");
-  std::memcpy(mem, out.data(), out.size());
-  *stream_out = mem;
-  *bytes_out = out.size();
+  }
+  *stream_out = out;
+  *bytes_out = bytes;
   return LFC_OK;
+}
+
+}  // namespace
+
+extern "C" lfc_status lfc_encode_gpu(const uint8_t *d_rgb, const lfc_params *p, void **stream_out, size_t *bytes_out,
+                                     lfc_encode_stats *stats, hipStream_t s) {
+  try {
+    return encode_gpu(d_rgb, p, stream_out, bytes_out, stats, s);
+  } catch (const std::bad_alloc &) {
+    return lfc::fail(LFC_E_NOMEM, "lfc_encode_gpu: out of host memory");
+  }
 }

@@ -14,8 +14,12 @@
 #include <cstdlib>
 #include <cstring>
 #include <functional>
+#include <mutex>
 #include <new>
 #include <thread>
+#include <unordered_map>
+
+#include <sys/mman.h>
 
 #include "encode.h"
 #include "internal.h"
@@ -40,6 +44,82 @@ static std::string fmt(const char *f, ...) {
   vsnprintf(buf, sizeof buf, f, ap);
   va_end(ap);
   return buf;
+}
+
+// ---------------------------------------------------------------------------
+// host memory of encoded streams
+// ---------------------------------------------------------------------------
+
+// A fresh large allocation costs a page fault per 4 KB at its first writing
+// (several ms for a stream of 25 MB, more than encoding it on the GPU), so
+// streams of at least kStreamBig bytes come from memory advised to use huge
+// pages, and the last one freed, up to kStreamKeep bytes, is kept for the next
+// (it goes back when a larger one takes its place, else when the process
+// ends).  Every thread may allocate and free.
+constexpr size_t kStreamBig = (size_t)1 << 20, kStreamKeep = (size_t)128 << 20, kHugePage = (size_t)2 << 20;
+
+namespace {
+struct StreamMemory {
+  std::mutex mu;
+  std::unordered_map<void *, size_t> big;   // sizes of the large allocations in use
+  void *kept = nullptr;
+  size_t kept_bytes = 0;
+};
+StreamMemory &stream_memory() {
+  static StreamMemory *m = new StreamMemory;   // (outlives every static destructor that frees a stream)
+  return *m;
+}
+}  // namespace
+
+void *stream_alloc(size_t bytes) noexcept {
+  if (bytes < kStreamBig) return std::malloc(std::max<size_t>(bytes, 1));
+  try {
+    StreamMemory &m = stream_memory();
+    const size_t need = (bytes + kHugePage - 1) / kHugePage * kHugePage;
+    void *p = nullptr;
+    size_t have = need;
+    {
+      std::lock_guard<std::mutex> lock(m.mu);
+      if (m.kept && m.kept_bytes >= need) {
+        p = m.kept;
+        have = m.kept_bytes;
+        m.kept = nullptr;
+      }
+    }
+    if (!p) {
+      p = std::aligned_alloc(kHugePage, need);
+      if (!p) return nullptr;
+      (void)madvise(p, need, MADV_HUGEPAGE);
+    }
+    std::lock_guard<std::mutex> lock(m.mu);
+    try {
+      m.big.emplace(p, have);
+    } catch (...) {
+      std::free(p);
+      return nullptr;
+    }
+    return p;
+  } catch (...) {
+    return nullptr;
+  }
+}
+
+void stream_free(void *p) noexcept {
+  if (!p) return;
+  StreamMemory &m = stream_memory();
+  {
+    std::lock_guard<std::mutex> lock(m.mu);
+    const auto it = m.big.find(p);
+    if (it != m.big.end()) {
+      const size_t bytes = it->second;
+      m.big.erase(it);
+      if (bytes <= kStreamKeep && (!m.kept || bytes > m.kept_bytes)) {
+        std::swap(m.kept, p);
+        m.kept_bytes = bytes;
+      }
+    }
+  }
+  std::free(p);
 }
 
 // ---------------------------------------------------------------------------
@@ -1393,7 +1473,7 @@ extern "C" lfc_status lfc_encode_ex(const uint8_t *rgb, const lfc_params *p, voi
     return fail(LFC_E_NOMEM, "lfc_encode: out of host memory");
   }
   if (st != LFC_OK || !stream_out) return st;
-  void *mem = std::malloc(buf.size());
+  void *mem = stream_alloc(buf.size());
   if (!mem) return fail(LFC_E_NOMEM, "lfc_encode: out of host memory");
   std::memcpy(mem, buf.data(), buf.size());
   *stream_out = mem;
@@ -1440,7 +1520,7 @@ extern "C" lfc_status lfc_encode_ctl(const uint8_t *rgb, const lfc_params *p, lf
     return fail(LFC_E_NOMEM, "lfc_encode_ctl: out of host memory");
   }
   if (st != LFC_OK || !stream_out) return st;
-  void *mem = std::malloc(buf.size());
+  void *mem = stream_alloc(buf.size());
   if (!mem) return fail(LFC_E_NOMEM, "lfc_encode_ctl: out of host memory");
   std::memcpy(mem, buf.data(), buf.size());
   *stream_out = mem;
@@ -1453,7 +1533,7 @@ extern "C" lfc_status lfc_encode(const uint8_t *rgb, const lfc_params *p, void *
   return lfc_encode_ex(rgb, p, stream_out, bytes_out, nullptr);
 }
 
-extern "C" void lfc_free(void *ptr) { std::free(ptr); }
+extern "C" void lfc_free(void *ptr) { stream_free(ptr); }
 
 extern "C" lfc_status lfc_validate(const void *stream, size_t bytes, lfc_params *p_out) {
   if (!stream) return fail(LFC_E_INVALID, "lfc_validate: null stream");
