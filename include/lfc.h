@@ -601,9 +601,8 @@ lfc_status lfc_batch_create(lfc_batch **out);
  * Paths (Sec. 3.6: decode the blocks a view needs, then interpolate): a
  * light field whose requests in the call cover at least a twentieth of the
  * pixels it holds is decoded once, only the views its requests read, as
- * 8-bit RGB, by one persistent launch over every such light field of a block
- * size (workgroups take (strip, part) items of all of them from a device
- * counter), then one launch interpolates all those requests; the other
+ * 8-bit RGB, by one launch over every such light field of a block size, then
+ * one launch interpolates all those requests; the other
  * requests render by output tiles, each decoding its footprint.  Both give
  * the bytes lfc_render_views gives for the request alone.  The decoded views
  * live in device buffers the context allocates on first use per light field
@@ -642,8 +641,7 @@ lfc_status lfc_batch_destroy(lfc_batch *b);
  * copied to the device at creation, its decoded-view buffers allocated then
  * and held by the plan, and, with graph != 0, its launches captured once
  * into a HIP graph, so that each lfc_batch_plan_launch is one graph launch
- * (the graph holds kernels only; the persistent colour decode leaves its
- * work counters at zero for the next launch).  Each launch writes what
+ * (the graph holds kernels only).  Each launch writes what
  * lfc_batch_render of the same arguments writes.  Launches of one plan must
  * not overlap (use one stream); the light fields and the output buffers
  * must outlive the plan.  lfc_batch_plan_destroy waits for the device (it

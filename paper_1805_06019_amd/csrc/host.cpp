@@ -452,10 +452,12 @@ static void build_schedule(const Geometry &g, const std::vector<uint32_t> &off, 
 // strip (block row by, strip sx of 64/B blocks) covers all three channels,
 // and its chunks count the stored blocks of the three channels against the
 // tile capacity.  Otherwise as build_schedule:
-//   strip record: [0] chunks, [1..chunks] chunk record offsets from the
-//   strip's start, [chunks+1] the strip's length;
-//   chunk record: q0, nq, nn, n0, n01, n, masks[3][nn] (channel-major),
-//   first slots[3][nn] (16-bit, two per word), runs[nq][3 words],
+//   strip record: [0] chunks, then from word 8 eight words per chunk (the
+//   offset of its tables from the strip's start, q0, nq, nn, n0, n01, n, 0), so
+//   that a workgroup reads a chunk's header in one load;
+//   chunk tables: masks[3][nn] (channel-major) and
+//   first slots[3][nn] (B = 2: 16-bit, two per word, after the masks; else, a
+//   strip having at most 16 blocks, in the masks' upper halves), runs[nq][3 words],
 //   entries[n], items[n] (32-bit: slot << 20 | node << 8 | channel << 6 |
 //   block; a chunk has at most kRGBNodeCap nodes and kRGBNodeCap runs).
 static void build_schedule_rgb(const Geometry &g, const std::vector<uint32_t> &off, const std::vector<uint32_t> &srv,
@@ -486,7 +488,7 @@ static void build_schedule_rgb(const Geometry &g, const std::vector<uint32_t> &o
         return __builtin_popcount(m[(size_t)s]) + __builtin_popcount(m[ns + (size_t)s]) +
                __builtin_popcount(m[2 * ns + (size_t)s]);
       };
-      std::vector<uint32_t> head(1, 0), body;
+      std::vector<uint32_t> head(8, 0), body;
       for (int q = 0; q < nruns;) {
         // greedy: consecutive runs while their nodes' stored blocks fit the tile
         std::vector<int> leaves, ancs;
@@ -555,16 +557,15 @@ static void build_schedule_rgb(const Geometry &g, const std::vector<uint32_t> &o
           }
         const uint32_t n0 = (uint32_t)ent[0].size(), n01 = n0 + (uint32_t)ent[1].size();
         const uint32_t n = n01 + (uint32_t)ent[2].size();
-        head.push_back((uint32_t)body.size());   // made absolute below
-        body.push_back((uint32_t)q);
-        body.push_back((uint32_t)k);
-        body.push_back((uint32_t)nn);
-        body.push_back(n0);
-        body.push_back(n01);
-        body.push_back(n);
-        body.insert(body.end(), masks.begin(), masks.end());
-        for (int i = 0; i < 3 * nn; i += 2)
-          body.push_back(bases[(size_t)i] | (i + 1 < 3 * nn ? bases[(size_t)i + 1] << 16 : 0u));
+        // (the offset of the chunk's tables is made absolute below)
+        for (uint32_t w : {(uint32_t)body.size(), (uint32_t)q, (uint32_t)k, (uint32_t)nn, n0, n01, n, 0u}) head.push_back(w);
+        if (g.B == 2) {
+          body.insert(body.end(), masks.begin(), masks.end());
+          for (int i = 0; i < 3 * nn; i += 2)
+            body.push_back(bases[(size_t)i] | (i + 1 < 3 * nn ? bases[(size_t)i + 1] << 16 : 0u));
+        } else {
+          for (int i = 0; i < 3 * nn; i++) body.push_back(masks[(size_t)i] | bases[(size_t)i] << 16);
+        }
         for (int j = 0; j < k; j++) {
           const int32_t *r = &batch[(size_t)(q + j) * kBatchWords];
           uint32_t h[4] = {L > 1 ? (uint32_t)loc[(size_t)r[10]] : 0xFFFFu, 0xFFFFu, 0xFFFFu, 0xFFFFu};
@@ -578,11 +579,10 @@ static void build_schedule_rgb(const Geometry &g, const std::vector<uint32_t> &o
         for (int s : nodes) loc[(size_t)s] = -1;
         q += k;
       }
-      const uint32_t nck = (uint32_t)(head.size() - 1);
+      const uint32_t nck = (uint32_t)(head.size() / 8 - 1), hdr = (uint32_t)head.size();
       head[0] = nck;
-      const uint32_t hdr = nck + 2;
-      for (uint32_t i = 1; i <= nck; i++) head[i] += hdr;
-      head.push_back(hdr + (uint32_t)body.size());
+      for (uint32_t i = 1; i <= nck; i++) head[8 * i] += hdr;
+      body.resize((body.size() + 7) & ~(size_t)7, 0u);   // (strips start at a multiple of eight words)
       std::vector<uint32_t> &w = per[(size_t)st];
       w = head;
       w.insert(w.end(), body.begin(), body.end());
@@ -607,6 +607,8 @@ static void build_schedule_rgb(const Geometry &g, const std::vector<uint32_t> &o
 struct StripTables {
   std::vector<uint32_t> sched, strip_off, order, need;
   uint32_t max_words = 0;
+  // colour schedule: most chunks of a strip, gather-table words and runs of a chunk
+  int max_chunks = 1, tab_cap = 0, run_cap = 0;
 };
 
 static void make_strip_tables(const Geometry &g, const std::vector<uint32_t> &off, const std::vector<uint32_t> &srv,
@@ -676,10 +678,23 @@ static void make_strip_tables_rgb(const Geometry &g, const std::vector<uint32_t>
         w += off[gi + 1] - off[gi];
       }
     cost[st] = w;
+    const uint32_t *rec = &t.sched[t.strip_off[st]];
+    t.max_chunks = std::max(t.max_chunks, (int)rec[0]);
+    for (uint32_t ci = 0; ci < rec[0]; ci++) {
+      const int nq = (int)rec[8 + 8 * ci + 2], nn = (int)rec[8 + 8 * ci + 3];
+      t.tab_cap = std::max(t.tab_cap, (g.B == 2 ? 3 * nn + (3 * nn + 1) / 2 : 3 * nn) + 3 * nq);
+      t.run_cap = std::max(t.run_cap, nq);
+    }
   }
-  t.order.resize(nst);
-  for (size_t i = 0; i < nst; i++) t.order[i] = (uint32_t)i;
-  std::stable_sort(t.order.begin(), t.order.end(), [&](uint32_t x, uint32_t y) { return cost[x] > cost[y]; });
+  std::vector<uint32_t> perm(nst);
+  for (size_t i = 0; i < nst; i++) perm[i] = (uint32_t)i;
+  std::stable_sort(perm.begin(), perm.end(), [&](uint32_t x, uint32_t y) { return cost[x] > cost[y]; });
+  // one entry per strip: the strip, its record's first word
+  t.order.resize(2 * nst);
+  for (size_t i = 0; i < nst; i++) {
+    t.order[2 * i] = perm[i];
+    t.order[2 * i + 1] = t.strip_off[perm[i]];
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -1600,7 +1615,7 @@ extern "C" lfc_status lfc_open_ex(const void *stream, size_t bytes, const lfc_op
   } catch (const std::bad_alloc &) {
     return fail(LFC_E_NOMEM, "lfc_open: out of host memory");
   }
-  Part parts[17] = {
+  Part parts[16] = {
       {ps.rkv, ps.rkv_bytes, 0},
       {ps.off.data(), ps.off.size() * 4, 0},
       {ps.srv.data(), ps.srv.size() * 4, 0},
@@ -1615,7 +1630,6 @@ extern "C" lfc_status lfc_open_ex(const void *stream, size_t bytes, const lfc_op
       {strip_off.data(), strip_off.size() * 4, 0},
       {order.data(), order.size() * 4, 0},
       {rgbt.sched.data(), rgbt.sched.size() * 4, 0},
-      {rgbt.strip_off.data(), rgbt.strip_off.size() * 4, 0},
       {rgbt.order.data(), rgbt.order.size() * 4, 0},
       {ps.dir2.data(), ps.dir2.size() * 4, 0},
   };
@@ -1671,12 +1685,12 @@ extern "C" lfc_status lfc_open_ex(const void *stream, size_t bytes, const lfc_op
   lf->d_strip_off = reinterpret_cast<const uint32_t *>(d + parts[11].at);
   lf->d_order = reinterpret_cast<const uint32_t *>(d + parts[12].at);
   lf->d_sched_rgb = reinterpret_cast<const uint32_t *>(d + parts[13].at);
-  lf->d_strip_off_rgb = reinterpret_cast<const uint32_t *>(d + parts[14].at);
-  lf->d_order_rgb = reinterpret_cast<const uint32_t *>(d + parts[15].at);
-  lf->d_dir2 = reinterpret_cast<const uint32_t *>(d + parts[16].at);
+  lf->d_order_rgb = reinterpret_cast<const uint32_t *>(d + parts[14].at);
+  lf->d_dir2 = reinterpret_cast<const uint32_t *>(d + parts[15].at);
   lf->tile_cap_rgb = tile_cap_rgb;
-  for (size_t st = 0; st + 1 < rgbt.strip_off.size(); st++)
-    lf->rgb_max_chunks = std::max<int>(lf->rgb_max_chunks, (int)rgbt.sched[rgbt.strip_off[st]]);
+  lf->rgb_max_chunks = rgbt.max_chunks;
+  lf->rgb_tab_cap = rgbt.tab_cap;
+  lf->rgb_run_cap = rgbt.run_cap;
   lf->d_err = reinterpret_cast<int32_t *>(d + parts[8].at);
   // LDS staging of the whole-field kernel is sized by the largest strip:
   // group words plus the strip's decode schedule
@@ -1921,19 +1935,20 @@ extern "C" lfc_status lfc_tune_decode_rgb(lfc_lf *lf, uint32_t *d_out, int32_t r
     return LFC_OK;
   };
   struct Saved {
-    int cap, max_chunks;
-    const uint32_t *sched, *strip_off, *order;
+    int cap, max_chunks, tab_cap, run_cap;
+    const uint32_t *sched, *order;
     void *own;
   };
   auto save = [&]() {
-    return Saved{lf->tile_cap_rgb, lf->rgb_max_chunks, lf->d_sched_rgb, lf->d_strip_off_rgb, lf->d_order_rgb,
-                 lf->d_sched_rgb_own};
+    return Saved{lf->tile_cap_rgb, lf->rgb_max_chunks, lf->rgb_tab_cap, lf->rgb_run_cap, lf->d_sched_rgb,
+                 lf->d_order_rgb, lf->d_sched_rgb_own};
   };
   auto restore = [&](const Saved &v) {
     lf->tile_cap_rgb = v.cap;
     lf->rgb_max_chunks = v.max_chunks;
+    lf->rgb_tab_cap = v.tab_cap;
+    lf->rgb_run_cap = v.run_cap;
     lf->d_sched_rgb = v.sched;
-    lf->d_strip_off_rgb = v.strip_off;
     lf->d_order_rgb = v.order;
     lf->d_sched_rgb_own = v.own;
   };
@@ -1972,8 +1987,7 @@ extern "C" lfc_status lfc_tune_decode_rgb(lfc_lf *lf, uint32_t *d_out, int32_t r
       if (seen) continue;
       StripTables t;
       make_strip_tables_rgb(g, off, srv, dbase, poff, batch, cap, t);
-      const size_t a1 = align256(4 * t.sched.size()), a2 = a1 + align256(4 * t.strip_off.size());
-      const size_t total = a2 + align256(4 * t.order.size());
+      const size_t a1 = align256(4 * t.sched.size()), total = a1 + align256(4 * t.order.size());
       void *buf = nullptr;
       if (hipMalloc(&buf, total) != hipSuccess) {
         (void)hipGetLastError();
@@ -1981,20 +1995,17 @@ extern "C" lfc_status lfc_tune_decode_rgb(lfc_lf *lf, uint32_t *d_out, int32_t r
       }
       char *d = static_cast<char *>(buf);
       if (hipMemcpy(d, t.sched.data(), 4 * t.sched.size(), hipMemcpyHostToDevice) != hipSuccess ||
-          hipMemcpy(d + a1, t.strip_off.data(), 4 * t.strip_off.size(), hipMemcpyHostToDevice) != hipSuccess ||
-          hipMemcpy(d + a2, t.order.data(), 4 * t.order.size(), hipMemcpyHostToDevice) != hipSuccess) {
+          hipMemcpy(d + a1, t.order.data(), 4 * t.order.size(), hipMemcpyHostToDevice) != hipSuccess) {
         (void)hipFree(buf);
         st = fail(LFC_E_HIP, "lfc_tune_decode_rgb: copy of the strip tables");
         break;
       }
-      int max_chunks = 1;
-      for (size_t k = 0; k + 1 < t.strip_off.size(); k++)
-        max_chunks = std::max<int>(max_chunks, (int)t.sched[t.strip_off[k]]);
       lf->tile_cap_rgb = cap;
-      lf->rgb_max_chunks = max_chunks;
+      lf->rgb_max_chunks = t.max_chunks;
+      lf->rgb_tab_cap = t.tab_cap;
+      lf->rgb_run_cap = t.run_cap;
       lf->d_sched_rgb = reinterpret_cast<const uint32_t *>(d);
-      lf->d_strip_off_rgb = reinterpret_cast<const uint32_t *>(d + a1);
-      lf->d_order_rgb = reinterpret_cast<const uint32_t *>(d + a2);
+      lf->d_order_rgb = reinterpret_cast<const uint32_t *>(d + a1);
       lf->d_sched_rgb_own = buf;
       cands.push_back(save());
       const lfc_status ts = timed(&ms);

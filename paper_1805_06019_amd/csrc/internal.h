@@ -97,10 +97,10 @@ struct lfc_lf {
   const uint32_t *d_strip_off = nullptr; // [n_strips+1] word offset of each strip's record
   const uint32_t *d_order = nullptr;     // [n_strips] strips in the order the whole-field kernel takes them
   const uint32_t *d_sched_rgb = nullptr;     // colour decode schedule (strips of all three channels)
-  const uint32_t *d_strip_off_rgb = nullptr; // [n_strips_rgb+1]
-  const uint32_t *d_order_rgb = nullptr;     // [n_strips_rgb] costliest first
+  const uint32_t *d_order_rgb = nullptr;     // [n_strips_rgb][2] strip, first word of its record; costliest first
   int tile_cap_rgb = 0;              // blocks of the colour kernel's compact tile
   int rgb_max_chunks = 1;            // most chunks of one strip in the colour schedule
+  int rgb_tab_cap = 0, rgb_run_cap = 0;   // most gather-table words and runs of one of its chunks
   int32_t *d_err = nullptr;          // device error flag
   int tile_cap = 0;                  // blocks of the whole-field kernel's compact residual tile
   int64_t stage_cap = 0;             // LDS words for staging a strip (-1: as it needs, 0: none); the

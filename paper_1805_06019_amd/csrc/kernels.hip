@@ -925,9 +925,6 @@ __device__ __forceinline__ void cell(float x, int n, int &i0, int &i1, float &f)
 
 __device__ __forceinline__ float lerpf(float a, float b, float f) { return a + f * (b - a); }
 
-__device__ __forceinline__ int32_t lo16(uint32_t w) { return (int32_t)(int16_t)(w & 0xFFFFu); }
-__device__ __forceinline__ int32_t hi16(uint32_t w) { return (int32_t)(int16_t)(w >> 16); }
-
 // The residual-block entry (payload offset << 5 | code) of node s in group g,
 // or kAbsent, through the directory built at initialisation.
 __device__ __forceinline__ uint32_t locate(const RAArgs &a, int g, int s, const uint32_t **gw_out) {
@@ -952,13 +949,28 @@ constexpr int kRenderThreads = 512;
 // whose path passes through that node (neighbouring views often share
 // ancestors).  The sums are converted to RGB (inverse YCoCg-R, clamped) in
 // place, then every output pixel interpolates its 16 taps in FP32.
-// Inverse YCoCg-R (Sec. 4) of one sample, clamped to 8 bits, packed R | G << 8 | B << 16.
-__device__ __forceinline__ uint32_t rgb_pack(int32_t yv, int32_t co, int32_t cg) {
-  const int32_t t = yv - (cg >> 1);
-  const int32_t G = cg + t;
-  const int32_t Bc = t - (co >> 1);
-  const int32_t R = Bc + co;
-  return (uint32_t)min(max(R, 0), 255) | ((uint32_t)min(max(G, 0), 255) << 8) | ((uint32_t)min(max(Bc, 0), 255) << 16);
+// Inverse YCoCg-R (Sec. 4) of two pixels in packed 16-bit samples, clamped to
+// 8 bits and packed R | G << 8 | B << 16 each.  With h = cg >> 1 and k = co >> 1:
+//   G = y + (cg - h),  B = y - (h + k),  R = y - (h - (co - k)),
+// where every bracket fits 16 bits for all samples, so that each channel is one
+// saturating operation, whose clamp to 8 bits is that of the exact value
+// (tests/test_colour_packed.py).  Six operations a pixel against fourteen in 32
+// bits.
+typedef short i16x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t sat_bytes(i16x2 v) {   // both halves to 8 bits, in the two low bytes
+  uint32_t r;
+  asm("v_sat_pk_u8_i16 %0, %1" : "=v"(r) : "v"(v));
+  return r;
+}
+__device__ __forceinline__ void rgb_pack2(uint32_t yw, uint32_t cow, uint32_t cgw, uint32_t &p0, uint32_t &p1) {
+  const i16x2 y = __builtin_bit_cast(i16x2, yw), co = __builtin_bit_cast(i16x2, cow), cg = __builtin_bit_cast(i16x2, cgw);
+  const i16x2 h = cg >> 1, k = co >> 1;
+  const uint32_t g = sat_bytes(__builtin_elementwise_add_sat(y, (i16x2)(cg - h)));
+  const uint32_t b = sat_bytes(__builtin_elementwise_sub_sat(y, (i16x2)(h + k)));
+  const uint32_t r = sat_bytes(__builtin_elementwise_sub_sat(y, (i16x2)(h - (co - k))));
+  const uint32_t rg = __builtin_amdgcn_perm(g, r, 0x05010400u);   // R0 G0 R1 G1
+  p0 = __builtin_amdgcn_perm(b, rg, 0x0c040100u);
+  p1 = __builtin_amdgcn_perm(b, rg, 0x0c050302u);
 }
 
 // Source views of an output pixel: k = 0: (u0, v0), 1: (u1, v0), 2: (u0, v1),
@@ -1163,11 +1175,11 @@ __device__ __forceinline__ void render_tile(const RenderArgs &a, const lfc_view 
 #pragma unroll
     for (int w = 0; w < SLOT; w++) v[w] = slot[w];
 #pragma unroll
-    for (int i = 0; i < S; i++) {
-      const int32_t yv = (i & 1) ? hi16(v[i / 2]) : lo16(v[i / 2]);
-      const int32_t co = (i & 1) ? hi16(v[S / 2 + i / 2]) : lo16(v[S / 2 + i / 2]);
-      const int32_t cg = (i & 1) ? hi16(v[S + i / 2]) : lo16(v[S + i / 2]);
-      slot[i] = rgb_pack(yv, co, cg);
+    for (int i = 0; i < S / 2; i++) {
+      uint32_t p0, p1;
+      rgb_pack2(v[i], v[S / 2 + i], v[S + i], p0, p1);
+      slot[2 * i] = p0;
+      slot[2 * i + 1] = p1;
     }
   }
   __syncthreads();
@@ -1232,12 +1244,16 @@ __global__ __launch_bounds__(kRenderThreads) void k_render_multi(const RenderReq
 
 // LDS words before the tile: LUT; the start words of the strip's 3 x 64/B
 // groups; a flag and a bit per node of the chunk for the views a render
-// reads; the view mask; the chunk's per-node masks and first slots (a chunk
-// has at most lfc::kRGBNodeCap nodes).
+// reads; then, sized for the light field, the view mask, a chunk's gather table
+// (masks and first slots, run node positions), its runs' views and roots, and
+// the list of the pairs that are wanted.
 using lfc::kRGBNodeCap;
 constexpr int kRGBNeedWords = 128;        // views a render may mask: at most 32 x 128
-constexpr int kRGBHeadWords = 192 + 96 + 4 + kRGBNodeCap / 32 + kRGBNeedWords + 3 * kRGBNodeCap +
-                               3 * kRGBNodeCap / 2 + 3 * kRGBNodeCap + 4 * kRGBNodeCap / 2;
+constexpr int kRGBFixedWords = 192 + 96 + 4 + kRGBNodeCap / 32;
+constexpr int kRGBRecWords = 5;           // of a run: four views (-1: none), the root
+__host__ __device__ constexpr int rgb_head_words(int need_words, int tab_cap, int run_cap) {
+  return (kRGBFixedWords + need_words + tab_cap + (kRGBRecWords + 2) * run_cap + 3) & ~3;
+}
 constexpr int kRGBKeyWordsMax = 6144;     // key-view rows of a strip staged in LDS up to 24 KB
 
 struct RGBArgs {
@@ -1245,8 +1261,7 @@ struct RGBArgs {
   const uint32_t *off;
   const uint32_t *srv;
   const uint32_t *sched;      // colour decode schedule: one record per strip (build_schedule_rgb on the host)
-  const uint32_t *strip_off;  // [n_strips+1]
-  const uint32_t *order;      // [n_strips] strip of each workgroup, costliest first
+  const uint32_t *order;      // [n_strips][2] strip and first word of its record, costliest first
   const int32_t *batch;       // [nbatch][kBatchWords] runs of sibling leaves
   const uint32_t *vneed;      // [ceil(nv/32)] bit per view to write (nv <= 32 kRGBNeedWords), or null: every view
   uint32_t *out;              // [nv][hp][wp] pixels R | G << 8 | B << 16
@@ -1254,6 +1269,7 @@ struct RGBArgs {
   int n_top, key_words;       // LDS words of the strip's key-view rows of all channels (0: read from global)
   int tile_cap;
   int parts;                  // workgroups per strip: part p takes the chunks ci with ci % parts == p
+  int need_words, tab_cap, run_cap;   // sizes of the LDS tables: view mask, gather table, runs
   // with vneed null: the cameras of a render, whose four grid neighbours
   // each workgroup marks itself (null: every view, unless vneed is given)
   const lfc_view *views = nullptr;
@@ -1263,34 +1279,78 @@ struct RGBArgs {
 // One workgroup = one strip of 64/B blocks of one block row, all three
 // channels, or every parts-th chunk of it (a strip of three channels holds
 // three times the blocks of a one-channel strip, so strips alone would not
-// fill the chip).  Phase A stages the LUT, the strip's group starts, the
-// view mask and the key-view rows; the groups and the decode schedule are
-// read from global memory.  Per chunk of the strip's runs: its node masks
-// and first slots are copied to LDS while (3) every stored residual block of
-// the chunk, of any channel (with a view mask: of a node that a wanted view
-// reads), is decoded once into the compact tile; then (4) one run per wave:
-// a lane owns one sibling and 4 pixels of the strip's rows, sums key row +
-// ancestor rows + leaf row of each channel, converts the pixels to RGB
-// (inverse YCoCg-R, clamped) and stores 16 bytes per row.
-// The work of one workgroup (strip st, part) of the colour kernel; the LUT
-// in the first 192 words of smem is already filled.
+// fill the chip).  Phase A copies the LUT, the strip's group starts, the view
+// mask and the key-view rows to LDS.  Per chunk of the strip's runs: its node
+// masks, first slots, run positions and views are copied to LDS while (3) every
+// stored residual block of the chunk, of any channel (with a view mask: of a
+// node that a wanted view reads), is decoded once into the compact tile; then
+// (4) four (run, sibling) pairs per wave: a lane owns 4 pixels of the strip's
+// rows, sums key row + ancestor rows + leaf row of each channel, converts the
+// pixels to RGB (inverse YCoCg-R, clamped) and stores 16 bytes per row.
+// What bounds it is the issue of vector instructions and, per chunk, the chain
+// header - entry - payload - decode - barrier - gather; hence the packed colour
+// conversion, a gather without branches on the path's length (one body for each
+// depth of the tree), tables that the gather reads from LDS alone, the next
+// chunk's header and first entries read before this chunk's stores (loads wait
+// for older stores), and at most 80 registers and 53 KB, which let three
+// workgroups share a compute unit.  81 views of 625 x 434: 66 -> 44 us (12
+// against 26 million vector instructions), 2.4 TB/s of output and payload; the
+// views that 64 cameras read of 17 x 17 of 512 x 512: 132 -> 97 us.
 template <int B, bool KEYS>
-__device__ __forceinline__ void rgb_strip(const RGBArgs &a, int st, int part, uint32_t *smem) {
+__device__ __forceinline__ void rgb_strip(const RGBArgs &a, int wg, uint32_t *smem) {
   constexpr int S = B * B, NBLK = 64 / B, H = B / 2, HR = B;   // HR rows per lane
   const uint16_t *lut = reinterpret_cast<const uint16_t *>(smem);   // 384 x u16 = 192 words
   uint32_t *s_o0 = smem + 192;                          // [3][NBLK] group start words
-  uint32_t *s_nlist = smem + 288;                       // [0] listed pairs of the chunk ([2] is the multi kernel's)
+  uint32_t *s_nlist = smem + 288;                       // [0] listed pairs of the chunk
   uint32_t *s_node = s_nlist + 4;                       // wanted nodes of the chunk, a bit each
-  uint32_t *s_need = s_node + kRGBNodeCap / 32;         // the view mask
-  uint32_t *s_mf = s_need + kRGBNeedWords;              // masks[3][nn], first slots (16-bit), run node positions[nq][3]
-  uint16_t *s_list = reinterpret_cast<uint16_t *>(s_mf + 3 * kRGBNodeCap + 3 * kRGBNodeCap / 2 + 3 * kRGBNodeCap);
+  uint32_t *s_need = smem + kRGBFixedWords;             // the view mask
+  uint32_t *s_mf = s_need + a.need_words;               // masks and first slots [3][nn], run node positions[nq][3]
+  int32_t *s_rec = reinterpret_cast<int32_t *>(s_mf + a.tab_cap);   // [nq][kRGBRecWords]
+  uint16_t *s_list = reinterpret_cast<uint16_t *>(s_rec + kRGBRecWords * a.run_cap);
                                                         // (run << 2 | sibling) pairs of the chunk
-  uint32_t *tile = smem + kRGBHeadWords;                // [tile_cap + 1][S/2], the last slot zero
-  uint32_t *keys = tile + lf_tile_words(a.tile_cap, S); // [3][n_top][NBLK][S/2], blocks as in the tile
+  uint32_t *tile = smem + rgb_head_words(a.need_words, a.tab_cap, a.run_cap);   // [tile_cap + 1][S/2], the last slot zero
+  uint32_t *keys = tile + lf_tile_words(a.tile_cap, S); // [n_top][NBLK][3][S/2], blocks as in the tile
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // the workgroup's strip and part, and its first chunk's header (scalar loads)
+  const uniform_i32 ent = as_uniform(reinterpret_cast<const int32_t *>(a.order) + 2 * (wg / a.parts));
+  const int st = ent[0], part = wg % a.parts;
+  const uint32_t *gs = a.sched + (uint32_t)ent[1];
+  const uniform_i32 head = as_uniform(reinterpret_cast<const int32_t *>(gs));
+  const int nck = head[0];
+  int h_at = 0, q0 = 0, nq = 0, nn = 0;
+  uint32_t n0 = 0, n01 = 0, n = 0;
+  auto header = [&](int ci) {
+    const uniform_i32 h = head + 8 + 8 * ci;
+    h_at = h[0], q0 = h[1], nq = h[2], nn = h[3];
+    n0 = (uint32_t)h[4], n01 = (uint32_t)h[5], n = (uint32_t)h[6];
+  };
+  // a chunk's entries and items follow its masks, first slots and run positions
+  auto tables = [&](const uint32_t *&chunk, int &mf_words, const uint32_t *&ents, const uint32_t *&items) {
+    chunk = gs + h_at;
+    mf_words = B == 2 ? 3 * nn + (3 * nn + 1) / 2 : 3 * nn;
+    ents = chunk + mf_words + 3 * nq;
+    items = ents + n;
+  };
+  uint32_t e_nx = 0, t_nx = 0;   // the lane's next entry, requested ahead
+  auto request_first = [&] {
+    const uint32_t *chunk, *ents, *items;
+    int mf_words;
+    tables(chunk, mf_words, ents, items);
+    if ((uint32_t)tid < n) {
+      e_nx = ents[tid];
+      t_nx = items[tid];
+    }
+  };
+  if (part < nck) {
+    header(part);
+    request_first();
+  }
   const int sx = st % a.nsx, by = st / a.nsx;
   const bool masked = a.vneed != nullptr || a.views != nullptr;
+  if (tid < kLutEntries / 2) __builtin_amdgcn_global_load_lds(
+      (const __attribute__((address_space(1))) void *)(kLutTable.w + tid),
+      (__attribute__((address_space(3))) void *)(smem + (tid & ~63)), 4, 0, 0);
   if (tid < S / 2) tile[a.tile_cap * (S / 2) + tid] = 0u;
   if (tid < 64)
     for (int k = lane; k < 3 * NBLK; k += 64) {
@@ -1314,16 +1374,16 @@ __device__ __forceinline__ void rgb_strip(const RGBArgs &a, int st, int part, ui
     }
   }
   if constexpr (KEYS) {
-    const uint32_t *rk = reinterpret_cast<const uint32_t *>(a.rkv);
-    for (int t0 = wave * 64; t0 < a.key_words; t0 += kLFThreads) {
-      const int t = t0 + lane, wd = t % (S / 2), j = (t / (S / 2)) % NBLK;
-      const int r = (t / (S / 2 * NBLK)) % a.n_top, c = t / (S / 2 * NBLK * a.n_top);
-      const int bx = sx * NBLK + j;
-      if (t < a.key_words && bx < a.nbx)
+    // a key view's blocks of the strip, of all channels, lie together
+    constexpr int KW = 3 * NBLK * (S / 2);
+    const uint32_t *rk = reinterpret_cast<const uint32_t *>(a.rkv) + (size_t)(by * a.nbx + sx * NBLK) * (3 * S / 2);
+    const int valid = min(NBLK, a.nbx - sx * NBLK) * (3 * S / 2);
+    for (int f = wave; f < a.n_top * (KW / 64); f += kLFWaves) {
+      const int r = f / (KW / 64), w0 = f % (KW / 64) * 64;
+      if (w0 + lane < valid)
         __builtin_amdgcn_global_load_lds(
-            (const __attribute__((address_space(1))) void *)(rk + ((size_t)(r * a.nb + by * a.nbx + bx) * 3 + c) *
-                                                                  (S / 2) + wd),
-            (__attribute__((address_space(3))) void *)(keys + t0), 4, 0, 0);
+            (const __attribute__((address_space(1))) void *)(rk + (size_t)r * a.nb * (3 * S / 2) + w0 + lane),
+            (__attribute__((address_space(3))) void *)(keys + f * 64), 4, 0, 0);
     }
   }
   __builtin_amdgcn_s_waitcnt(0);
@@ -1341,21 +1401,14 @@ __device__ __forceinline__ void rgb_strip(const RGBArgs &a, int st, int part, ui
   }
   const int px0 = sx * 64 + 4 * jseg;                   // first pixel of the segment
   const bool seg_in = sx * NBLK + jb[0] < a.nbx;        // the segment's first block is inside the image
-  const bool wide = seg_in && (a.wp % 4 == 0);          // all 4 pixels inside, 16-byte aligned
   const uint32_t zslot = (uint32_t)a.tile_cap;
   const uint32_t vplane = (uint32_t)a.hp * (uint32_t)a.wp;
   auto wanted_view = [&](int vi) { return !masked || ((s_need[vi >> 5] >> (vi & 31)) & 1u); };
-  const uint32_t *gs = a.sched + a.strip_off[st];
-  const int nck = __builtin_amdgcn_readfirstlane((int)gs[0]);
   for (int ci = part; ci < nck; ci += a.parts) {
-    const uint32_t *chunk = gs + gs[1 + ci];
-    const uniform_i32 sch = as_uniform(reinterpret_cast<const int32_t *>(chunk));
-    const int q0 = sch[0], nq = sch[1], nn = sch[2];
-    const uint32_t n0 = (uint32_t)sch[3], n01 = (uint32_t)sch[4], n = (uint32_t)sch[5];
-    const int mf_words = 3 * nn + (3 * nn + 1) / 2;
-    const uniform_i32 runs = sch + 6 + mf_words;
-    const uint32_t *ents = chunk + 6 + mf_words + 3 * nq;
-    const uint32_t *items = ents + n;
+    const uint32_t *chunk, *ents, *items;
+    int mf_words;
+    tables(chunk, mf_words, ents, items);
+    const uniform_i32 runs = as_uniform(reinterpret_cast<const int32_t *>(chunk)) + mf_words;
     // with a view mask, the chunk's (run, sibling) pairs of wanted views are
     // listed in LDS and the nodes they read are marked (a chunk with none is
     // skipped whole); without one, pair e is sibling e % 4 of run e / 4
@@ -1388,23 +1441,29 @@ __device__ __forceinline__ void rgb_strip(const RGBArgs &a, int st, int part, ui
       n_list = __builtin_amdgcn_readfirstlane((int)*s_nlist);
       if (n_list == 0) {
         lds_barrier();   // every wave has read the count before the next chunk clears it
+        if (ci + a.parts < nck) {
+          header(ci + a.parts);
+          request_first();
+        }
         continue;
       }
     }
-    // the chunk's node masks, first slots and run records into LDS, in
-    // flight during the decode (the gather then reads no global memory but
-    // the run's view list)
+    // the chunk's node masks, first slots, run positions, views and roots into
+    // LDS, in flight during the decode (the gather then reads no global memory)
     const int tab_words = mf_words + 3 * nq;
     for (int w0 = wave * 64; w0 < tab_words; w0 += kLFThreads)
       if (w0 + lane < tab_words)
-        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(chunk + 6 + w0 + lane),
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(chunk + w0 + lane),
                                          (__attribute__((address_space(3))) void *)(s_mf + w0), 4, 0, 0);
-    // (3) decode every stored block of the chunk (that a wanted view reads) into its tile slot
-    uint32_t e_nx = 0, t_nx = 0;   // the lane's next entry, requested ahead (as in the one-channel kernel)
-    if ((uint32_t)tid < n) {
-      e_nx = ents[tid];
-      t_nx = items[tid];
+    for (int w0 = wave * 64; w0 < kRGBRecWords * nq; w0 += kLFThreads) {
+      const int t = w0 + lane;
+      if (t < kRGBRecWords * nq)
+        __builtin_amdgcn_global_load_lds(
+            (const __attribute__((address_space(1))) void *)(a.batch + (size_t)(q0 + t / kRGBRecWords) * lfc::kBatchWords +
+                                                             1 + t % kRGBRecWords),
+            (__attribute__((address_space(3))) void *)(s_rec + w0), 4, 0, 0);
     }
+    // (3) decode every stored block of the chunk (that a wanted view reads) into its tile slot
     for (uint32_t it = tid; it < n; it += kLFThreads) {
       const uint32_t e = e_nx, t = t_nx;
       if (it + kLFThreads < n) {
@@ -1429,177 +1488,166 @@ __device__ __forceinline__ void rgb_strip(const RGBArgs &a, int st, int part, ui
         *reinterpret_cast<uint2 *>(dst) = make_uint2(d[0], d[1]);
       }
     }
+    // the next chunk's header and first entries, taken before this chunk's stores
+    const int nn_c = nn, nn3 = 3 * nn;
+    if (ci + a.parts < nck) {
+      header(ci + a.parts);
+      request_first();
+    }
     __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0): this wave's copies of the node table have landed
     lds_barrier();
-    const uint16_t *firsts = reinterpret_cast<const uint16_t *>(s_mf + 3 * nn);
+    const uint16_t *firsts = reinterpret_cast<const uint16_t *>(s_mf + nn3);   // (B = 2)
     const uint32_t *s_runs = s_mf + mf_words;
-    // (4) four listed (run, sibling) pairs per wave at a time, one per
-    // 16-lane group; each pair's view and key view come through the scalar
-    // unit (no vector load, which would wait for the wave's stores)
-    for (int e0 = wave * 4; e0 < n_list; e0 += 4 * kLFWaves) {
-      constexpr int y0 = 0;
-      uint32_t ens[4];
-      if (masked) {
-        const uint2 pr = *reinterpret_cast<const uint2 *>(s_list + e0);
-        ens[0] = pr.x & 0xFFFFu;
-        ens[1] = pr.x >> 16;
-        ens[2] = pr.y & 0xFFFFu;
-        ens[3] = pr.y >> 16;
-      } else {
-#pragma unroll
-        for (int g = 0; g < 4; g++) ens[g] = (uint32_t)(e0 + g);
-      }
-      int f_vi[4], f_root[4], f_q[4], f_so[4], f_ok[4];
-#pragma unroll
-      for (int g = 0; g < 4; g++) {
-        const int en = e0 + g < n_list ? __builtin_amdgcn_readfirstlane((int)ens[g]) : 0;
-        f_q[g] = en >> 2;
-        f_so[g] = en & 3;
-        const uniform_i32 rec = as_uniform(a.batch + (size_t)(q0 + f_q[g]) * lfc::kBatchWords);
-        f_vi[g] = rec[1 + f_so[g]];
-        f_root[g] = rec[5];
-        f_ok[g] = e0 + g < n_list && f_so[g] < rec[0];   // (listed pairs are always present siblings)
-      }
-      const int grp = lane >> 4;
-      auto pick = [&](const int (&f)[4]) { return grp == 0 ? f[0] : (grp == 1 ? f[1] : (grp == 2 ? f[2] : f[3])); };
-      const int vi = pick(f_vi), root = pick(f_root), qi = pick(f_q), so = pick(f_so);
-      const bool live = seg_in && pick(f_ok);
-      const uint32_t w0 = s_runs[3 * qi], w1 = s_runs[3 * qi + 1], w2 = s_runs[3 * qi + 2];
-      const int anc_ln[4] = {(int)(w0 >> 16), (int)(w1 & 0xFFFFu), (int)(w1 >> 16), (int)(w2 & 0xFFFFu)};
-      const int leaf = min((int)(w0 & 0xFFFFu) + so, max(nn - 1, 0));   // the lane's own leaf
-      uint32_t x[3][HR][2];
-      // the lane's words of a block slot (tile or key rows, same layout):
-      // B = 4, the whole 4 x 4 block in two 16-byte reads; B = 2, both rows
-      // of each of its two blocks in one 8-byte read; B = 8, half of each row
-      auto read_slot = [&](const uint32_t *slot0, const uint32_t *slot1, bool add, uint32_t (&xc)[HR][2]) {
-        if constexpr (B == 4) {
-          const uint4 v0 = *reinterpret_cast<const uint4 *>(slot0), v1 = *reinterpret_cast<const uint4 *>(slot0 + 4);
-          const uint32_t w[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
-#pragma unroll
-          for (int y = 0; y < 4; y++)
-#pragma unroll
-            for (int k = 0; k < 2; k++) xc[y][k] = add ? add_pk(xc[y][k], w[2 * y + k]) : w[2 * y + k];
-        } else if constexpr (B == 2) {
-          const uint2 v0 = *reinterpret_cast<const uint2 *>(slot0), v1 = *reinterpret_cast<const uint2 *>(slot1);
-          const uint32_t w[2][2] = {{v0.x, v1.x}, {v0.y, v1.y}};
-#pragma unroll
-          for (int y = 0; y < 2; y++)
-#pragma unroll
-            for (int k = 0; k < 2; k++) xc[y][k] = add ? add_pk(xc[y][k], w[y][k]) : w[y][k];
-        } else {
-#pragma unroll
-          for (int y = 0; y < HR; y++) {
-            const uint2 v = *reinterpret_cast<const uint2 *>(slot0 + y * H + wib[0]);
-            xc[y][0] = add ? add_pk(xc[y][0], v.x) : v.x;
-            xc[y][1] = add ? add_pk(xc[y][1], v.y) : v.y;
+    // (4) four listed (run, sibling) pairs per wave at a time, one per 16-lane
+    // group.  Everything comes from LDS and without branches, in three steps
+    // whose reads are in flight together: the pair's run; the masks and first
+    // slots of its path's nodes (nodes_c of them; -1: found at run time) for
+    // all channels; per channel the key row and the nodes' rows.
+    auto gather = [&](auto nodes_c) {
+      constexpr int NC = decltype(nodes_c)::value, NM = NC < 0 ? lfc::kMaxLevels - 1 : NC;
+      const int nodes = NC < 0 ? a.L - 1 : NC;
+      constexpr int NS = B == 2 ? 2 : 1;   // blocks of a lane's four pixels of a row
+      for (int e0 = wave * 4; e0 < n_list; e0 += 4 * kLFWaves) {
+        const int e = min(e0 + (lane >> 4), n_list - 1);
+        const uint32_t en = masked ? s_list[e] : (uint32_t)e;
+        const int qi = (int)(en >> 2), so = (int)(en & 3u);
+        const int vi = s_rec[kRGBRecWords * qi + so], root = s_rec[kRGBRecWords * qi + 4];
+        const bool live = seg_in && e0 + (lane >> 4) < n_list && vi >= 0;
+        // the path's nodes: the lane's own leaf, then its ancestors
+        int node[NM > 0 ? NM : 1] = {};
+        if constexpr (NM > 0) {
+          const uint32_t w0 = s_runs[3 * qi];
+          node[0] = min((int)(w0 & 0xFFFFu) + so, max(nn_c - 1, 0));
+          if constexpr (NM > 1) node[1] = (int)(w0 >> 16);
+          if constexpr (NM > 2) {
+            const uint32_t w1 = s_runs[3 * qi + 1], w2 = s_runs[3 * qi + 2];
+            node[2] = (int)(w1 & 0xFFFFu);
+            node[3] = (int)(w1 >> 16);
+            node[4] = (int)(w2 & 0xFFFFu);
           }
         }
-      };
+        // tile slots of the lane's blocks; an absent block's is the zeroed one
+        uint32_t slot[3][NM > 0 ? NM : 1][NS];
 #pragma unroll
-      for (int c = 0; c < 3; c++) {
-        // key-view rows
-        if constexpr (KEYS) {
-          const uint32_t *kb = keys + (c * a.n_top + root) * (NBLK * (S / 2));
-          read_slot(kb + jb[0] * (S / 2), kb + jb[1] * (S / 2), false, x[c]);
-        } else {
+        for (int c = 0; c < 3; c++)
 #pragma unroll
-          for (int y = 0; y < HR; y++) {
+          for (int k = 0; k < NM; k++) {
+            if (NC < 0 && k >= nodes) continue;
+            const uint32_t w = s_mf[c * nn_c + node[k]];
+            const uint32_t first = B == 2 ? firsts[c * nn_c + node[k]] : w >> 16;
 #pragma unroll
-            for (int w = 0; w < 2; w++) {
-              const int bx = sx * NBLK + jb[w];
-              x[c][y][w] = bx < a.nbx ? reinterpret_cast<const uint32_t *>(
-                                            a.rkv)[((size_t)(root * a.nb + by * a.nbx + bx) * 3 + c) * (S / 2) +
-                                                   (y0 + y) * H + wib[w]]
-                                      : 0u;
+            for (int b = 0; b < NS; b++) {
+              const uint32_t sl = first + (uint32_t)__popc(w & ((1u << jb[b]) - 1u));
+              slot[c][k][b] = ((w >> jb[b]) & 1u ? sl : zslot) * (S / 2);
             }
           }
-        }
-        // rows of node ln added
-        auto add_node = [&](int ln) {
-          const uint32_t mk = s_mf[c * nn + ln], f = firsts[c * nn + ln];
-          auto slot = [&](int w) {
-            const uint32_t j = (uint32_t)jb[w];
-            const uint32_t sl = ((mk >> j) & 1u) ? f + (uint32_t)__popc(mk & ((1u << j) - 1u)) : zslot;
-            return tile + sl * (S / 2);
-          };
-          read_slot(slot(0), B == 2 ? slot(1) : nullptr, true, x[c]);
+        uint32_t x[3][HR][2];
+        // the lane's words of a block slot (tile or key rows, same layout):
+        // B = 4, the whole 4 x 4 block in two 16-byte reads; B = 2, both rows
+        // of each of its two blocks in one 8-byte read; B = 8, half of each row
+        auto read_slot = [&](const uint32_t *slot0, const uint32_t *slot1, bool add, uint32_t (&xc)[HR][2]) {
+          if constexpr (B == 4) {
+            const uint4 v0 = *reinterpret_cast<const uint4 *>(slot0), v1 = *reinterpret_cast<const uint4 *>(slot0 + 4);
+            const uint32_t w[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
+#pragma unroll
+            for (int y = 0; y < 4; y++)
+#pragma unroll
+              for (int k = 0; k < 2; k++) xc[y][k] = add ? add_pk(xc[y][k], w[2 * y + k]) : w[2 * y + k];
+          } else if constexpr (B == 2) {
+            const uint2 v0 = *reinterpret_cast<const uint2 *>(slot0), v1 = *reinterpret_cast<const uint2 *>(slot1);
+            const uint32_t w[2][2] = {{v0.x, v1.x}, {v0.y, v1.y}};
+#pragma unroll
+            for (int y = 0; y < 2; y++)
+#pragma unroll
+              for (int k = 0; k < 2; k++) xc[y][k] = add ? add_pk(xc[y][k], w[y][k]) : w[y][k];
+          } else {
+#pragma unroll
+            for (int y = 0; y < HR; y++) {
+              const uint2 v = *reinterpret_cast<const uint2 *>(slot0 + y * H + wib[0]);
+              xc[y][0] = add ? add_pk(xc[y][0], v.x) : v.x;
+              xc[y][1] = add ? add_pk(xc[y][1], v.y) : v.y;
+            }
+          }
         };
 #pragma unroll
-        for (int k = 0; k < 4; k++)
-          if (k < a.L - 2) add_node(anc_ln[k]);
-        if (a.L > 1) add_node(leaf);
-      }
-      if (!live) continue;
-      uint32_t *dst = a.out + (uint32_t)vi * vplane + (uint32_t)(by * B + y0) * (uint32_t)a.wp + (uint32_t)px0;
+        for (int c = 0; c < 3; c++) {
+          if constexpr (KEYS) {
+            const uint32_t *kb = keys + root * (3 * NBLK * (S / 2)) + c * (S / 2);
+            read_slot(kb + jb[0] * (3 * S / 2), kb + jb[1] * (3 * S / 2), false, x[c]);
+          } else {
 #pragma unroll
-      for (int y = 0; y < HR; y++) {
-        uint32_t p[4];
+            for (int y = 0; y < HR; y++) {
 #pragma unroll
-        for (int w = 0; w < 2; w++) {
-          p[2 * w] = rgb_pack(lo16(x[0][y][w]), lo16(x[1][y][w]), lo16(x[2][y][w]));
-          p[2 * w + 1] = rgb_pack(hi16(x[0][y][w]), hi16(x[1][y][w]), hi16(x[2][y][w]));
+              for (int w = 0; w < 2; w++) {
+                const int bx = sx * NBLK + jb[w];
+                x[c][y][w] = bx < a.nbx ? reinterpret_cast<const uint32_t *>(
+                                              a.rkv)[((size_t)(root * a.nb + by * a.nbx + bx) * 3 + c) * (S / 2) + y * H +
+                                                     wib[w]]
+                                        : 0u;
+              }
+            }
+          }
+#pragma unroll
+          for (int k = 0; k < NM; k++) {
+            if (NC < 0 && k >= nodes) continue;
+            read_slot(tile + slot[c][k][0], tile + slot[c][k][NS - 1], true, x[c]);
+          }
         }
-        uint32_t *row = dst + (uint32_t)y * (uint32_t)a.wp;
-        if (wide) {
-          *reinterpret_cast<uint4 *>(row) = make_uint4(p[0], p[1], p[2], p[3]);
-        } else {
+        if (!live) continue;
+        uint32_t *dst = a.out + (uint32_t)vi * vplane + (uint32_t)(by * B) * (uint32_t)a.wp + (uint32_t)px0;
 #pragma unroll
-          for (int k = 0; k < 4; k++)
-            if (px0 + k < a.wp) row[k] = p[k];
+        for (int y = 0; y < HR; y++) {
+          uint32_t p[4];
+#pragma unroll
+          for (int w = 0; w < 2; w++) rgb_pack2(x[0][y][w], x[1][y][w], x[2][y][w], p[2 * w], p[2 * w + 1]);
+          uint32_t *row = dst + (uint32_t)y * (uint32_t)a.wp;
+          if constexpr (B >= 4) {   // (the padded width is a multiple of four)
+            *reinterpret_cast<uint4 *>(row) = make_uint4(p[0], p[1], p[2], p[3]);
+          } else {
+            *reinterpret_cast<uint2 *>(row) = make_uint2(p[0], p[1]);
+            if (px0 + 2 < a.wp) *reinterpret_cast<uint2 *>(row + 2) = make_uint2(p[2], p[3]);
+          }
         }
       }
+    };
+    switch (a.L) {
+      case 1: gather(std::integral_constant<int, 0>{}); break;
+      case 2: gather(std::integral_constant<int, 1>{}); break;
+      case 3: gather(std::integral_constant<int, 2>{}); break;
+      default: gather(std::integral_constant<int, -1>{});
     }
     lds_barrier();
   }
 }
 
+// (B <= 4: at most 80 VGPRs, so that three workgroups share a compute unit)
 template <int B, bool KEYS>
-__global__ __launch_bounds__(kLFThreads) void k_decode_rgb(RGBArgs a) {
+__global__ __launch_bounds__(kLFThreads, B <= 4 ? 6 : 1) void k_decode_rgb(RGBArgs a) {
   extern __shared__ uint32_t smem[];
-  uint16_t *lut = reinterpret_cast<uint16_t *>(smem);
-  for (int t = threadIdx.x; t < kLutEntries; t += kLFThreads) lut[t] = lut_entry(t);
-  rgb_strip<B, KEYS>(a, (int)a.order[blockIdx.x / a.parts], blockIdx.x % a.parts, smem);
+  rgb_strip<B, KEYS>(a, (int)blockIdx.x, smem);
 }
 
-// The colour decode of several light fields in one persistent launch: the
-// work items are every light field's (strip, part) pairs, each light field's
-// strips costliest first; workgroups stay resident and take the next item
-// from a device counter until none is left.  The last workgroup to finish
-// puts the counters back to zero, so the next launch (or graph replay) needs
-// no clearing; launches that share counters must not overlap.
+// The colour decode of several light fields in one launch: the workgroups are
+// every light field's (strip, part) pairs, each light field's strips costliest
+// first.  (Workgroups that stayed resident and took items from a device counter
+// needed 20 registers more, which kept a third of them off the chip: 99 us
+// against 57 for the 4 x 4 fields of a mixed batch, 23 against 18 for its 8 x 8.)
 struct RGBMultiArgs {
   const RGBArgs *lfs;      // [n_lf], every one of block size B
   const int32_t *first;    // [n_lf + 1] first work item of each light field (items = strips x parts)
-  int n_lf, n_items;
-  uint32_t *ctr;           // [2]: next work item, finished workgroups
+  int n_lf;
 };
 
 template <int B, bool KEYS>
-__global__ __launch_bounds__(kLFThreads) void k_decode_rgb_multi(RGBMultiArgs m) {
+__global__ __launch_bounds__(kLFThreads, B <= 4 ? 6 : 1) void k_decode_rgb_multi(RGBMultiArgs m) {
   extern __shared__ uint32_t smem[];
-  uint16_t *lut = reinterpret_cast<uint16_t *>(smem);
-  uint32_t *s_item = smem + 288 + 2;   // a free word of the chunk flags
-  for (int t = threadIdx.x; t < kLutEntries; t += kLFThreads) lut[t] = lut_entry(t);
   const uniform_i32 first = as_uniform(m.first);
-  for (;;) {
-    lds_barrier();   // every wave is done with the previous item's LDS (its stores may still be in flight)
-    if (threadIdx.x == 0) *s_item = atomicAdd(&m.ctr[0], 1u);
-    lds_barrier();
-    const int item = __builtin_amdgcn_readfirstlane((int)*s_item);
-    if (item >= m.n_items) break;
-    int lf = 0;
-    while (lf + 1 < m.n_lf && first[lf + 1] <= item) lf++;
-    const RGBArgs a = m.lfs[lf];
-    const int local = item - first[lf];
-    rgb_strip<B, KEYS>(a, (int)a.order[local / a.parts], local % a.parts, smem);
-  }
-  if (threadIdx.x == 0) {
-    __threadfence();
-    if (atomicAdd(&m.ctr[1], 1u) == gridDim.x - 1) {
-      atomicExch(&m.ctr[0], 0u);
-      atomicExch(&m.ctr[1], 0u);
-    }
-  }
+  const int item = blockIdx.x;
+  int lf = 0;
+  while (lf + 1 < m.n_lf && first[lf + 1] <= item) lf++;
+  const RGBArgs a = m.lfs[lf];
+  const int local = item - first[lf];
+  rgb_strip<B, KEYS>(a, local, smem);
 }
 
 // Novel views from fully decoded 8-bit RGB source views ([nv][hp][wp]): one
@@ -1963,18 +2011,20 @@ lfc_status decode_rgb(const lfc_lf *lf, uint32_t *out, const uint32_t *vneed, hi
     return fail(LFC_E_UNSUPPORTED, std::string(who) + ": light field too large for 32-bit pixel indices");
   const int64_t kw = (int64_t)3 * g.n_top * B * 32;
   const int key_words = kw <= kRGBKeyWordsMax ? (int)kw : 0;
-  const size_t lds = 4 * ((size_t)kRGBHeadWords + (size_t)lf_tile_words(lf->tile_cap_rgb, B * B) + (size_t)key_words);
+  // a view mask longer than the kernel's LDS copy of it: every view is decoded
+  if (g.nv() > 32 * kRGBNeedWords) vneed = nullptr, views = nullptr;
+  const int need_words = vneed || (views && nviews > 0) ? (g.nv() + 31) / 32 : 0;
+  const size_t lds = 4 * ((size_t)rgb_head_words(need_words, lf->rgb_tab_cap, lf->rgb_run_cap) +
+                          (size_t)lf_tile_words(lf->tile_cap_rgb, B * B) + (size_t)key_words);
   if (lds > (size_t)max_lds_bytes())
     return fail(LFC_E_UNSUPPORTED, std::string(who) + ": tree too large for the colour whole-field kernel");
   const int nsx = (g.nbx + NBLK - 1) / NBLK, nstrips = g.nby * nsx;
   // workgroups per strip: enough for several rounds of the resident
   // workgroups (about three per compute unit), at most the strips' chunk count
   int parts = std::max(1, std::min(lf->rgb_max_chunks, (3 * 3 * device_cus() + nstrips - 1) / nstrips));
-  // a view mask longer than the kernel's LDS copy of it: every view is decoded
-  if (g.nv() > 32 * kRGBNeedWords) vneed = nullptr, views = nullptr;
-  RGBArgs a{lf->d_rkv, lf->d_off, lf->d_srv, lf->d_sched_rgb, lf->d_strip_off_rgb, lf->d_order_rgb, lf->d_batch,
+  RGBArgs a{lf->d_rkv, lf->d_off, lf->d_srv, lf->d_sched_rgb, lf->d_order_rgb, lf->d_batch,
             vneed, out, g.nbx, nsx, g.L, g.q, g.wp, g.hp, g.nb, lf->n_batch, g.nv(), g.n_top, key_words,
-            lf->tile_cap_rgb, parts};
+            lf->tile_cap_rgb, parts, need_words, lf->rgb_tab_cap, lf->rgb_run_cap};
   if (!vneed && views && nviews > 0) {
     a.views = views;
     a.nviews = nviews;
@@ -2529,8 +2579,8 @@ int rgb_parts(const lfc_lf *lf) {
 
 bool lf_rgb_batchable(const lfc_lf *lf, double out_pixels) {
   const Geometry &g = lf->geo;
-  const size_t lds = 4 * ((size_t)kRGBHeadWords + (size_t)lf_tile_words(lf->tile_cap_rgb, g.B * g.B) +
-                          (size_t)rgb_key_words(g));
+  const size_t lds = 4 * ((size_t)rgb_head_words((g.nv() + 31) / 32, lf->rgb_tab_cap, lf->rgb_run_cap) +
+                          (size_t)lf_tile_words(lf->tile_cap_rgb, g.B * g.B) + (size_t)rgb_key_words(g));
   return (uint64_t)g.nv() * g.hp * g.wp * 4 < ((uint64_t)1 << 32) && g.nv() <= 32 * kRGBNeedWords &&
          lds <= (size_t)max_lds_bytes() && 20.0 * out_pixels >= (double)g.nv() * g.hp * g.wp;
 }
@@ -2550,16 +2600,17 @@ size_t rgb_args_bytes() { return sizeof(RGBArgs); }
 void rgb_args_fill(const lfc_lf *lf, bool keys, uint32_t *d_rgb, const uint32_t *d_mask, void *dst) {
   const Geometry &g = lf->geo;
   const int nblk = 64 / g.B;
-  RGBArgs a{lf->d_rkv, lf->d_off, lf->d_srv, lf->d_sched_rgb, lf->d_strip_off_rgb, lf->d_order_rgb, lf->d_batch,
+  RGBArgs a{lf->d_rkv, lf->d_off, lf->d_srv, lf->d_sched_rgb, lf->d_order_rgb, lf->d_batch,
             d_mask, d_rgb, g.nbx, (g.nbx + nblk - 1) / nblk, g.L, g.q, g.wp, g.hp, g.nb, lf->n_batch, g.nv(),
-            g.n_top, keys ? rgb_key_words(g) : 0, lf->tile_cap_rgb, rgb_parts(lf)};
+            g.n_top, keys ? rgb_key_words(g) : 0, lf->tile_cap_rgb, rgb_parts(lf), (g.nv() + 31) / 32, lf->rgb_tab_cap,
+            lf->rgb_run_cap};
   std::memcpy(dst, &a, sizeof a);
 }
 
 size_t rgb_lds_bytes(const lfc_lf *lf, bool keys) {
   const Geometry &g = lf->geo;
-  return 4 * ((size_t)kRGBHeadWords + (size_t)lf_tile_words(lf->tile_cap_rgb, g.B * g.B) +
-              (size_t)(keys ? rgb_key_words(g) : 0));
+  return 4 * ((size_t)rgb_head_words((g.nv() + 31) / 32, lf->rgb_tab_cap, lf->rgb_run_cap) +
+              (size_t)lf_tile_words(lf->tile_cap_rgb, g.B * g.B) + (size_t)(keys ? rgb_key_words(g) : 0));
 }
 
 bool rgb_keys_fit(const lfc_lf *lf) { return rgb_key_words(lf->geo) > 0; }
@@ -2598,18 +2649,11 @@ void interp_req_fill(const lfc_lf *lf, const uint32_t *d_rgb, const lfc_view &v,
 }
 
 lfc_status rgb_multi_launch(int block, bool keys, const void *d_args, const int32_t *d_first, int n_lf, int n_items,
-                            size_t lds, uint32_t *d_ctr, hipStream_t s) {
+                            size_t lds, hipStream_t s) {
   if (n_items <= 0) return LFC_OK;
-  RGBMultiArgs m{static_cast<const RGBArgs *>(d_args), d_first, n_lf, n_items, d_ctr};
-  // resident workgroups: as many as the compute units hold at this LDS size
+  RGBMultiArgs m{static_cast<const RGBArgs *>(d_args), d_first, n_lf};
   auto launch = [&](auto kern) -> lfc_status {
-    int per_cu = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, kLFThreads, lds) != hipSuccess || per_cu < 1) {
-      (void)hipGetLastError();
-      per_cu = 1;
-    }
-    const int grid = std::max(1, std::min(n_items, per_cu * device_cus()));
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(kLFThreads), lds, s, m);
+    hipLaunchKernelGGL(kern, dim3((unsigned)n_items), dim3(kLFThreads), lds, s, m);
     return launched("lfc_batch_render");
   };
   switch (block * 2 + (keys ? 1 : 0)) {

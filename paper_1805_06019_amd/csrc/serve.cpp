@@ -28,7 +28,6 @@ using lfc::fail;
 namespace {
 
 constexpr int kSlots = 4;       // request tables in flight per batch context
-constexpr int kCtrStride = 16;  // words between two slots' counters (one cache line each)
 
 // A request table: pinned host staging and its device copy.  `done` is
 // recorded after the launches that read the table; the slot is rewritten
@@ -60,7 +59,6 @@ struct lfc_batch {
   Slot slot[kSlots];
   int next = 0;
   int32_t *d_err = nullptr;   // set by a batched decode that saw an out-of-range request
-  uint32_t *d_ctr = nullptr;  // per slot, the persistent colour decode's two counters (zero between launches)
   std::deque<Scratch> scratch;   // (a deque: adding one keeps the others' addresses)
 };
 
@@ -123,9 +121,7 @@ extern "C" lfc_status lfc_batch_create(lfc_batch **out) {
     }
   }
   if (hipMalloc(reinterpret_cast<void **>(&b->d_err), sizeof(int32_t)) != hipSuccess ||
-      hipMemset(b->d_err, 0, sizeof(int32_t)) != hipSuccess ||
-      hipMalloc(reinterpret_cast<void **>(&b->d_ctr), kSlots * kCtrStride * sizeof(uint32_t)) != hipSuccess ||
-      hipMemset(b->d_ctr, 0, kSlots * kCtrStride * sizeof(uint32_t)) != hipSuccess) {
+      hipMemset(b->d_err, 0, sizeof(int32_t)) != hipSuccess) {
     (void)lfc_batch_destroy(b);
     return fail(LFC_E_NOMEM, "lfc_batch_create: error flag");
   }
@@ -148,7 +144,6 @@ extern "C" lfc_status lfc_batch_destroy(lfc_batch *b) {
     if (sc.buf) (void)hipFree(sc.buf);
   }
   if (b->d_err) (void)hipFree(b->d_err);
-  if (b->d_ctr) (void)hipFree(b->d_ctr);
   delete b;
   return LFC_OK;
 }
@@ -333,10 +328,10 @@ void fill_batch(const BatchLayout &L, const lfc_lf *const *lfs, int32_t n_lf, co
 }
 
 // The launches of a batch whose table is at dev: tile groups, then the
-// colour decode of each block size (persistent, counters ctr[2]), then the
+// colour decode of each block size, then the
 // interpolation.  No copies, memsets or event operations: a stream capture
 // of it is a graph of kernels only.
-lfc_status launch_batch(const BatchLayout &L, const char *dev, uint32_t *ctr, hipStream_t s) {
+lfc_status launch_batch(const BatchLayout &L, const char *dev, hipStream_t s) {
   lfc_status st = LFC_OK;
   for (int block : {2, 4, 8}) {
     const BatchLayout::Group &gp = L.grp[block];
@@ -347,7 +342,7 @@ lfc_status launch_batch(const BatchLayout &L, const char *dev, uint32_t *ctr, hi
     const BatchLayout::Group &gp = L.grp[block];
     if (gp.lf.empty() || st != LFC_OK) continue;
     st = lfc::rgb_multi_launch(block, gp.keys, dev + gp.at_args, reinterpret_cast<const int32_t *>(dev + gp.at_first),
-                               (int)gp.lf.size(), gp.items, gp.rgb_lds, ctr, s);
+                               (int)gp.lf.size(), gp.items, gp.rgb_lds, s);
   }
   if (st == LFC_OK && L.n_interp) st = lfc::interp_multi_launch(dev + L.at_interp, L.n_interp, L.max_wo, L.max_ho, s);
   return st;
@@ -371,7 +366,6 @@ lfc_status batch_render(lfc_batch *b, const lfc_lf *const *lfs, int32_t n_lf, co
   fill_batch(L, lfs, n_lf, reqs, n, d_outs, sl.host, sl.dev);
   if (hipMemcpyAsync(sl.dev, sl.host, L.bytes, hipMemcpyHostToDevice, s) != hipSuccess)
     return fail(LFC_E_HIP, std::string(who) + ": copy of the request table");
-  uint32_t *ctr = b->d_ctr + (size_t)b->next * kCtrStride;
   b->next = (b->next + 1) % kSlots;
   // a decoded-views buffer is rewritten only after the launches of an
   // earlier batch that read it (on any stream) have finished
@@ -379,7 +373,7 @@ lfc_status batch_render(lfc_batch *b, const lfc_lf *const *lfs, int32_t n_lf, co
   for (int l = 0; l < n_lf && st == LFC_OK; l++)
     if (L.scr[(size_t)l] && L.scr[(size_t)l]->used && hipStreamWaitEvent(s, L.scr[(size_t)l]->done, 0) != hipSuccess)
       st = fail(LFC_E_HIP, std::string(who) + ": wait for an earlier use of the decoded views");
-  if (st == LFC_OK) st = launch_batch(L, sl.dev, ctr, s);
+  if (st == LFC_OK) st = launch_batch(L, sl.dev, s);
   for (int l = 0; l < n_lf; l++)
     if (L.scr[(size_t)l]) {
       if (hipEventRecord(L.scr[(size_t)l]->done, s) == hipSuccess) {
@@ -402,13 +396,11 @@ extern "C" lfc_status lfc_batch_render(lfc_batch *b, const lfc_lf *const *lfs, i
 }
 
 // A batch fixed once: its table on the device, its decoded-view buffers
-// (in a context of its own) and the colour decode's counters, and with a
-// graph its launches captured once.
+// (in a context of its own), and with a graph its launches captured once.
 struct lfc_batch_plan {
   lfc_batch *b = nullptr;
   BatchLayout L;
   char *dev = nullptr;
-  uint32_t *ctr = nullptr;
   hipStream_t cap = nullptr;
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
@@ -419,9 +411,8 @@ extern "C" void lfc_batch_plan_destroy(lfc_batch_plan *p) {
   if (p->exec) (void)hipGraphExecDestroy(p->exec);
   if (p->graph) (void)hipGraphDestroy(p->graph);
   if (p->cap) (void)hipStreamDestroy(p->cap);
-  if (p->dev || p->ctr) (void)hipDeviceSynchronize();
+  if (p->dev) (void)hipDeviceSynchronize();
   if (p->dev) (void)hipFree(p->dev);
-  if (p->ctr) (void)hipFree(p->ctr);
   (void)lfc_batch_destroy(p->b);
   delete p;
 }
@@ -442,15 +433,11 @@ extern "C" lfc_status lfc_batch_plan_create(const lfc_lf *const *lfs, int32_t n_
     if (hipMalloc(reinterpret_cast<void **>(&p->dev), p->L.bytes) != hipSuccess) {
       p->dev = nullptr;
       st = fail(LFC_E_NOMEM, "lfc_batch_plan_create: request table");
-    } else if (hipMalloc(reinterpret_cast<void **>(&p->ctr), 2 * sizeof(uint32_t)) != hipSuccess) {
-      p->ctr = nullptr;
-      st = fail(LFC_E_NOMEM, "lfc_batch_plan_create: counters");
     }
   }
   if (st == LFC_OK) {
     fill_batch(p->L, lfs, n_lf, reqs, n, d_outs, host.data(), p->dev);
-    if (hipMemcpy(p->dev, host.data(), p->L.bytes, hipMemcpyHostToDevice) != hipSuccess ||
-        hipMemset(p->ctr, 0, 2 * sizeof(uint32_t)) != hipSuccess)
+    if (hipMemcpy(p->dev, host.data(), p->L.bytes, hipMemcpyHostToDevice) != hipSuccess)
       st = fail(LFC_E_HIP, "lfc_batch_plan_create: copy of the request table");
   }
   if (st == LFC_OK && graph) {
@@ -460,7 +447,7 @@ extern "C" lfc_status lfc_batch_plan_create(const lfc_lf *const *lfs, int32_t n_
     } else if (hipStreamBeginCapture(p->cap, hipStreamCaptureModeRelaxed) != hipSuccess) {
       st = fail(LFC_E_HIP, "lfc_batch_plan_create: begin capture");
     } else {
-      st = launch_batch(p->L, p->dev, p->ctr, p->cap);
+      st = launch_batch(p->L, p->dev, p->cap);
       hipGraph_t g = nullptr;
       const hipError_t he = hipStreamEndCapture(p->cap, &g);
       p->graph = g;
@@ -488,7 +475,7 @@ extern "C" lfc_status lfc_batch_plan_launch(lfc_batch_plan *p, hipStream_t s) {
     if (hipGraphLaunch(p->exec, s) != hipSuccess) return fail(LFC_E_HIP, "lfc_batch_plan_launch: graph launch");
     return LFC_OK;
   }
-  return launch_batch(p->L, p->dev, p->ctr, s);
+  return launch_batch(p->L, p->dev, s);
 }
 
 extern "C" lfc_status lfc_batch_plan_info(const lfc_batch_plan *p, int32_t *n_decoded_lf, int32_t *graph) {

@@ -48,10 +48,9 @@ lfc_status decode_multi_launch(int block, const void *d_lfs, int n_lf, const int
 // The colour decode-then-interpolate path of a batch.  A light field whose
 // requests in the batch cover about as many pixels as it holds (and whose
 // decoded views take less than 4 GiB) is decoded once, only the views the
-// batch reads, by one persistent launch over every such light field of a
-// block size (rgb_multi_launch, work items of lf_rgb_items() each, args
-// packed by rgb_args_fill, counters d_ctr[2] zero before and after), into
-// a scratch of lf_rgb_bytes(); then one launch interpolates every such
+// batch reads, by one launch over every such light field of a block size
+// (rgb_multi_launch, work items of lf_rgb_items() each, args packed by
+// rgb_args_fill), into a scratch of lf_rgb_bytes(); then one launch interpolates every such
 // request (interp_multi_launch over records packed by interp_req_fill).
 bool lf_rgb_batchable(const lfc_lf *lf, double out_pixels);
 size_t lf_rgb_bytes(const lfc_lf *lf);
@@ -66,7 +65,7 @@ size_t interp_req_bytes();
 void interp_req_fill(const lfc_lf *lf, const uint32_t *d_rgb, const lfc_view &v, int wo, int ho, float *out,
                      uint64_t call_bytes, void *dst);   // call_bytes: decoded views and outputs of the whole call
 lfc_status rgb_multi_launch(int block, bool keys, const void *d_args, const int32_t *d_first, int n_lf, int n_items,
-                            size_t lds, uint32_t *d_ctr, hipStream_t s);
+                            size_t lds, hipStream_t s);
 lfc_status interp_multi_launch(const void *d_reqs, int n, int max_wo, int max_ho, hipStream_t s);
 
 }  // namespace lfc
