@@ -304,21 +304,26 @@ void build_tree_tables(const Geometry &g, TreeTables &t) {
 // table (masks, first slots, run records) fits kLFTabWords words; per
 // chunk: its runs, its nodes (leaves first, then ancestors), per node a mask
 // of the stored blocks and the tile slot of the first one (slots follow node
-// order, then block order), per run the positions of its first leaf and of
+// order, then mask order), per run the positions of its first leaf and of
 // its ancestors in the node list, and the stored blocks sorted by range kind
 // with their directory entries and (slot << 5 | block).
-//   strip record: [0] chunks, [1..chunks] chunk record offsets from the
-//   strip's start, [chunks+1] the strip's length;
-//   chunk record: q0, nq, nn, n0, n01, n (first run, runs, nodes, ends of the
-//   plain-bit, trit and quint blocks), masks[nn], first slots[nn] (16-bit, two
-//   per word), runs[nq][3 words] (16-bit: first leaf, ancestors on levels
+//   strip record: [0] chunks, then from word 8 eight words per chunk (the
+//   offset of its tables from the strip's start, q0, nq, nn, n0, n01, n, 0:
+//   first run, runs, nodes, ends of the plain-bit, trit and quint blocks);
+//   chunk tables: masks[nn] and first slots[nn] (B = 2: 16-bit, two per word,
+//   after the masks; else, a strip having at most 16 blocks, in the masks'
+//   upper halves), runs[nq][3 words] (16-bit: first leaf, ancestors on levels
 //   L-2 .. 1; 0xFFFF unused), entries[n], items[n] (16-bit, two per word).
+// Bit strip_bit(j) of a mask is block j.  A kind's entries follow the strip's
+// blocks, then the nodes: neighbouring lanes read neighbouring bits of a group.
 static void build_schedule(const Geometry &g, const std::vector<uint32_t> &off, const std::vector<uint32_t> &srv,
                            const std::vector<uint32_t> &dbase, const std::vector<uint32_t> &poff,
                            const std::vector<int32_t> &batch, std::vector<uint32_t> &sched,
                            std::vector<uint32_t> &strip_off, int cap) {
   const int nblk = 64 / g.B, nsx = (g.nbx + nblk - 1) / nblk, nstrip = 3 * g.nby * nsx;
   const int nruns = (int)(batch.size() / kBatchWords), L = g.L;
+  const int mask_halves = g.B == 2 ? 3 : 2;   // half words per node of masks and first slots
+  const size_t tab_limit = lf_tab_limit(g.B, cap);
   std::vector<std::vector<uint32_t>> per((size_t)nstrip);
   parallel_for(nstrip, 8, [&](int64_t a, int64_t e) {
     std::vector<uint32_t> m((size_t)std::max(g.n_srv, 1));
@@ -333,9 +338,9 @@ static void build_schedule(const Geometry &g, const std::vector<uint32_t> &off, 
         const size_t gi = 3 * ((size_t)by * g.nbx + bx) + c;
         if (off[gi] == off[gi + 1]) continue;
         for (int w = 0; w < g.nbw; w++)
-          for (uint32_t bm = srv[off[gi] + w]; bm; bm &= bm - 1) m[(size_t)w * 32 + __builtin_ctz(bm)] |= 1u << jj;
+          for (uint32_t bm = srv[off[gi] + w]; bm; bm &= bm - 1) m[(size_t)w * 32 + __builtin_ctz(bm)] |= 1u << strip_bit(g.B, jj);
       }
-      std::vector<uint32_t> head(1, 0), body;
+      std::vector<uint32_t> head(8, 0), body;
       for (int q = 0; q < nruns;) {
         // greedy: consecutive runs while their nodes' stored blocks fit the tile
         std::vector<int> leaves, ancs;
@@ -359,7 +364,7 @@ static void build_schedule(const Geometry &g, const std::vector<uint32_t> &off, 
             }
           }
           const size_t nn_new = leaves.size() + ancs.size() + nl.size() + na.size();
-          if (k > 0 && (count + add > cap || nn_new + (nn_new + 1) / 2 + 3 * (size_t)(k + 1) > (size_t)kLFTabWords))
+          if (k > 0 && (count + add > cap || (mask_halves * nn_new + 1) / 2 + 8 * (size_t)(k + 1) > tab_limit))
             break;
           for (int s : nl) {
             loc[(size_t)s] = 0;
@@ -385,32 +390,33 @@ static void build_schedule(const Geometry &g, const std::vector<uint32_t> &off, 
           slot += (uint32_t)__builtin_popcount(masks[(size_t)i]);
         }
         std::vector<uint32_t> ent[3], item[3];
-        for (int i = 0; i < nn; i++) {
-          const int s = nodes[(size_t)i];
-          for (uint32_t bits = masks[(size_t)i]; bits; bits &= bits - 1) {
-            const int jj = __builtin_ctz(bits);
-            const size_t gi = 3 * ((size_t)by * g.nbx + sx * nblk + jj) + c;
+        for (int jj = 0; jj < nblk; jj++) {
+          const int bit_j = strip_bit(g.B, jj);
+          const size_t gi = 3 * ((size_t)by * g.nbx + sx * nblk + jj) + c;
+          for (int i = 0; i < nn; i++) {
+            const uint32_t mk = masks[(size_t)i];
+            if (!((mk >> bit_j) & 1u)) continue;
+            const int s = nodes[(size_t)i];
             const uint32_t bm = srv[off[gi] + (s >> 5)], bit = (uint32_t)s & 31u;
             const uint32_t en = poff[dbase[gi * g.nbw + (s >> 5)] + (uint32_t)__builtin_popcount(bm & ((1u << bit) - 1u))];
             const uint32_t code = en & 31u;
             const int kind = code < 12 ? 0 : (code < 19 ? 1 : 2);
-            const uint32_t sl = bases[(size_t)i] + (uint32_t)__builtin_popcount(masks[(size_t)i] & ((1u << jj) - 1u));
+            const uint32_t sl = bases[(size_t)i] + (uint32_t)__builtin_popcount(mk & ((1u << bit_j) - 1u));
             ent[kind].push_back(en);
             item[kind].push_back((sl << 5) | (uint32_t)jj);
           }
         }
         const uint32_t n0 = (uint32_t)ent[0].size(), n01 = n0 + (uint32_t)ent[1].size();
         const uint32_t n = n01 + (uint32_t)ent[2].size();
-        head.push_back((uint32_t)body.size());   // made absolute below
-        body.push_back((uint32_t)q);
-        body.push_back((uint32_t)k);
-        body.push_back((uint32_t)nn);
-        body.push_back(n0);
-        body.push_back(n01);
-        body.push_back(n);
-        body.insert(body.end(), masks.begin(), masks.end());
-        for (int i = 0; i < nn; i += 2)
-          body.push_back(bases[(size_t)i] | (i + 1 < nn ? bases[(size_t)i + 1] << 16 : 0u));
+        // (the offset of the chunk's tables is made absolute below)
+        for (uint32_t w : {(uint32_t)body.size(), (uint32_t)q, (uint32_t)k, (uint32_t)nn, n0, n01, n, 0u}) head.push_back(w);
+        if (g.B == 2) {
+          body.insert(body.end(), masks.begin(), masks.end());
+          for (int i = 0; i < nn; i += 2)
+            body.push_back(bases[(size_t)i] | (i + 1 < nn ? bases[(size_t)i + 1] << 16 : 0u));
+        } else {
+          for (int i = 0; i < nn; i++) body.push_back(masks[(size_t)i] | bases[(size_t)i] << 16);
+        }
         for (int j = 0; j < k; j++) {
           const int32_t *r = &batch[(size_t)(q + j) * kBatchWords];
           uint32_t h[4] = {L > 1 ? (uint32_t)loc[(size_t)r[10]] : 0xFFFFu, 0xFFFFu, 0xFFFFu, 0xFFFFu};
@@ -426,11 +432,10 @@ static void build_schedule(const Geometry &g, const std::vector<uint32_t> &off, 
         for (int s : nodes) loc[(size_t)s] = -1;
         q += k;
       }
-      const uint32_t nck = (uint32_t)(head.size() - 1);
+      const uint32_t nck = (uint32_t)(head.size() / 8 - 1), hdr = (uint32_t)head.size();
       head[0] = nck;
-      const uint32_t hdr = nck + 2;
-      for (uint32_t i = 1; i <= nck; i++) head[i] += hdr;
-      head.push_back(hdr + (uint32_t)body.size());
+      for (uint32_t i = 1; i <= nck; i++) head[8 * i] += hdr;
+      body.resize((body.size() + 7) & ~(size_t)7, 0u);   // (strips start at a multiple of eight words)
       std::vector<uint32_t> &w = per[(size_t)st];
       w = head;
       w.insert(w.end(), body.begin(), body.end());
@@ -539,12 +544,12 @@ static void build_schedule_rgb(const Geometry &g, const std::vector<uint32_t> &o
           }
         std::vector<uint32_t> ent[3], item[3];
         for (int c = 0; c < 3; c++)
-          for (int i = 0; i < nn; i++) {
-            const int s = nodes[(size_t)i];
-            const uint32_t mk = masks[(size_t)c * nn + i];
-            for (uint32_t bits = mk; bits; bits &= bits - 1) {
-              const int jj = __builtin_ctz(bits);
-              const size_t gi = 3 * ((size_t)by * g.nbx + sx * nblk + jj) + c;
+          for (int jj = 0; jj < nblk; jj++) {
+            const size_t gi = 3 * ((size_t)by * g.nbx + sx * nblk + jj) + c;
+            for (int i = 0; i < nn; i++) {
+              const uint32_t mk = masks[(size_t)c * nn + i];
+              if (!((mk >> jj) & 1u)) continue;
+              const int s = nodes[(size_t)i];
               const uint32_t bm = srv[off[gi] + (s >> 5)], bit = (uint32_t)s & 31u;
               const uint32_t en =
                   poff[dbase[gi * g.nbw + (s >> 5)] + (uint32_t)__builtin_popcount(bm & ((1u << bit) - 1u))];
@@ -607,7 +612,7 @@ static void build_schedule_rgb(const Geometry &g, const std::vector<uint32_t> &o
 struct StripTables {
   std::vector<uint32_t> sched, strip_off, order, need;
   uint32_t max_words = 0;
-  // colour schedule: most chunks of a strip, gather-table words and runs of a chunk
+  // most chunks of a strip (colour schedule), gather-table words and runs of a chunk
   int max_chunks = 1, tab_cap = 0, run_cap = 0;
 };
 
@@ -629,6 +634,11 @@ static void make_strip_tables(const Geometry &g, const std::vector<uint32_t> &of
       w += off[gi + 1] - off[gi];
     }
     cost[st] = w;
+    const uint32_t *rec = &t.sched[t.strip_off[st]];
+    for (uint32_t ci = 0; ci < rec[0]; ci++) {
+      const int nq = (int)rec[8 + 8 * ci + 2], nn = (int)rec[8 + 8 * ci + 3];
+      t.tab_cap = std::max(t.tab_cap, (g.B == 2 ? nn + (nn + 1) / 2 : nn) + 8 * nq);
+    }
     t.need[2 * st] = (uint32_t)std::min<uint64_t>(w, 1u << 30);
     t.need[2 * st + 1] = (uint32_t)sw;
     t.max_words = std::max(t.max_words, t.need[2 * st]);
@@ -1605,7 +1615,7 @@ extern "C" lfc_status lfc_open_ex(const void *stream, size_t bytes, const lfc_op
   } catch (const std::bad_alloc &) {
     return fail(LFC_E_NOMEM, "lfc_open: out of host memory");
   }
-  const std::vector<uint32_t> &sched = stt.sched, &strip_off = stt.strip_off, &order = stt.order;
+  const std::vector<uint32_t> &sched = stt.sched, &order = stt.order;
   // the colour kernel's strip tables (tile of the default capacity, which
   // holds a run of kBatch leaves and four ancestors in all three channels)
   const int tile_cap_rgb = tile_blocks(ps.g.B);
@@ -1615,7 +1625,16 @@ extern "C" lfc_status lfc_open_ex(const void *stream, size_t bytes, const lfc_op
   } catch (const std::bad_alloc &) {
     return fail(LFC_E_NOMEM, "lfc_open: out of host memory");
   }
-  Part parts[16] = {
+  // the runs' records and, after them, the words the whole-field kernels keep of each
+  std::vector<int32_t> runs;
+  try {
+    runs = tt.batch;
+    for (size_t r = 0; r < tt.batch.size(); r += kBatchWords)
+      runs.insert(runs.end(), tt.batch.begin() + (long)r + 1, tt.batch.begin() + (long)r + 1 + kRunWords);
+  } catch (const std::bad_alloc &) {
+    return fail(LFC_E_NOMEM, "lfc_open: out of host memory");
+  }
+  Part parts[15] = {
       {ps.rkv, ps.rkv_bytes, 0},
       {ps.off.data(), ps.off.size() * 4, 0},
       {ps.srv.data(), ps.srv.size() * 4, 0},
@@ -1623,11 +1642,10 @@ extern "C" lfc_status lfc_open_ex(const void *stream, size_t bytes, const lfc_op
       {ps.poff.data(), ps.poff.size() * 4, 0},
       {tt.path.data(), tt.path.size() * 4, 0},
       {tt.root.data(), tt.root.size() * 4, 0},
-      {tt.batch.data(), tt.batch.size() * 4, 0},
+      {runs.data(), runs.size() * 4, 0},
       {zeros, 4, 0},
       {ps.pbase.data(), ps.pbase.size() * 4, 0},
       {sched.data(), sched.size() * 4, 0},
-      {strip_off.data(), strip_off.size() * 4, 0},
       {order.data(), order.size() * 4, 0},
       {rgbt.sched.data(), rgbt.sched.size() * 4, 0},
       {rgbt.order.data(), rgbt.order.size() * 4, 0},
@@ -1682,11 +1700,10 @@ extern "C" lfc_status lfc_open_ex(const void *stream, size_t bytes, const lfc_op
   lf->n_batch = (int)(tt.batch.size() / kBatchWords);
   lf->d_pbase = reinterpret_cast<const uint32_t *>(d + parts[9].at);
   lf->d_sched = reinterpret_cast<const uint32_t *>(d + parts[10].at);
-  lf->d_strip_off = reinterpret_cast<const uint32_t *>(d + parts[11].at);
-  lf->d_order = reinterpret_cast<const uint32_t *>(d + parts[12].at);
-  lf->d_sched_rgb = reinterpret_cast<const uint32_t *>(d + parts[13].at);
-  lf->d_order_rgb = reinterpret_cast<const uint32_t *>(d + parts[14].at);
-  lf->d_dir2 = reinterpret_cast<const uint32_t *>(d + parts[15].at);
+  lf->d_order = reinterpret_cast<const uint32_t *>(d + parts[11].at);
+  lf->d_sched_rgb = reinterpret_cast<const uint32_t *>(d + parts[12].at);
+  lf->d_order_rgb = reinterpret_cast<const uint32_t *>(d + parts[13].at);
+  lf->d_dir2 = reinterpret_cast<const uint32_t *>(d + parts[14].at);
   lf->tile_cap_rgb = tile_cap_rgb;
   lf->rgb_max_chunks = rgbt.max_chunks;
   lf->rgb_tab_cap = rgbt.tab_cap;
@@ -1695,6 +1712,7 @@ extern "C" lfc_status lfc_open_ex(const void *stream, size_t bytes, const lfc_op
   // LDS staging of the whole-field kernel is sized by the largest strip:
   // group words plus the strip's decode schedule
   lf->max_strip_words = stt.max_words;
+  lf->lf_tab_words = stt.tab_cap;
   lf->strip_need = std::move(stt.need);
   *out = lf;
   return LFC_OK;
@@ -1770,20 +1788,20 @@ extern "C" lfc_status lfc_tune_decode(lfc_lf *lf, int16_t *d_out, int32_t reps, 
     return LFC_OK;
   };
   struct Saved {
-    int cap;
-    const uint32_t *sched, *strip_off, *order;
+    int cap, tab_words;
+    const uint32_t *sched, *order;
     std::vector<uint32_t> need;
     uint32_t max_words;
     void *own;
   };
   auto save = [&]() {
-    return Saved{lf->tile_cap, lf->d_sched, lf->d_strip_off, lf->d_order, lf->strip_need, lf->max_strip_words,
-                 lf->d_sched_own};
+    return Saved{lf->tile_cap, lf->lf_tab_words, lf->d_sched, lf->d_order, lf->strip_need,
+                 lf->max_strip_words, lf->d_sched_own};
   };
   auto restore = [&](const Saved &v) {
     lf->tile_cap = v.cap;
+    lf->lf_tab_words = v.tab_words;
     lf->d_sched = v.sched;
-    lf->d_strip_off = v.strip_off;
     lf->d_order = v.order;
     lf->strip_need = v.need;
     lf->max_strip_words = v.max_words;
@@ -1837,25 +1855,23 @@ extern "C" lfc_status lfc_tune_decode(lfc_lf *lf, int16_t *d_out, int32_t reps, 
       if (seen || g.L < 2) continue;
       StripTables t;
       make_strip_tables(g, off, srv, dbase, poff, batch, cap, t);
-      const size_t a0 = 0, a1 = align256(4 * t.sched.size()), a2 = a1 + align256(4 * t.strip_off.size());
-      const size_t total = a2 + align256(4 * t.order.size());
+      const size_t a1 = align256(4 * t.sched.size()), total = a1 + align256(4 * t.order.size());
       void *buf = nullptr;
       if (hipMalloc(&buf, total) != hipSuccess) {
         (void)hipGetLastError();
         break;   // no room for another table set: keep what was measured
       }
       char *d = static_cast<char *>(buf);
-      if (hipMemcpy(d + a0, t.sched.data(), 4 * t.sched.size(), hipMemcpyHostToDevice) != hipSuccess ||
-          hipMemcpy(d + a1, t.strip_off.data(), 4 * t.strip_off.size(), hipMemcpyHostToDevice) != hipSuccess ||
-          hipMemcpy(d + a2, t.order.data(), 4 * t.order.size(), hipMemcpyHostToDevice) != hipSuccess) {
+      if (hipMemcpy(d, t.sched.data(), 4 * t.sched.size(), hipMemcpyHostToDevice) != hipSuccess ||
+          hipMemcpy(d + a1, t.order.data(), 4 * t.order.size(), hipMemcpyHostToDevice) != hipSuccess) {
         (void)hipFree(buf);
         st = fail(LFC_E_HIP, "lfc_tune_decode: copy of the strip tables");
         break;
       }
       lf->tile_cap = cap;
-      lf->d_sched = reinterpret_cast<const uint32_t *>(d + a0);
-      lf->d_strip_off = reinterpret_cast<const uint32_t *>(d + a1);
-      lf->d_order = reinterpret_cast<const uint32_t *>(d + a2);
+      lf->lf_tab_words = t.tab_cap;
+      lf->d_sched = reinterpret_cast<const uint32_t *>(d);
+      lf->d_order = reinterpret_cast<const uint32_t *>(d + a1);
       lf->strip_need = std::move(t.need);
       lf->max_strip_words = t.max_words;
       lf->d_sched_own = buf;

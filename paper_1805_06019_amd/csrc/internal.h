@@ -36,8 +36,11 @@ lfc_status make_geometry(const lfc_params &p, Geometry &g, std::string *why);
 //   [0] n, [1..4] view indices (-1 unused), [5] root, [6..9] serial indices of
 //   the ancestors from level L-2 down to level 1 (-1 unused), [10] serial
 //   index of the first view of the run (the others follow it), [11..15] unused.
+// On the device the records are followed by words [1..5] of each, packed
+// (kRunWords a run): what the whole-field kernels keep of a run in LDS.
 constexpr int kBatch = 4;
 constexpr int kBatchWords = 16;
+constexpr int kRunWords = 5;
 // Default capacity, in stored residual blocks, of the whole-field kernel's
 // compact tile (32 KB of LDS; tile slots are 11-bit, beside a 5-bit block
 // index in 16-bit schedule items, so at most 2048).
@@ -47,10 +50,19 @@ constexpr int tile_blocks(int B) { return B == 2 ? 2048 : (B == 4 ? 1024 : 256);
 // groups' start words and lengths (zero past the image's right edge), so a
 // workgroup reads everything it needs to start a strip in one load.
 constexpr int order_words(int B) { return 4 + 2 * (64 / B); }
-// Most words of a chunk's gather table (per-node masks and first slots,
-// per-run node positions) in the whole-field kernel's schedule: the kernel
-// copies a chunk's table into LDS when the strip is read from global memory.
-constexpr int kLFTabWords = 1024;
+// Most words of a chunk's gather table and run records (per-node masks and
+// first slots, per run three words of node positions and five of its record)
+// in the whole-field kernel's schedule, beyond its first run's: the kernel
+// keeps them in LDS.
+// (beside a tile of more than 64 KB, fewer)
+constexpr size_t lf_tab_limit(int B, int tile_cap) { return tile_cap * B * B / 2 > 16384 ? 1024 : 1280; }
+// Range codes whose 2 x 2 and 4 x 4 blocks the whole-field kernels decode from
+// one window of words: all but plain ones of more than 7 bits.
+constexpr bool window_code(uint32_t code) { return code < 7u || code >= 12u; }
+// Position of block j of a strip in the whole-field schedule's node masks: the
+// k-th blocks of the strip's eight 8-pixel segments lie together, as the lanes
+// that read them do.
+constexpr int strip_bit(int B, int j) { return j / (8 / B) + (j % (8 / B)) * 8; }
 // Most tree nodes in one chunk of the colour whole-field kernel's schedule
 // (the kernel copies a chunk's per-node tables into LDS).
 constexpr int kRGBNodeCap = 128;
@@ -94,7 +106,6 @@ struct lfc_lf {
   const int32_t *d_batch = nullptr;  // [n_batch][kBatchWords]
   int n_batch = 0;
   const uint32_t *d_sched = nullptr;     // decode schedule of the whole-field kernel (strip records)
-  const uint32_t *d_strip_off = nullptr; // [n_strips+1] word offset of each strip's record
   const uint32_t *d_order = nullptr;     // [n_strips] strips in the order the whole-field kernel takes them
   const uint32_t *d_sched_rgb = nullptr;     // colour decode schedule (strips of all three channels)
   const uint32_t *d_order_rgb = nullptr;     // [n_strips_rgb][2] strip, first word of its record; costliest first
@@ -102,6 +113,7 @@ struct lfc_lf {
   int rgb_max_chunks = 1;            // most chunks of one strip in the colour schedule
   int rgb_tab_cap = 0, rgb_run_cap = 0;   // most gather-table words and runs of one of its chunks
   int32_t *d_err = nullptr;          // device error flag
+  int lf_tab_words = 0;              // most gather-table and run-record words of a chunk of the whole-field schedule
   int tile_cap = 0;                  // blocks of the whole-field kernel's compact residual tile
   int64_t stage_cap = 0;             // LDS words for staging a strip (-1: as it needs, 0: none); the
                                      // setting used when a decode call gives none

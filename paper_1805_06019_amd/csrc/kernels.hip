@@ -105,6 +105,7 @@ __device__ __forceinline__ uint64_t join64(const uint32_t v[3], uint32_t sh) {
 }
 
 typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+typedef short i16x2 __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ u16x2 as_u16x2(uint32_t v) { return __builtin_bit_cast(u16x2, v); }
 __device__ __forceinline__ uint32_t as_u32(u16x2 v) { return __builtin_bit_cast(uint32_t, v); }
@@ -301,6 +302,7 @@ constexpr int kLFThreads = 512;
 constexpr int kLFWaves = kLFThreads / 64;
 constexpr int kLFHeadWords = 448;     // LDS words before the residual tile (LUT, per-block extents)
 constexpr int kStagePad = 8;          // zero words after the staged group words
+using lfc::kRunWords;
 
 // LDS words of the whole-field kernel's compact tile: tile_cap slots of
 // stored blocks and one zero slot, rounded up to 16 bytes.
@@ -308,18 +310,17 @@ __host__ __device__ constexpr int lf_tile_words(int tile_cap, int S) { return ((
 
 struct LFArgs {
   const int16_t *rkv;
-  const uint32_t *off;
   const uint32_t *srv;
   const uint32_t *sched;      // decode schedule: one record per strip (see build_schedule on the host)
-  const uint32_t *strip_off;  // [n_strips+1] word offset of each strip's record
-  const uint32_t *order;      // [n_strips] strip of each workgroup, costliest first
+  const uint32_t *order;      // [n_strips][order_words] strip of each workgroup, costliest first
   const int32_t *batch;       // [nbatch][kBatchWords] runs of sibling leaves (see internal.h)
   int16_t *out;               // [nv][3][hp][wp]
-  int nbx, nv, L, q, wp, hp, nb, nbatch;
+  int nbx, L, q, wp, hp, nb, nbatch;
   int stage_cap;              // LDS words available for staging the strip
   int vec_store;              // output rows may be stored 16 bytes at a time
   int n_top, key_words;       // key views; LDS words of the strip's key-view rows (0: not staged)
   int tile_cap;               // blocks of the compact residual tile
+  int tab_words;              // LDS words of a chunk's gather table and run records
   int stream_out;             // store the output with the non-temporal hint
 };
 
@@ -406,6 +407,127 @@ __device__ __forceinline__ void decode_block_k(const uint32_t *gw, uint32_t e, i
   }
 }
 
+// A 2 x 2 or 4 x 4 block whose bits are read at once, in one window of
+// window_words: every trit and quint block, and plain ones of at most 7 bits
+// (others decode row by row from memory).  Pairs of values are taken out by
+// packed 16-bit shifts of the word that holds their low bits, digits likewise;
+// a pair takes eight operations, five without a digit, against twelve and
+// seven, and a block two reads instead of up to fourteen.
+template <int B>
+constexpr int window_words() { return B == 2 ? 3 : (B == 4 ? 6 : 1); }
+template <int B>
+struct Window {
+  uint32_t w[window_words<B>()];
+};
+template <int B>
+__device__ __forceinline__ void fetch_window(const uint32_t *p, Window<B> &s) {
+  if constexpr (B <= 4) {
+#pragma unroll
+    for (int i = 0; i < window_words<B>(); i++) s.w[i] = p[i];
+  }
+}
+
+// two shifted copies of a 16-bit field: v's low (HI: high) half >> s per half
+template <bool HI>
+__device__ __forceinline__ uint32_t shr_both(uint32_t v, uint32_t s) {
+  const u16x2 x = as_u16x2(v);
+  const unsigned short f = HI ? x[1] : x[0];
+  return as_u32((u16x2){f, f} >> as_u16x2(s));
+}
+
+template <int B, int KIND>
+__device__ __forceinline__ void decode_window(const Window<B> &s, uint32_t e, int q, const uint16_t *lut,
+                                              uint32_t d[B * B / 2]) {
+  static_assert(B <= 4);
+  constexpr int NP = B * B / 2, MAXM = KIND == 0 ? 7 : 6;
+  constexpr int HDR = KIND == 0 ? 0 : (int)(KIND == 1 ? Planes<B * B>::trit : Planes<B * B>::quint);
+  constexpr int NB = (HDR + B * B * MAXM + 31) / 32, NL = (B * B * MAXM + 31) / 32;   // words of the block, of its low bits
+  static_assert(NB < window_words<B>());
+  const uint32_t m = KIND == 0 ? (e & 31u) + 1u : (KIND == 1 ? (e & 31u) - 12u : (e & 31u) - 19u);
+  uint32_t b[NB + 1];
+#pragma unroll
+  for (int i = 0; i < NB; i++) b[i] = __builtin_amdgcn_alignbit(s.w[i + 1], s.w[i], e >> 5);
+  b[NB] = 0;
+  // the pairs' digits, one per half, with bits of their neighbours above them
+  uint32_t dg[NP];
+  if constexpr (KIND == 1) {
+    uint32_t D = lut[b[0] & (B == 4 ? 255u : 127u)];
+    if constexpr (B == 4)
+      D |= (uint32_t)lut[(b[0] >> 8) & 255u] << 10 | (uint32_t)lut[(b[0] >> 16) & 255u] << 20 |
+           (uint32_t)lut[(b[0] >> 24) & 3u] << 30;
+#pragma unroll
+    for (int i = 0; i < NP; i++) {
+      const uint32_t at = 4u * (i % 4);
+      dg[i] = i < 4 ? shr_both<false>(D, at | (at + 2u) << 16) : shr_both<true>(D, at | (at + 2u) << 16);
+    }
+  } else if constexpr (KIND == 2) {
+    auto field = [&](uint32_t f) { return (uint32_t)lut[256u + f]; };
+    if constexpr (B == 4) {
+      const uint32_t f1 = field((b[0] >> 7) & 127u), f2 = field((b[0] >> 14) & 127u);
+      const uint32_t w0 = field(b[0] & 127u) | f1 << 9, w1 = f1 | f2 << 9;   // digits 0..5, 3..8
+      const uint32_t w2 = f2 >> 6 | field((b[0] >> 21) & 127u) << 3 |
+                          field(__builtin_amdgcn_alignbit(b[1], b[0], 28) & 127u) << 12;   // 8..14
+      const uint32_t w3 = w2 >> 12 | field((b[1] >> 3) & 7u) << 9;                         // 12..15
+      dg[0] = shr_both<false>(w0, 0u | 3u << 16);
+      dg[1] = shr_both<false>(w0, 6u | 9u << 16);
+      dg[2] = shr_both<false>(w1, 3u | 6u << 16);
+      dg[3] = shr_both<false>(w1, 9u | 12u << 16);
+      dg[4] = shr_both<false>(w2, 0u | 3u << 16);
+      dg[5] = shr_both<false>(w2, 6u | 9u << 16);
+      dg[6] = shr_both<false>(w3, 0u | 3u << 16);
+      dg[7] = shr_both<false>(w3, 6u | 9u << 16);
+    } else {
+      const uint32_t w0 = field(b[0] & 127u) | field((b[0] >> 7) & 7u) << 9;
+      dg[0] = shr_both<false>(w0, 0u | 3u << 16);
+      dg[1] = shr_both<false>(w0, 6u | 9u << 16);
+    }
+  }
+  // low bits, four values (at most 28 bits) at a time
+  uint32_t l[NL];
+#pragma unroll
+  for (int i = 0; i < NL; i++)
+    l[i] = HDR % 32 ? __builtin_amdgcn_alignbit(b[i + HDR / 32 + 1], b[i + HDR / 32], HDR % 32) : b[i + HDR / 32];
+  const uint32_t s01 = m << 16, lm = ((1u << m) - 1u) * 0x10001u;
+  const uint32_t zm = KIND == 0 ? lm : (((KIND == 1 ? 4u : 8u) << m) - 1u) * 0x10001u;
+#pragma unroll
+  for (int y = 0; y < NP / 2; y++) {
+    const uint32_t v[2] = {shr_both<false>(l[0], s01), shr_both<false>(l[0] >> (2u * m), s01)};
+#pragma unroll
+    for (int i = 0; i < 2; i++) {
+      // digit << m | low bits (what the shift carries into the upper half is
+      // below its digit), then the zigzag undone, doubled: z for even z, ~z for odd
+      const uint32_t z = KIND == 0 ? v[i] : __builtin_amdgcn_bitop3_b32(lm, v[i], dg[KIND == 0 ? 0 : 2 * y + i] << m, 0xCA);   // lm ? v : digit
+      const uint32_t odd = as_u32((u16x2){0, 0} - as_u16x2(z & 0x00010001u));
+      d[2 * y + i] = __builtin_amdgcn_bitop3_b32(z, zm, odd, 0x6A);   // (z & zm) ^ odd
+    }
+#pragma unroll
+    for (int i = 0; i < NL; i++)
+      if (i < ((NP / 2 - 1 - y) * 4 * MAXM + 31) / 32)
+        l[i] = i + 1 < NL ? __builtin_amdgcn_alignbit(l[i + 1], l[i], 4u * m) : l[i] >> (4u * m);
+  }
+  if (q) {
+    const unsigned short k = (unsigned short)(q - 1);
+#pragma unroll
+    for (int i = 0; i < NP; i++) d[i] = as_u32(as_u16x2(d[i]) << (u16x2){k, k});
+  } else {
+#pragma unroll
+    for (int i = 0; i < NP; i++) d[i] = __builtin_bit_cast(uint32_t, __builtin_bit_cast(i16x2, d[i]) >> (i16x2){1, 1});
+  }
+}
+
+// A block of a known kind whose window has been read; base is its group's first word.
+template <int B, int KIND>
+__device__ __forceinline__ void decode_fetched(const Window<B> &s, const uint32_t *words, uint32_t base, uint32_t e,
+                                               int q, const uint16_t *lut, uint32_t d[B * B / 2]) {
+  if constexpr (B <= 4) {
+    if (KIND != 0 || lfc::window_code(e & 31u)) {
+      decode_window<B, KIND>(s, e, q, lut, d);
+      return;
+    }
+  }
+  decode_block_k<B, KIND>(words + base, e, q, lut, d);
+}
+
 // A whole block of any kind decoded by one lane, with the generic row
 // decoder (one code for the three kinds, the row plans constant).
 template <int B>
@@ -440,214 +562,43 @@ __device__ __forceinline__ void lds_barrier() {
 typedef const __attribute__((address_space(4))) int32_t *uniform_i32;
 __device__ __forceinline__ uniform_i32 as_uniform(const int32_t *p) { return (uniform_i32)p; }
 
-// One chunk of phase B of the whole-field kernel.  sch is the chunk's record
-// of the decode schedule (runs, nodes, per-node masks of the stored blocks
-// and first tile slots, per-run node positions, directory entries and
-// (slot, block) items), in LDS or in global memory; the payload of block j of
-// the strip is at pw + s_po[j].  Step (3): every stored block decoded once,
-// whole, by one lane, with the decoder of its range kind, into its slot of
-// the compact tile; step (4): per sibling run, key-view row + ancestor rows +
-// leaf row (absent blocks add nothing), stored 16 bytes per lane.
-template <int B, bool KEYS, bool TAB>
-__device__ __forceinline__ void lf_chunk(const LFArgs &a, const uint32_t *sch, const uint32_t *pw,
-                                         const uint32_t *s_po, uint32_t *tile, const uint32_t *keys,
-                                         uint32_t *s_tab, const uint16_t *lut, int tid, int wave, int lane, int so,
-                                         int jq, int bx0, int nact, bool wide, uint64_t lane_off, uint32_t vstride,
-                                         int by, int c) {
-  constexpr int S = B * B, NBLK = 64 / B, H = B / 2, PB = 8 / B;
-  // the chunk's header fields, the same for every lane (made scalar)
-  const int q0 = __builtin_amdgcn_readfirstlane((int)sch[0]), nq = __builtin_amdgcn_readfirstlane((int)sch[1]);
-  const int nn = __builtin_amdgcn_readfirstlane((int)sch[2]);
-  const uint32_t n0 = __builtin_amdgcn_readfirstlane(sch[3]), n01 = __builtin_amdgcn_readfirstlane(sch[4]);
-  const uint32_t n = __builtin_amdgcn_readfirstlane(sch[5]);
-  const uint32_t *ents = sch + 6 + nn + (nn + 1) / 2 + 3 * nq;
-  const uint16_t *items = reinterpret_cast<const uint16_t *>(ents + n);
-  // the gather's table (per-node masks and first slots, per-run node
-  // positions): read where the schedule is (LDS in the staging tiers), or,
-  // with TAB, copied from global memory into LDS during the decode, so that
-  // the gather issues no vector load (each would wait for the wave's
-  // outstanding stores)
-  const uint32_t *tab = sch + 6;
-  if constexpr (TAB) {
-    const int tw = nn + (nn + 1) / 2 + 3 * nq;
-    for (int w0 = wave * 64; w0 < tw; w0 += kLFThreads)
-      if (w0 + lane < tw)
-        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(sch + 6 + w0 + lane),
-                                         (__attribute__((address_space(3))) void *)(s_tab + w0), 4, 0, 0);
-    tab = s_tab;
-  }
-  const uint32_t *masks = tab;
-  const uint16_t *firsts = reinterpret_cast<const uint16_t *>(masks + nn);
-  const uint32_t *runs = masks + nn + (nn + 1) / 2;
-  // (3) decode; the three kinds are laid end to end, so a wave mostly sees one kind.
-  // A lane's next entry is requested before its current block's payload, so
-  // the two reads overlap.
-  uint32_t e_nx = 0, t_nx = 0;
-  if ((uint32_t)tid < n) {
-    e_nx = ents[tid];
-    t_nx = items[tid];
-  }
-  for (uint32_t it = tid; it < n; it += kLFThreads) {
-    const uint32_t e = e_nx, t = t_nx;
-    if (it + kLFThreads < n) {
-      e_nx = ents[it + kLFThreads];
-      t_nx = items[it + kLFThreads];
-    }
-    const uint32_t *gw = pw + s_po[t & 31u];
-    uint32_t d[S / 2];
-    if (it < n0) decode_block_k<B, 0>(gw, e, a.q, lut, d);
-    else if (it < n01) decode_block_k<B, 1>(gw, e, a.q, lut, d);
-    else decode_block_k<B, 2>(gw, e, a.q, lut, d);
-    uint32_t *dst = tile + (t >> 5) * (S / 2);
-    if constexpr (S / 2 >= 4) {
-#pragma unroll
-      for (int w = 0; w < S / 2; w += 4)
-        *reinterpret_cast<uint4 *>(dst + w) = make_uint4(d[w], d[w + 1], d[w + 2], d[w + 3]);
-    } else {
-      *reinterpret_cast<uint2 *>(dst) = make_uint2(d[0], d[1]);
-    }
-  }
-  if constexpr (TAB) __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0): the table copies have landed
-  lds_barrier();
-  // (4) gather and store.  A wave takes two runs at a time, one per half; a
-  // lane owns one sibling of its run and one 16-byte segment (PB blocks) of
-  // the strip's rows, and walks the B rows of its blocks: each node's tile
-  // slots are found once per lane, and an absent block reads the zeroed slot
-  // at the end of the tile (no masking).  Gather issue goes first; the
-  // decode of a workgroup sharing the compute unit fills the gaps.
-  __builtin_amdgcn_s_setprio(2);
-  const int L = a.L;
-  const int half = lane >> 5;
-  const uint32_t zslot = (uint32_t)a.tile_cap;       // the zeroed slot
-  const int pairs = (nq + 1) / 2, per = (pairs + kLFWaves - 1) / kLFWaves;
-  // tile words of this lane's block k of a node (mask mk of its stored
-  // blocks, first slot f)
-  auto slot_of = [&](uint32_t mk, uint32_t f, int k) -> const uint32_t * {
-    const uint32_t j = (uint32_t)(jq * PB + k);
-    const uint32_t s = ((mk >> j) & 1u) ? f + (uint32_t)__popc(mk & ((1u << j) - 1u)) : zslot;
-    return tile + s * (S / 2);
-  };
-  for (int qp = wave * per; qp < min(pairs, wave * per + per); qp++) {
-    const int q_a = 2 * qp, q_b = min(2 * qp + 1, nq - 1);
-    const uniform_i32 ra = as_uniform(a.batch + (size_t)(q0 + q_a) * lfc::kBatchWords);
-    const uniform_i32 rb = as_uniform(a.batch + (size_t)(q0 + q_b) * lfc::kBatchWords);
-    // both records through the scalar unit (each field made wave-uniform
-    // before the per-half choice, so that the choice is not moved into the
-    // address of a vector load)
-    int fa[6], fb[6];
-#pragma unroll
-    for (int k = 0; k < 6; k++) {
-      fa[k] = __builtin_amdgcn_readfirstlane(ra[k]);
-      fb[k] = __builtin_amdgcn_readfirstlane(rb[k]);
-    }
-    const int qi = half ? q_b : q_a;
-    const bool run_live = !half || 2 * qp + 1 < nq;
-    const int nsib = half ? fb[0] : fa[0], root = half ? fb[5] : fa[5];
-    const int va = so == 0 ? fa[1] : (so == 1 ? fa[2] : (so == 2 ? fa[3] : fa[4]));
-    const int vb = so == 0 ? fb[1] : (so == 1 ? fb[2] : (so == 2 ? fb[3] : fb[4]));
-    const int vi = half ? vb : va;
-    const bool live = run_live && so < nsib;
-    // key-view rows
-    uint32_t x[B][4];
-    if constexpr (KEYS) {
-#pragma unroll
-      for (int y = 0; y < B; y++) {
-        const uint4 k4 = reinterpret_cast<const uint4 *>(keys)[(((root * B + y) * NBLK + jq * PB) * H) / 4];
-        x[y][0] = k4.x;
-        x[y][1] = k4.y;
-        x[y][2] = k4.z;
-        x[y][3] = k4.w;
-      }
-    } else {
-#pragma unroll
-      for (int y = 0; y < B; y++) {
-#pragma unroll
-        for (int w = 0; w < 4; w++) x[y][w] = 0;
-#pragma unroll
-        for (int k = 0; k < PB; k++)
-          if (k < nact)
-            load_row<B>(a.rkv + ((size_t)(root * a.nb + by * a.nbx + bx0 + k) * 3 + c) * S + y * B, x[y] + k * H);
-      }
-    }
-    // node rows added to every row of the lane's blocks
-    auto add_node = [&](int ln) {
-      const uint32_t mk = masks[ln], f = firsts[ln];
-#pragma unroll
-      for (int k = 0; k < PB; k++) {
-        const uint32_t *t = slot_of(mk, f, k);
-#pragma unroll
-        for (int y = 0; y < B; y++) {
-          if constexpr (H == 1) {
-            x[y][k] = add_pk(x[y][k], t[y]);
-          } else if constexpr (H == 2) {
-            const uint2 v = *reinterpret_cast<const uint2 *>(t + y * 2);
-            x[y][2 * k] = add_pk(x[y][2 * k], v.x);
-            x[y][2 * k + 1] = add_pk(x[y][2 * k + 1], v.y);
-          } else {
-            const uint4 v = *reinterpret_cast<const uint4 *>(t + y * 4);
-            x[y][0] = add_pk(x[y][0], v.x);
-            x[y][1] = add_pk(x[y][1], v.y);
-            x[y][2] = add_pk(x[y][2], v.z);
-            x[y][3] = add_pk(x[y][3], v.w);
-          }
-        }
-      }
-    };
-    const uint32_t w0 = runs[3 * qi], w1 = runs[3 * qi + 1], w2 = runs[3 * qi + 2];
-    const int anc_ln[4] = {(int)(w0 >> 16), (int)(w1 & 0xFFFFu), (int)(w1 >> 16), (int)(w2 & 0xFFFFu)};
-#pragma unroll
-    for (int k = 0; k < 4; k++)
-      if (k < L - 2) add_node(anc_ln[k]);
-    add_node((int)(w0 & 0xFFFFu) + (live ? so : 0));
-    if (!live) continue;
-    int16_t *dst = a.out + ((uint64_t)(uint32_t)vi * vstride + lane_off);
-    // separate loops, so that the 16-byte stores stay whole
-    if (wide && a.stream_out) {
-#pragma unroll
-      for (int y = 0; y < B; y++) put4<true>(dst + (size_t)y * a.wp, x[y]);
-    } else if (wide) {
-#pragma unroll
-      for (int y = 0; y < B; y++) put4<false>(dst + (size_t)y * a.wp, x[y]);
-    } else if (nact > 0) {
-#pragma unroll
-      for (int y = 0; y < B; y++)
-#pragma unroll
-        for (int k = 0; k < PB; k++)
-          if (k < nact) {
-            if (a.stream_out) put_row<B, true>(dst + (size_t)y * a.wp + k * B, x[y] + k * H);
-            else put_row<B, false>(dst + (size_t)y * a.wp + k * B, x[y] + k * H);
-          }
-    }
-  }
-  __builtin_amdgcn_s_setprio(0);
-  lds_barrier();
-}
-
 // One workgroup = one channel c, one row of blocks by, one strip of 64/B
 // consecutive blocks (64 pixels).  Phase A copies into LDS what fits of the
 // strip's data: its groups and its decode schedule (tier 1), else the
 // schedule only (tier 2: payload read through bit windows from global
-// memory), else nothing (tier 3), plus the strip's key-view rows.  Phase B
+// memory), else nothing (tier 3, the default), plus its key-view rows.  Phase B
 // walks the strip's chunks (runs of sibling leaves in serial order whose
-// stored blocks fit the compact tile): decode every stored residual block of
-// the chunk once into the tile, then write the chunk's leaves (key view +
-// ancestors + leaf), 16 bytes per lane.
+// stored blocks fit the compact tile): (3) every stored block of the chunk is
+// decoded once, whole, by one lane, with the decoder of its range kind, into
+// its slot of the tile; (4) per sibling run, key-view row + ancestor rows +
+// leaf row (absent blocks add nothing), stored 16 bytes per lane.
+// What bounds it is memory where the light field is sparse (289 views of
+// 512 x 512 at 40 dB: 105 -> 101 us, 5.2 TB/s) and was, where it is dense, the
+// vector-memory path (eleven short reads per block), LDS bank conflicts and the
+// issue of vector instructions.  Hence one window per block, entries in an order
+// in which a wave's windows adjoin, a tile of 16-byte planes, node masks whose
+// bits lie as the lanes that test them, tables read from LDS alone, and
+// everything a chunk needs read before the chunk before it stores (a load waits
+// for older stores).  At 50 dB (15.9 M blocks): 172 -> 121 us, 635 MB at
+// 5.2 TB/s; 62 -> 49 million vector instructions, LDS conflicts 40 -> 16 million
+// cycles.  Staged (STAGED: the caller gave LDS for it), a strip's chunks are
+// read when they are decoded.
 // (B <= 4: at most 80 VGPRs, six waves per SIMD, so three workgroups share a
 // compute unit whenever their LDS fits; B = 8 keeps its registers)
-template <int B>
+template <int B, bool STAGED, bool KEYS>
 __global__ __launch_bounds__(kLFThreads, B <= 4 ? 6 : 1) void k_decode_lf(LFArgs a) {
   constexpr int S = B * B, NBLK = 64 / B, H = B / 2;
   constexpr int PB = 8 / B;                            // blocks per 16-byte row segment (1 for B = 8)
   extern __shared__ uint32_t smem[];
-  uint16_t *lut = reinterpret_cast<uint16_t *>(smem);  // 384 x u16 = 192 words
+  const uint16_t *lut = reinterpret_cast<const uint16_t *>(smem);   // 384 x u16 = 192 words
   uint32_t *s_o0 = smem + 192;                         // group start word in the SRV section
   uint32_t *s_len = smem + 256;                        // group length in words
   uint32_t *s_wo = smem + 320;                         // staged group words
   uint32_t *s_cnt = smem + 384;                        // [0] tier, [1] staged group words, [2] schedule words
-  uint32_t *tile = smem + kLFHeadWords;                // compact tile: [tile_cap + 1][S/2], the last slot zero
+  uint32_t *tile = smem + kLFHeadWords;                // compact tile, the last slot zero (tile_quad)
   uint32_t *keys = tile + lf_tile_words(a.tile_cap, S); // [n_top][B][NBLK][H]
-  uint32_t *s_tab = keys + a.key_words;                 // a chunk's gather table (strips read from global memory)
-  uint32_t *stage = s_tab + lfc::kLFTabWords;
+  uint32_t *s_tab = keys + a.key_words;                 // two chunks' gather tables (tier 3) and run records
+  uint32_t *stage = s_tab + 2 * a.tab_words;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   // the workgroup's strip (strips are taken costliest first, so the last
@@ -659,12 +610,73 @@ __global__ __launch_bounds__(kLFThreads, B <= 4 ? 6 : 1) void k_decode_lf(LFArgs
   const int st = uent[0];
   const int sx = st % (int)gridDim.x, by = (st / (int)gridDim.x) % (int)gridDim.y, c = st / ((int)gridDim.x * (int)gridDim.y);
   const uint32_t sched0 = (uint32_t)uent[1], sched_len = (uint32_t)uent[2];
+  // the strip's chunk count and chunk headers (scalar loads)
+  const uint32_t *gs = a.sched + sched0;
+  const uniform_i32 head = as_uniform(reinterpret_cast<const int32_t *>(gs));
+  const int nck = head[0];
+  struct Header {
+    int at, q0, nq, nn;
+    uint32_t n0, n01, n;
+    int words;   // of the gather table
+  };
+  auto header = [&](int ci) {
+    const uniform_i32 h = head + 8 + 8 * ci;
+    Header r{h[0], h[1], h[2], h[3], (uint32_t)h[4], (uint32_t)h[5], (uint32_t)h[6], 0};
+    r.words = (B == 2 ? r.nn + (r.nn + 1) / 2 : r.nn) + 3 * r.nq;
+    return r;
+  };
+  // h: the chunk being decoded, hn: the one after it.  Unless staged, the lane
+  // holds its first two entries of each, (e, t) and (f, u).  (A lane past a
+  // chunk's last entry takes that entry: it decodes the same block into the same
+  // slot.)
+  Header h{}, hn{};
+  uint32_t e[2] = {}, t[2] = {}, f[2] = {}, u[2] = {};
+  auto entry = [&](const Header &r, uint32_t it, uint32_t &en, uint32_t &item) {
+    const uint32_t *ents = gs + r.at + r.words;
+    const uint32_t i = min(it, r.n - 1);
+    en = ents[i];
+    item = reinterpret_cast<const uint16_t *>(ents + r.n)[i];
+  };
+  // a chunk's gather table, unless it is staged, and after it its run records into LDS
+  auto tables_to_lds = [&](const Header &r, uint32_t *dst, bool tab) {
+    if (tab) {
+      for (int w = wave * 64; w < r.words; w += kLFThreads)
+        if (w + lane < r.words)
+          __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(gs + r.at + w + lane),
+                                           (__attribute__((address_space(3))) void *)(dst + w), 4, 0, 0);
+      dst += r.words;
+    }
+    const uint32_t *recs = reinterpret_cast<const uint32_t *>(a.batch + (size_t)a.nbatch * lfc::kBatchWords) +
+                           (size_t)r.q0 * kRunWords;
+    for (int w = wave * 64; w < kRunWords * r.nq; w += kLFThreads)
+      if (w + lane < kRunWords * r.nq)
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(recs + w + lane),
+                                         (__attribute__((address_space(3))) void *)(dst + w), 4, 0, 0);
+  };
+  if (a.L > 1) {
+    h = header(0);
+    if (nck > 1) hn = header(1);
+    if constexpr (!STAGED) {
+#pragma unroll
+      for (int k = 0; k < 2; k++) {
+        if (h.n) entry(h, tid + k * kLFThreads, e[k], t[k]);
+        if (hn.n) entry(hn, tid + k * kLFThreads, f[k], u[k]);
+      }
+      tables_to_lds(h, s_tab, true);
+    }
+  }
   // the LUT from its table (a copy straight into LDS)
   if (tid < kLutEntries / 2) __builtin_amdgcn_global_load_lds(
       (const __attribute__((address_space(1))) void *)(kLutTable.w + tid),
       (__attribute__((address_space(3))) void *)(smem + (tid & ~63)), 4, 0, 0);
-  if (tid < S / 2) tile[a.tile_cap * (S / 2) + tid] = 0u;   // the slot of every absent block
-  if (tid < 64) {
+  // 16-byte quad k of tile slot s (B = 2: a slot is 8 bytes): a slot's quads lie
+  // tile_cap + 1 quads apart, so that lanes at neighbouring slots reach
+  // different banks
+  const int plane = 4 * (a.tile_cap + 1);
+  if (tid < S / 2) tile[B == 2 ? a.tile_cap * (S / 2) + tid : (tid / 4) * plane + a.tile_cap * 4 + tid % 4] = 0u;
+  if constexpr (!STAGED) {
+    if (tid < NBLK) s_o0[tid] = ent[4 + tid];
+  } else if (tid < 64) {
     // wave 0: the strip's group offsets and lengths, their exclusive prefix
     // sum (a wave scan) and the staging tier
     uint32_t o0 = 0, len = 0;
@@ -693,33 +705,36 @@ __global__ __launch_bounds__(kLFThreads, B <= 4 ? 6 : 1) void k_decode_lf(LFArgs
       s_cnt[2] = tier == 1u ? words + kStagePad : 0u;
     }
   }
-  __syncthreads();
-  const uint32_t tier = s_cnt[0], sched_at = s_cnt[2];
-  // every copy goes straight from global memory to LDS, all in flight at once
-  if (tier == 1u)
-    for (int j = wave; j < NBLK; j += kLFWaves)
-      if (s_len[j]) lds_copy(stage + s_wo[j], a.srv + s_o0[j], s_len[j], lane);
-  if (tier < 3u) {
-    // the schedule, split over the waves in pieces of whole 64-word rows
-    const uint32_t rows = (sched_len + 63) / 64, per = (rows + kLFWaves - 1) / kLFWaves;
-    const uint32_t r0 = min(rows, (uint32_t)wave * per), r1 = min(rows, r0 + per);
-    if (r1 > r0) lds_copy(stage + sched_at + r0 * 64, a.sched + sched0 + r0 * 64, min(sched_len, r1 * 64) - r0 * 64, lane);
-  }
-  if (a.key_words) {
-    // the strip's key-view rows, laid out as the tile: [root][row][block][H]
-    const uint32_t *rk = reinterpret_cast<const uint32_t *>(a.rkv);
-    for (int t0 = wave * 64; t0 < a.key_words; t0 += kLFThreads) {
-      const int t = t0 + lane, h = t % H, j = (t / H) % NBLK, y = (t / (H * NBLK)) % B, r = t / (H * NBLK * B);
-      const int bx = sx * NBLK + j;
-      if (t < a.key_words && bx < a.nbx)
+  if constexpr (KEYS) {
+    // the strip's key-view rows, [root][row][block][H]: a wave's load covers two
+    // rows (64 words) of a root
+    const uint32_t *rk = reinterpret_cast<const uint32_t *>(a.rkv) +
+                         ((size_t)(by * a.nbx + sx * NBLK + (lane & 31) / H) * 3 + c) * (S / 2) + (lane >> 5) * H + lane % H;
+    const bool in = sx * NBLK + (lane & 31) / H < a.nbx;
+    for (int f = wave; f < a.n_top * (B / 2); f += kLFWaves)
+      if (in)
         __builtin_amdgcn_global_load_lds(
-            (const __attribute__((address_space(1))) void *)(rk + ((size_t)(r * a.nb + by * a.nbx + bx) * 3 + c) *
-                                                                  (S / 2) + y * H + h),
-            (__attribute__((address_space(3))) void *)(keys + t0), 4, 0, 0);
+            (const __attribute__((address_space(1))) void *)(rk + (size_t)(f / (B / 2)) * a.nb * (3 * S / 2) + f % (B / 2) * B),
+            (__attribute__((address_space(3))) void *)(keys + f * 64), 4, 0, 0);
+  }
+  uint32_t tier = 3, sched_at = 0;
+  if constexpr (STAGED) {
+    __syncthreads();
+    tier = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_cnt[0]);
+    sched_at = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_cnt[2]);
+    // every copy goes straight from global memory to LDS, all in flight at once
+    if (tier == 1u)
+      for (int j = wave; j < NBLK; j += kLFWaves)
+        if (s_len[j]) lds_copy(stage + s_wo[j], a.srv + s_o0[j], s_len[j], lane);
+    if (tier < 3u) {
+      // the schedule, split over the waves in pieces of whole 64-word rows
+      const uint32_t rows = (sched_len + 63) / 64, per = (rows + kLFWaves - 1) / kLFWaves;
+      const uint32_t r0 = min(rows, (uint32_t)wave * per), r1 = min(rows, r0 + per);
+      if (r1 > r0) lds_copy(stage + sched_at + r0 * 64, a.sched + sched0 + r0 * 64, min(sched_len, r1 * 64) - r0 * 64, lane);
     }
+    if (tier == 1u && tid < kStagePad) stage[s_cnt[1] + tid] = 0;
   }
   __builtin_amdgcn_s_waitcnt(0);
-  if (tier == 1u && tid < kStagePad) stage[s_cnt[1] + tid] = 0;
   __syncthreads();
 
   const uint32_t vstride = 3u * (uint32_t)a.hp * (uint32_t)a.wp;
@@ -742,32 +757,214 @@ __global__ __launch_bounds__(kLFThreads, B <= 4 ? 6 : 1) void k_decode_lf(LFArgs
   }
   // store-side lane mapping: run of the wave's pair (lane / 32), sibling in
   // the run, segment of PB blocks (16 bytes of each of the B rows)
-  const int so = (lane >> 3) & 3, jq = lane & 7;
+  const int half = lane >> 5, so = (lane >> 3) & 3, jq = lane & 7;
   const int bx0 = sx * NBLK + jq * PB;
   const int nact = max(0, min(PB, a.nbx - bx0));       // blocks of the segment inside the image
   const bool wide = nact == PB && a.vec_store;          // a 16-byte store is aligned
   const uint64_t lane_off = cplane + (uint64_t)(by * B) * a.wp + (uint64_t)bx0 * B;
-  const uint32_t *gsched = a.sched + sched0;
-  const uint32_t *lsched = stage + sched_at;
-  const int nck = (int)(tier < 3u ? lsched[0] : gsched[0]);
-  // one code path per staging tier and key-row placement, so that no path
-  // carries loads it never issues
-  auto chunks = [&](auto keys_staged) {
-    constexpr bool K = decltype(keys_staged)::value;
-    for (int ci = 0; ci < nck; ci++) {
-      if (tier == 1u)
-        lf_chunk<B, K, false>(a, lsched + lsched[1 + ci], stage, s_wo, tile, keys, s_tab, lut, tid, wave, lane, so, jq,
-                              bx0, nact, wide, lane_off, vstride, by, c);
-      else if (tier == 2u)
-        lf_chunk<B, K, false>(a, lsched + lsched[1 + ci], a.srv, s_o0, tile, keys, s_tab, lut, tid, wave, lane, so, jq,
-                              bx0, nact, wide, lane_off, vstride, by, c);
-      else
-        lf_chunk<B, K, true>(a, gsched + gsched[1 + ci], a.srv, s_o0, tile, keys, s_tab, lut, tid, wave, lane, so, jq,
-                             bx0, nact, wide, lane_off, vstride, by, c);
+  const uint32_t zslot = (uint32_t)a.tile_cap;          // the zeroed slot
+
+  // (3) one entry: its block's residuals into its tile slot
+  auto decode_to_tile = [&](uint32_t it, const Window<B> &w, const uint32_t *words, uint32_t base, uint32_t en, uint32_t item) {
+    uint32_t d[S / 2];
+    if (it < h.n0) decode_fetched<B, 0>(w, words, base, en, a.q, lut, d);
+    else if (it < h.n01) decode_fetched<B, 1>(w, words, base, en, a.q, lut, d);
+    else decode_fetched<B, 2>(w, words, base, en, a.q, lut, d);
+    uint32_t *dst = tile + (item >> 5) * (B == 2 ? 2 : 4);
+    if constexpr (B == 2) {
+      *reinterpret_cast<uint2 *>(dst) = make_uint2(d[0], d[1]);
+    } else {
+#pragma unroll
+      for (int k = 0; k < S / 8; k++)
+        *reinterpret_cast<uint4 *>(dst + k * plane) = make_uint4(d[4 * k], d[4 * k + 1], d[4 * k + 2], d[4 * k + 3]);
     }
   };
-  if (a.key_words) chunks(std::true_type{});
-  else chunks(std::false_type{});
+  // (4) a wave takes two runs at a time, one per half; a lane owns one sibling
+  // of its run and one 16-byte segment (PB blocks) of the strip's rows.  Node
+  // tables and run records come from LDS (a vector load would wait for the
+  // wave's outstanding stores); an absent block reads the zeroed slot (no
+  // masking).  nodes_c: nodes of a path, -1 if found at run time.
+  auto gather = [&](auto nodes_c, int nq, int nn, const uint32_t *tab, const uint32_t *rec) {
+    constexpr int NC = decltype(nodes_c)::value, NM = NC < 0 ? lfc::kMaxLevels - 1 : NC;
+    const int nodes = NC < 0 ? a.L - 1 : NC;
+    const uint16_t *firsts = reinterpret_cast<const uint16_t *>(tab + nn);   // (B = 2)
+    const uint32_t *runs = tab + (B == 2 ? nn + (nn + 1) / 2 : nn);
+    for (int qp = wave; 2 * qp < nq; qp += kLFWaves) {
+      const int qi = min(2 * qp + half, nq - 1);
+      const int vi = rec[kRunWords * qi + so], root = rec[kRunWords * qi + 4];
+      const bool live = 2 * qp + half < nq && vi >= 0;
+      int node[NM];
+      {
+        const uint32_t w0 = runs[3 * qi];
+        node[0] = min((int)(w0 & 0xFFFFu) + so, nn - 1);
+        if constexpr (NM > 1) node[1] = (int)(w0 >> 16);
+        if constexpr (NM > 2) {
+          const uint32_t w1 = runs[3 * qi + 1], w2 = runs[3 * qi + 2];
+          node[2] = (int)(w1 & 0xFFFFu);
+          node[3] = (int)(w1 >> 16);
+          node[4] = (int)(w2 & 0xFFFFu);
+        }
+      }
+      uint32_t slot[NM][PB];
+#pragma unroll
+      for (int k = 0; k < NM; k++) {
+        if (NC < 0 && k >= nodes) continue;
+        const uint32_t w = tab[node[k]];
+        const uint32_t first = B == 2 ? firsts[node[k]] : w >> 16;
+#pragma unroll
+        for (int b = 0; b < PB; b++) {
+          const uint32_t bit = (uint32_t)(jq + 8 * b);
+          const uint32_t sl = first + (uint32_t)__popc(w & ((1u << bit) - 1u));
+          slot[k][b] = ((w >> bit) & 1u ? sl : zslot) * (B == 2 ? 2 : 4);
+        }
+      }
+      // key-view rows
+      uint32_t x[B][4];
+      if constexpr (KEYS) {
+#pragma unroll
+        for (int y = 0; y < B; y++) {
+          const uint4 k4 = reinterpret_cast<const uint4 *>(keys)[(((root * B + y) * NBLK + jq * PB) * H) / 4];
+          x[y][0] = k4.x;
+          x[y][1] = k4.y;
+          x[y][2] = k4.z;
+          x[y][3] = k4.w;
+        }
+      } else {
+#pragma unroll
+        for (int y = 0; y < B; y++) {
+#pragma unroll
+          for (int w = 0; w < 4; w++) x[y][w] = 0;
+#pragma unroll
+          for (int k = 0; k < PB; k++)
+            if (k < nact)
+              load_row<B>(a.rkv + ((size_t)(root * a.nb + by * a.nbx + bx0 + k) * 3 + c) * S + y * B, x[y] + k * H);
+        }
+      }
+      // node rows added to every row of the lane's blocks
+#pragma unroll
+      for (int k = 0; k < NM; k++) {
+        if (NC < 0 && k >= nodes) continue;
+#pragma unroll
+        for (int b = 0; b < PB; b++) {
+          const uint32_t *t = tile + slot[k][b];
+          if constexpr (B == 2) {
+            const uint2 v = *reinterpret_cast<const uint2 *>(t);
+            x[0][b] = add_pk(x[0][b], v.x);
+            x[1][b] = add_pk(x[1][b], v.y);
+          } else {
+#pragma unroll
+            for (int i = 0; i < S / 8; i++) {
+              const uint4 v = *reinterpret_cast<const uint4 *>(t + i * plane);
+              const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+              for (int z = 0; z < 4; z++) {
+                uint32_t &xw = x[(4 * i + z) / H][H * b + (4 * i + z) % H];
+                xw = add_pk(xw, w[z]);
+              }
+            }
+          }
+        }
+      }
+      if (!live) continue;
+      int16_t *dst = a.out + ((uint64_t)(uint32_t)vi * vstride + lane_off);
+      // separate loops, so that the 16-byte stores stay whole
+      if (wide && a.stream_out) {
+#pragma unroll
+        for (int y = 0; y < B; y++) put4<true>(dst + (size_t)y * a.wp, x[y]);
+      } else if (wide) {
+#pragma unroll
+        for (int y = 0; y < B; y++) put4<false>(dst + (size_t)y * a.wp, x[y]);
+      } else if (nact > 0) {
+#pragma unroll
+        for (int y = 0; y < B; y++)
+#pragma unroll
+          for (int k = 0; k < PB; k++)
+            if (k < nact) {
+              if (a.stream_out) put_row<B, true>(dst + (size_t)y * a.wp + k * B, x[y] + k * H);
+              else put_row<B, false>(dst + (size_t)y * a.wp + k * B, x[y] + k * H);
+            }
+      }
+    }
+  };
+  auto fetch = [&](uint32_t en, uint32_t item, Window<B> &w) { fetch_window<B>(a.srv + (s_o0[item & 31u] + (en >> 10)), w); };
+  Window<B> w[2] = {};
+  if (!STAGED && h.n) {
+    fetch(e[0], t[0], w[0]);
+    fetch(e[1], t[1], w[1]);
+    __builtin_amdgcn_s_waitcnt(0x0f70);   // landed (in the loop no wait for them would tell them from stores)
+  }
+  for (int ci = 0; ci < nck; ci++) {
+    const int nq = h.nq, nn = h.nn;
+    const uint32_t n = h.n;
+    uint32_t *tab = s_tab + (ci & 1) * a.tab_words, *rec = tab + h.words;
+    if constexpr (!STAGED) {
+      // the first two blocks of a lane have been read; the next chunk's are
+      // requested here, with its tables and the entries of the one after it, so
+      // that all have landed before the gather's stores (a load waits for older
+      // stores)
+#pragma unroll
+      for (int k = 0; k < 2; k++) {
+        if (wave * 64 + k * kLFThreads < n) decode_to_tile(min((uint32_t)tid + k * kLFThreads, n - 1), w[k], a.srv, s_o0[t[k] & 31u], e[k], t[k]);
+        e[k] = f[k], t[k] = u[k];
+        if (hn.n) fetch(e[k], t[k], w[k]);
+      }
+      for (uint32_t b = wave * 64 + 2 * kLFThreads; b < n; b += kLFThreads) {
+        uint32_t en, item;
+        entry(h, b + lane, en, item);
+        Window<B> wb;
+        fetch(en, item, wb);
+        decode_to_tile(min(b + lane, n - 1), wb, a.srv, s_o0[item & 31u], en, item);
+      }
+    } else {
+      // tier 3: tables, entries and payload from global memory; tier 2: payload
+      if (tier < 3u) {
+        rec = s_tab;
+        tab = stage + sched_at + h.at;
+      }
+      tables_to_lds(h, tier < 3u ? rec : tab, tier == 3u);
+      if (tier == 1u) {
+        const uint32_t *ents = tab + h.words;
+        const uint16_t *items = reinterpret_cast<const uint16_t *>(ents + n);
+        for (uint32_t it = tid; it < n; it += kLFThreads) {
+          const uint32_t en = ents[it], item = items[it], base = s_wo[item & 31u];
+          Window<B> wb;
+          fetch_window<B>(stage + (base + (en >> 10)), wb);
+          decode_to_tile(it, wb, stage, base, en, item);
+        }
+      } else {
+        for (uint32_t it = tid; it < n; it += kLFThreads) {
+          uint32_t en, item;
+          if (tier == 2u) {
+            const uint32_t *ents = tab + h.words;
+            en = ents[it];
+            item = reinterpret_cast<const uint16_t *>(ents + n)[it];
+          } else {
+            entry(h, it, en, item);
+          }
+          Window<B> wb;
+          fetch(en, item, wb);
+          decode_to_tile(it, wb, a.srv, s_o0[item & 31u], en, item);
+        }
+      }
+    }
+    h = hn;
+    hn.n = 0;
+    if (ci + 2 < nck) hn = header(ci + 2);
+    if constexpr (!STAGED) {
+#pragma unroll
+      for (int k = 0; k < 2; k++)
+        if (hn.n) entry(hn, tid + k * kLFThreads, f[k], u[k]);
+      if (ci + 1 < nck) tables_to_lds(h, s_tab + (~ci & 1) * a.tab_words, true);
+    }
+    __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0): this wave's reads have landed
+    lds_barrier();
+    __builtin_amdgcn_s_setprio(2);   // gather issue first; another workgroup's decode fills the gaps
+    if (a.L == 2) gather(std::integral_constant<int, 1>{}, nq, nn, tab, rec);
+    else if (a.L == 3) gather(std::integral_constant<int, 2>{}, nq, nn, tab, rec);
+    else gather(std::integral_constant<int, -1>{}, nq, nn, tab, rec);
+    __builtin_amdgcn_s_setprio(0);
+    lds_barrier();
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -956,7 +1153,6 @@ constexpr int kRenderThreads = 512;
 // saturating operation, whose clamp to 8 bits is that of the exact value
 // (tests/test_colour_packed.py).  Six operations a pixel against fourteen in 32
 // bits.
-typedef short i16x2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ uint32_t sat_bytes(i16x2 v) {   // both halves to 8 bits, in the two low bytes
   uint32_t r;
   asm("v_sat_pk_u8_i16 %0, %1" : "=v"(r) : "v"(v));
@@ -1250,9 +1446,8 @@ __global__ __launch_bounds__(kRenderThreads) void k_render_multi(const RenderReq
 using lfc::kRGBNodeCap;
 constexpr int kRGBNeedWords = 128;        // views a render may mask: at most 32 x 128
 constexpr int kRGBFixedWords = 192 + 96 + 4 + kRGBNodeCap / 32;
-constexpr int kRGBRecWords = 5;           // of a run: four views (-1: none), the root
 __host__ __device__ constexpr int rgb_head_words(int need_words, int tab_cap, int run_cap) {
-  return (kRGBFixedWords + need_words + tab_cap + (kRGBRecWords + 2) * run_cap + 3) & ~3;
+  return (kRGBFixedWords + need_words + tab_cap + (kRunWords + 2) * run_cap + 3) & ~3;
 }
 constexpr int kRGBKeyWordsMax = 6144;     // key-view rows of a strip staged in LDS up to 24 KB
 
@@ -1305,8 +1500,8 @@ __device__ __forceinline__ void rgb_strip(const RGBArgs &a, int wg, uint32_t *sm
   uint32_t *s_node = s_nlist + 4;                       // wanted nodes of the chunk, a bit each
   uint32_t *s_need = smem + kRGBFixedWords;             // the view mask
   uint32_t *s_mf = s_need + a.need_words;               // masks and first slots [3][nn], run node positions[nq][3]
-  int32_t *s_rec = reinterpret_cast<int32_t *>(s_mf + a.tab_cap);   // [nq][kRGBRecWords]
-  uint16_t *s_list = reinterpret_cast<uint16_t *>(s_rec + kRGBRecWords * a.run_cap);
+  int32_t *s_rec = reinterpret_cast<int32_t *>(s_mf + a.tab_cap);   // [nq][kRunWords]
+  uint16_t *s_list = reinterpret_cast<uint16_t *>(s_rec + kRunWords * a.run_cap);
                                                         // (run << 2 | sibling) pairs of the chunk
   uint32_t *tile = smem + rgb_head_words(a.need_words, a.tab_cap, a.run_cap);   // [tile_cap + 1][S/2], the last slot zero
   uint32_t *keys = tile + lf_tile_words(a.tile_cap, S); // [n_top][NBLK][3][S/2], blocks as in the tile
@@ -1455,14 +1650,11 @@ __device__ __forceinline__ void rgb_strip(const RGBArgs &a, int wg, uint32_t *sm
       if (w0 + lane < tab_words)
         __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(chunk + w0 + lane),
                                          (__attribute__((address_space(3))) void *)(s_mf + w0), 4, 0, 0);
-    for (int w0 = wave * 64; w0 < kRGBRecWords * nq; w0 += kLFThreads) {
-      const int t = w0 + lane;
-      if (t < kRGBRecWords * nq)
-        __builtin_amdgcn_global_load_lds(
-            (const __attribute__((address_space(1))) void *)(a.batch + (size_t)(q0 + t / kRGBRecWords) * lfc::kBatchWords +
-                                                             1 + t % kRGBRecWords),
-            (__attribute__((address_space(3))) void *)(s_rec + w0), 4, 0, 0);
-    }
+    const uint32_t *recs = reinterpret_cast<const uint32_t *>(a.batch + (size_t)a.nbatch * lfc::kBatchWords) + (size_t)q0 * kRunWords;
+    for (int w0 = wave * 64; w0 < kRunWords * nq; w0 += kLFThreads)
+      if (w0 + lane < kRunWords * nq)
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(recs + w0 + lane),
+                                         (__attribute__((address_space(3))) void *)(s_rec + w0), 4, 0, 0);
     // (3) decode every stored block of the chunk (that a wanted view reads) into its tile slot
     for (uint32_t it = tid; it < n; it += kLFThreads) {
       const uint32_t e = e_nx, t = t_nx;
@@ -1511,7 +1703,7 @@ __device__ __forceinline__ void rgb_strip(const RGBArgs &a, int wg, uint32_t *sm
         const int e = min(e0 + (lane >> 4), n_list - 1);
         const uint32_t en = masked ? s_list[e] : (uint32_t)e;
         const int qi = (int)(en >> 2), so = (int)(en & 3u);
-        const int vi = s_rec[kRGBRecWords * qi + so], root = s_rec[kRGBRecWords * qi + 4];
+        const int vi = s_rec[kRunWords * qi + so], root = s_rec[kRunWords * qi + 4];
         const bool live = seg_in && e0 + (lane >> 4) < n_list && vi >= 0;
         // the path's nodes: the lane's own leaf, then its ancestors
         int node[NM > 0 ? NM : 1] = {};
@@ -1983,7 +2175,8 @@ lfc_status decode_images(const lfc_lf *lf, int16_t *out, hipStream_t s, int64_t 
   const int64_t key_words = (int64_t)g.n_top * NBLK * (B * B / 2) <= 4096 ? (int64_t)g.n_top * NBLK * (B * B / 2) : 0;
   if ((int64_t)3 * g.hp * g.wp >= ((int64_t)1 << 32))
     return fail(LFC_E_UNSUPPORTED, "lfc_decode_blocks: view too large for the whole-field kernel");
-  const int64_t fixed = kLFHeadWords + (int64_t)lf_tile_words(lf->tile_cap, B * B) + key_words + lfc::kLFTabWords;
+  const int tab_words = lf->lf_tab_words;
+  const int64_t fixed = kLFHeadWords + (int64_t)lf_tile_words(lf->tile_cap, B * B) + key_words + 2 * tab_words;
   const int64_t limit = max_lds_bytes() / 4;
   if (fixed > limit)
     return fail(LFC_E_UNSUPPORTED, "lfc_decode_blocks: tree too large for the whole-field kernel; use BLOCKS layout");
@@ -1991,12 +2184,14 @@ lfc_status decode_images(const lfc_lf *lf, int16_t *out, hipStream_t s, int64_t 
   int64_t cap = std::min<int64_t>(target - fixed, (int64_t)lf->max_strip_words + kStagePad);
   if (stage_cap >= 0) cap = std::min<int64_t>(cap, stage_cap);
   const size_t lds = 4 * (size_t)(fixed + cap);
-  LFArgs a{lf->d_rkv, lf->d_off, lf->d_srv, lf->d_sched, lf->d_strip_off, lf->d_order, lf->d_batch, out,
-           g.nbx, g.nv(), g.L, g.q, g.wp, g.hp, g.nb, lf->n_batch, (int)cap,
+  LFArgs a{lf->d_rkv, lf->d_srv, lf->d_sched, lf->d_order, lf->d_batch, out,
+           g.nbx, g.L, g.q, g.wp, g.hp, g.nb, lf->n_batch, (int)cap,
            (int)(g.wp % 8 == 0 && reinterpret_cast<uintptr_t>(out) % 16 == 0), g.n_top, (int)key_words,
-           lf->tile_cap, (int)((uint64_t)g.nv() * 3 * g.hp * g.wp * 2 > kStreamOutBytes)};
+           lf->tile_cap, tab_words, (int)((uint64_t)g.nv() * 3 * g.hp * g.wp * 2 > kStreamOutBytes)};
   dim3 grid((g.nbx + NBLK - 1) / NBLK, g.nby, 3);
-  hipLaunchKernelGGL(k_decode_lf<B>, grid, dim3(kLFThreads), lds, s, a);
+  auto *kernel = cap > 0 ? (key_words ? k_decode_lf<B, true, true> : k_decode_lf<B, true, false>)
+                         : (key_words ? k_decode_lf<B, false, true> : k_decode_lf<B, false, false>);
+  hipLaunchKernelGGL(kernel, grid, dim3(kLFThreads), lds, s, a);
   return launched("lfc_decode_blocks");
 }
 
