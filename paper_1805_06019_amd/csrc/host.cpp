@@ -458,8 +458,9 @@ static void build_schedule(const Geometry &g, const std::vector<uint32_t> &off, 
 // and its chunks count the stored blocks of the three channels against the
 // tile capacity.  Otherwise as build_schedule:
 //   strip record: [0] chunks, then from word 8 eight words per chunk (the
-//   offset of its tables from the strip's start, q0, nq, nn, n0, n01, n, 0), so
-//   that a workgroup reads a chunk's header in one load;
+//   offset of its tables from the strip's start, q0, nq | key views << 16, nn,
+//   n0, n01, n, first key view), so that a workgroup reads a chunk's header in
+//   one load;
 //   chunk tables: masks[3][nn] (channel-major) and
 //   first slots[3][nn] (B = 2: 16-bit, two per word, after the masks; else, a
 //   strip having at most 16 blocks, in the masks' upper halves), runs[nq][3 words],
@@ -470,7 +471,7 @@ static void build_schedule_rgb(const Geometry &g, const std::vector<uint32_t> &o
                                const std::vector<int32_t> &batch, std::vector<uint32_t> &sched,
                                std::vector<uint32_t> &strip_off, int cap) {
   const int nblk = 64 / g.B, nsx = (g.nbx + nblk - 1) / nblk, nstrip = g.nby * nsx;
-  const int nruns = (int)(batch.size() / kBatchWords), L = g.L;
+  const int nruns = (int)(batch.size() / kBatchWords), L = g.L, key_cap = rgb_key_roots(g.B);
   const size_t ns = (size_t)std::max(g.n_srv, 1);
   std::vector<std::vector<uint32_t>> per((size_t)nstrip);
   parallel_for(nstrip, 8, [&](int64_t a, int64_t e) {
@@ -498,8 +499,10 @@ static void build_schedule_rgb(const Geometry &g, const std::vector<uint32_t> &o
         // greedy: consecutive runs while their nodes' stored blocks fit the tile
         std::vector<int> leaves, ancs;
         int count = 0, k = 0;
+        int r0 = g.n_top, r1 = -1;   // the chunk's key views
         while (q + k < nruns) {
           const int32_t *r = &batch[(size_t)(q + k) * kBatchWords];
+          const int a0 = std::min(r0, (int)r[5]), a1 = std::max(r1, (int)r[5]);
           int add = 0;
           std::vector<int> nl, na;
           for (int i = 0; i < r[0] && L > 1; i++) {
@@ -516,7 +519,7 @@ static void build_schedule_rgb(const Geometry &g, const std::vector<uint32_t> &o
               add += stored(s);
             }
           }
-          if (k > 0 && (count + add > cap || k >= kRGBNodeCap ||
+          if (k > 0 && (count + add > cap || k >= kRGBNodeCap || (g.n_top > key_cap && a1 - a0 >= key_cap) ||
                         leaves.size() + ancs.size() + nl.size() + na.size() > (size_t)kRGBNodeCap))
             break;
           for (int s : nl) {
@@ -529,6 +532,7 @@ static void build_schedule_rgb(const Geometry &g, const std::vector<uint32_t> &o
           }
           count += add;
           k++;
+          r0 = a0, r1 = a1;
         }
         std::vector<int> nodes(leaves);
         nodes.insert(nodes.end(), ancs.begin(), ancs.end());
@@ -563,7 +567,9 @@ static void build_schedule_rgb(const Geometry &g, const std::vector<uint32_t> &o
         const uint32_t n0 = (uint32_t)ent[0].size(), n01 = n0 + (uint32_t)ent[1].size();
         const uint32_t n = n01 + (uint32_t)ent[2].size();
         // (the offset of the chunk's tables is made absolute below)
-        for (uint32_t w : {(uint32_t)body.size(), (uint32_t)q, (uint32_t)k, (uint32_t)nn, n0, n01, n, 0u}) head.push_back(w);
+        for (uint32_t w : {(uint32_t)body.size(), (uint32_t)q, (uint32_t)k | (uint32_t)std::min(r1 - r0 + 1, key_cap) << 16,
+                           (uint32_t)nn, n0, n01, n, (uint32_t)r0})
+          head.push_back(w);
         if (g.B == 2) {
           body.insert(body.end(), masks.begin(), masks.end());
           for (int i = 0; i < 3 * nn; i += 2)
@@ -691,7 +697,7 @@ static void make_strip_tables_rgb(const Geometry &g, const std::vector<uint32_t>
     const uint32_t *rec = &t.sched[t.strip_off[st]];
     t.max_chunks = std::max(t.max_chunks, (int)rec[0]);
     for (uint32_t ci = 0; ci < rec[0]; ci++) {
-      const int nq = (int)rec[8 + 8 * ci + 2], nn = (int)rec[8 + 8 * ci + 3];
+      const int nq = (int)(rec[8 + 8 * ci + 2] & 0xFFFFu), nn = (int)rec[8 + 8 * ci + 3];
       t.tab_cap = std::max(t.tab_cap, (g.B == 2 ? 3 * nn + (3 * nn + 1) / 2 : 3 * nn) + 3 * nq);
       t.run_cap = std::max(t.run_cap, nq);
     }

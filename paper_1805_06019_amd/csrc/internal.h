@@ -66,6 +66,14 @@ constexpr int strip_bit(int B, int j) { return j / (8 / B) + (j % (8 / B)) * 8; 
 // Most tree nodes in one chunk of the colour whole-field kernel's schedule
 // (the kernel copies a chunk's per-node tables into LDS).
 constexpr int kRGBNodeCap = 128;
+// Key views in one chunk, whose rows the kernel holds in LDS (24 KB at most, so
+// that three workgroups share a compute unit; at 8 x 8, where two do, 42 KB).
+constexpr int rgb_key_roots(int B) { return B == 8 ? 13 : (B == 4 ? 16 : 32); }
+// LDS words from one 64-word piece of them to the next, and of a key view: an
+// 8 x 8 block takes one and a half pieces, and without the gaps lanes at
+// neighbouring blocks would reach the same banks.
+constexpr int rgb_key_step(int B) { return B == 8 ? 68 : 64; }
+constexpr int rgb_key_words(int B) { return 3 * B * 32 / 64 * rgb_key_step(B); }
 struct TreeTables {
   std::vector<int32_t> path, root, batch;
   std::vector<std::vector<int32_t>> serial;  // [level][node id] -> BFS index (-1 on top)

@@ -1449,8 +1449,6 @@ constexpr int kRGBFixedWords = 192 + 96 + 4 + kRGBNodeCap / 32;
 __host__ __device__ constexpr int rgb_head_words(int need_words, int tab_cap, int run_cap) {
   return (kRGBFixedWords + need_words + tab_cap + (kRunWords + 2) * run_cap + 3) & ~3;
 }
-constexpr int kRGBKeyWordsMax = 6144;     // key-view rows of a strip staged in LDS up to 24 KB
-
 struct RGBArgs {
   const int16_t *rkv;
   const uint32_t *off;
@@ -1461,7 +1459,7 @@ struct RGBArgs {
   const uint32_t *vneed;      // [ceil(nv/32)] bit per view to write (nv <= 32 kRGBNeedWords), or null: every view
   uint32_t *out;              // [nv][hp][wp] pixels R | G << 8 | B << 16
   int nbx, nsx, L, q, wp, hp, nb, nbatch, nv;
-  int n_top, key_words;       // LDS words of the strip's key-view rows of all channels (0: read from global)
+  int n_top, key_roots;       // key views; those whose rows (all channels) the LDS holds: all, else a chunk's
   int tile_cap;
   int parts;                  // workgroups per strip: part p takes the chunks ci with ci % parts == p
   int need_words, tab_cap, run_cap;   // sizes of the LDS tables: view mask, gather table, runs
@@ -1483,15 +1481,17 @@ struct RGBArgs {
 // rows, sums key row + ancestor rows + leaf row of each channel, converts the
 // pixels to RGB (inverse YCoCg-R, clamped) and stores 16 bytes per row.
 // What bounds it is the issue of vector instructions and, per chunk, the chain
-// header - entry - payload - decode - barrier - gather; hence the packed colour
+// header - entry - window - decode - barrier - gather; hence the packed colour
 // conversion, a gather without branches on the path's length (one body for each
-// depth of the tree), tables that the gather reads from LDS alone, the next
-// chunk's header and first entries read before this chunk's stores (loads wait
-// for older stores), and at most 80 registers and 53 KB, which let three
-// workgroups share a compute unit.  81 views of 625 x 434: 66 -> 44 us (12
-// against 26 million vector instructions), 2.4 TB/s of output and payload; the
-// views that 64 cameras read of 17 x 17 of 512 x 512: 132 -> 97 us.
-template <int B, bool KEYS>
+// depth of the tree), tables and key views that the gather reads from LDS alone,
+// the next chunk's header and first entries read before this chunk's stores
+// (loads wait for older stores), 16-byte planes of the tile against bank
+// conflicts, and at most 80 registers and 53 KB, which let three workgroups share
+// a compute unit (two at 8 x 8).  81 views of 625 x 434: 66 -> 43 us (12 against
+// 26 million vector instructions), 2.5 TB/s of output and payload; the views that
+// 64 cameras read of 17 x 17 of 512 x 512: 132 -> 90 us; 8 x 8 blocks, 80 views
+// of 317 x 521: 92 -> 49 us.
+template <int B>
 __device__ __forceinline__ void rgb_strip(const RGBArgs &a, int wg, uint32_t *smem) {
   constexpr int S = B * B, NBLK = 64 / B, H = B / 2, HR = B;   // HR rows per lane
   const uint16_t *lut = reinterpret_cast<const uint16_t *>(smem);   // 384 x u16 = 192 words
@@ -1503,7 +1503,7 @@ __device__ __forceinline__ void rgb_strip(const RGBArgs &a, int wg, uint32_t *sm
   int32_t *s_rec = reinterpret_cast<int32_t *>(s_mf + a.tab_cap);   // [nq][kRunWords]
   uint16_t *s_list = reinterpret_cast<uint16_t *>(s_rec + kRunWords * a.run_cap);
                                                         // (run << 2 | sibling) pairs of the chunk
-  uint32_t *tile = smem + rgb_head_words(a.need_words, a.tab_cap, a.run_cap);   // [tile_cap + 1][S/2], the last slot zero
+  uint32_t *tile = smem + rgb_head_words(a.need_words, a.tab_cap, a.run_cap);   // residual tile
   uint32_t *keys = tile + lf_tile_words(a.tile_cap, S); // [n_top][NBLK][3][S/2], blocks as in the tile
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1513,11 +1513,11 @@ __device__ __forceinline__ void rgb_strip(const RGBArgs &a, int wg, uint32_t *sm
   const uint32_t *gs = a.sched + (uint32_t)ent[1];
   const uniform_i32 head = as_uniform(reinterpret_cast<const int32_t *>(gs));
   const int nck = head[0];
-  int h_at = 0, q0 = 0, nq = 0, nn = 0;
+  int h_at = 0, q0 = 0, nq = 0, nr = 0, nn = 0, r0 = 0;
   uint32_t n0 = 0, n01 = 0, n = 0;
   auto header = [&](int ci) {
     const uniform_i32 h = head + 8 + 8 * ci;
-    h_at = h[0], q0 = h[1], nq = h[2], nn = h[3];
+    h_at = h[0], q0 = h[1], nq = h[2] & 0xFFFF, nr = h[2] >> 16, nn = h[3], r0 = h[7];
     n0 = (uint32_t)h[4], n01 = (uint32_t)h[5], n = (uint32_t)h[6];
   };
   // a chunk's entries and items follow its masks, first slots and run positions
@@ -1546,7 +1546,10 @@ __device__ __forceinline__ void rgb_strip(const RGBArgs &a, int wg, uint32_t *sm
   if (tid < kLutEntries / 2) __builtin_amdgcn_global_load_lds(
       (const __attribute__((address_space(1))) void *)(kLutTable.w + tid),
       (__attribute__((address_space(3))) void *)(smem + (tid & ~63)), 4, 0, 0);
-  if (tid < S / 2) tile[a.tile_cap * (S / 2) + tid] = 0u;
+  // 16-byte quad k of tile slot s (B = 2: a slot is 8 bytes) at k * plane + 4 s;
+  // the last slot is zero
+  const int plane = 4 * (a.tile_cap + 1);
+  if (tid < S / 2) tile[B == 2 ? a.tile_cap * 2 + tid : (tid / 4) * plane + a.tile_cap * 4 + tid % 4] = 0u;
   if (tid < 64)
     for (int k = lane; k < 3 * NBLK; k += 64) {
       const int c = k / NBLK, bx = sx * NBLK + k % NBLK;
@@ -1568,19 +1571,22 @@ __device__ __forceinline__ void rgb_strip(const RGBArgs &a, int wg, uint32_t *sm
       for (int k = 0; k < 4; k++) atomicOr(&s_need[vs[k] >> 5], 1u << (vs[k] & 31));
     }
   }
-  if constexpr (KEYS) {
-    // a key view's blocks of the strip, of all channels, lie together
+  // key views r0 .. r0 + nr - 1: a key view's blocks of the strip, of all channels, lie together
+  auto stage_keys = [&](int r0, int nr) {
     constexpr int KW = 3 * NBLK * (S / 2);
-    const uint32_t *rk = reinterpret_cast<const uint32_t *>(a.rkv) + (size_t)(by * a.nbx + sx * NBLK) * (3 * S / 2);
+    const uint32_t *rk = reinterpret_cast<const uint32_t *>(a.rkv) +
+                         ((size_t)r0 * a.nb + by * a.nbx + sx * NBLK) * (3 * S / 2);
     const int valid = min(NBLK, a.nbx - sx * NBLK) * (3 * S / 2);
-    for (int f = wave; f < a.n_top * (KW / 64); f += kLFWaves) {
+    for (int f = wave; f < nr * (KW / 64); f += kLFWaves) {
       const int r = f / (KW / 64), w0 = f % (KW / 64) * 64;
       if (w0 + lane < valid)
         __builtin_amdgcn_global_load_lds(
             (const __attribute__((address_space(1))) void *)(rk + (size_t)r * a.nb * (3 * S / 2) + w0 + lane),
-            (__attribute__((address_space(3))) void *)(keys + f * 64), 4, 0, 0);
+            (__attribute__((address_space(3))) void *)(keys + f * lfc::rgb_key_step(B)), 4, 0, 0);
     }
-  }
+  };
+  const bool all_keys = a.n_top <= a.key_roots;
+  if (all_keys) stage_keys(0, a.n_top);
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
 
@@ -1655,9 +1661,13 @@ __device__ __forceinline__ void rgb_strip(const RGBArgs &a, int wg, uint32_t *sm
       if (w0 + lane < kRunWords * nq)
         __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(recs + w0 + lane),
                                          (__attribute__((address_space(3))) void *)(s_rec + w0), 4, 0, 0);
+    if (!all_keys) stage_keys(r0, nr);
     // (3) decode every stored block of the chunk (that a wanted view reads) into its tile slot
     for (uint32_t it = tid; it < n; it += kLFThreads) {
       const uint32_t e = e_nx, t = t_nx;
+      const uint32_t base = s_o0[((t >> 6) & 3u) * NBLK + (t & 63u)];
+      Window<B> w;
+      fetch_window<B>(a.srv + (base + (e >> 10)), w);
       if (it + kLFThreads < n) {
         e_nx = ents[it + kLFThreads];
         t_nx = items[it + kLFThreads];
@@ -1666,22 +1676,21 @@ __device__ __forceinline__ void rgb_strip(const RGBArgs &a, int wg, uint32_t *sm
         const uint32_t ln = (t >> 8) & 4095u;
         if (!((s_node[ln >> 5] >> (ln & 31u)) & 1u)) continue;
       }
-      const uint32_t *gw = a.srv + s_o0[((t >> 6) & 3u) * NBLK + (t & 63u)];
       uint32_t d[S / 2];
-      if (it < n0) decode_block_k<B, 0>(gw, e, a.q, lut, d);
-      else if (it < n01) decode_block_k<B, 1>(gw, e, a.q, lut, d);
-      else decode_block_k<B, 2>(gw, e, a.q, lut, d);
-      uint32_t *dst = tile + (t >> 20) * (S / 2);
-      if constexpr (S / 2 >= 4) {
-#pragma unroll
-        for (int w = 0; w < S / 2; w += 4)
-          *reinterpret_cast<uint4 *>(dst + w) = make_uint4(d[w], d[w + 1], d[w + 2], d[w + 3]);
-      } else {
+      if (it < n0) decode_fetched<B, 0>(w, a.srv, base, e, a.q, lut, d);
+      else if (it < n01) decode_fetched<B, 1>(w, a.srv, base, e, a.q, lut, d);
+      else decode_fetched<B, 2>(w, a.srv, base, e, a.q, lut, d);
+      uint32_t *dst = tile + (t >> 20) * (B == 2 ? 2 : 4);
+      if constexpr (B == 2) {
         *reinterpret_cast<uint2 *>(dst) = make_uint2(d[0], d[1]);
+      } else {
+#pragma unroll
+        for (int q = 0; q < S / 8; q++)
+          *reinterpret_cast<uint4 *>(dst + q * plane) = make_uint4(d[4 * q], d[4 * q + 1], d[4 * q + 2], d[4 * q + 3]);
       }
     }
     // the next chunk's header and first entries, taken before this chunk's stores
-    const int nn_c = nn, nn3 = 3 * nn;
+    const int nn_c = nn, nn3 = 3 * nn, root0 = all_keys ? 0 : r0;
     if (ci + a.parts < nck) {
       header(ci + a.parts);
       request_first();
@@ -1703,7 +1712,7 @@ __device__ __forceinline__ void rgb_strip(const RGBArgs &a, int wg, uint32_t *sm
         const int e = min(e0 + (lane >> 4), n_list - 1);
         const uint32_t en = masked ? s_list[e] : (uint32_t)e;
         const int qi = (int)(en >> 2), so = (int)(en & 3u);
-        const int vi = s_rec[kRunWords * qi + so], root = s_rec[kRunWords * qi + 4];
+        const int vi = s_rec[kRunWords * qi + so], root = s_rec[kRunWords * qi + 4] - root0;
         const bool live = seg_in && e0 + (lane >> 4) < n_list && vi >= 0;
         // the path's nodes: the lane's own leaf, then its ancestors
         int node[NM > 0 ? NM : 1] = {};
@@ -1730,16 +1739,16 @@ __device__ __forceinline__ void rgb_strip(const RGBArgs &a, int wg, uint32_t *sm
 #pragma unroll
             for (int b = 0; b < NS; b++) {
               const uint32_t sl = first + (uint32_t)__popc(w & ((1u << jb[b]) - 1u));
-              slot[c][k][b] = ((w >> jb[b]) & 1u ? sl : zslot) * (S / 2);
+              slot[c][k][b] = ((w >> jb[b]) & 1u ? sl : zslot) * (B == 2 ? 2 : 4);
             }
           }
         uint32_t x[3][HR][2];
-        // the lane's words of a block slot (tile or key rows, same layout):
+        // the lane's words of a block, at the given distance of its 16-byte quads:
         // B = 4, the whole 4 x 4 block in two 16-byte reads; B = 2, both rows
         // of each of its two blocks in one 8-byte read; B = 8, half of each row
-        auto read_slot = [&](const uint32_t *slot0, const uint32_t *slot1, bool add, uint32_t (&xc)[HR][2]) {
+        auto read_slot = [&](const uint32_t *slot0, const uint32_t *slot1, int quads, bool add, uint32_t (&xc)[HR][2]) {
           if constexpr (B == 4) {
-            const uint4 v0 = *reinterpret_cast<const uint4 *>(slot0), v1 = *reinterpret_cast<const uint4 *>(slot0 + 4);
+            const uint4 v0 = *reinterpret_cast<const uint4 *>(slot0), v1 = *reinterpret_cast<const uint4 *>(slot0 + quads);
             const uint32_t w[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
 #pragma unroll
             for (int y = 0; y < 4; y++)
@@ -1755,7 +1764,7 @@ __device__ __forceinline__ void rgb_strip(const RGBArgs &a, int wg, uint32_t *sm
           } else {
 #pragma unroll
             for (int y = 0; y < HR; y++) {
-              const uint2 v = *reinterpret_cast<const uint2 *>(slot0 + y * H + wib[0]);
+              const uint2 v = *reinterpret_cast<const uint2 *>(slot0 + y * quads + wib[0]);
               xc[y][0] = add ? add_pk(xc[y][0], v.x) : v.x;
               xc[y][1] = add ? add_pk(xc[y][1], v.y) : v.y;
             }
@@ -1763,26 +1772,15 @@ __device__ __forceinline__ void rgb_strip(const RGBArgs &a, int wg, uint32_t *sm
         };
 #pragma unroll
         for (int c = 0; c < 3; c++) {
-          if constexpr (KEYS) {
-            const uint32_t *kb = keys + root * (3 * NBLK * (S / 2)) + c * (S / 2);
-            read_slot(kb + jb[0] * (3 * S / 2), kb + jb[1] * (3 * S / 2), false, x[c]);
-          } else {
-#pragma unroll
-            for (int y = 0; y < HR; y++) {
-#pragma unroll
-              for (int w = 0; w < 2; w++) {
-                const int bx = sx * NBLK + jb[w];
-                x[c][y][w] = bx < a.nbx ? reinterpret_cast<const uint32_t *>(
-                                              a.rkv)[((size_t)(root * a.nb + by * a.nbx + bx) * 3 + c) * (S / 2) + y * H +
-                                                     wib[w]]
-                                        : 0u;
-              }
-            }
+          {
+            const uint32_t *kb = keys + root * lfc::rgb_key_words(B);
+            const int k0 = jb[0] * (3 * S / 2) + c * (S / 2), k1 = jb[1] * (3 * S / 2) + c * (S / 2);
+            read_slot(kb + k0 + k0 / 64 * (lfc::rgb_key_step(B) - 64), kb + k1, 4, false, x[c]);
           }
 #pragma unroll
           for (int k = 0; k < NM; k++) {
             if (NC < 0 && k >= nodes) continue;
-            read_slot(tile + slot[c][k][0], tile + slot[c][k][NS - 1], true, x[c]);
+            read_slot(tile + slot[c][k][0], tile + slot[c][k][NS - 1], plane, true, x[c]);
           }
         }
         if (!live) continue;
@@ -1812,26 +1810,26 @@ __device__ __forceinline__ void rgb_strip(const RGBArgs &a, int wg, uint32_t *sm
   }
 }
 
-// (B <= 4: at most 80 VGPRs, so that three workgroups share a compute unit)
-template <int B, bool KEYS>
-__global__ __launch_bounds__(kLFThreads, B <= 4 ? 6 : 1) void k_decode_rgb(RGBArgs a) {
+template <int B>
+__global__ __launch_bounds__(kLFThreads, B <= 4 ? 6 : 4) void k_decode_rgb(RGBArgs a) {
   extern __shared__ uint32_t smem[];
-  rgb_strip<B, KEYS>(a, (int)blockIdx.x, smem);
+  rgb_strip<B>(a, (int)blockIdx.x, smem);
 }
 
 // The colour decode of several light fields in one launch: the workgroups are
 // every light field's (strip, part) pairs, each light field's strips costliest
 // first.  (Workgroups that stayed resident and took items from a device counter
-// needed 20 registers more, which kept a third of them off the chip: 99 us
-// against 57 for the 4 x 4 fields of a mixed batch, 23 against 18 for its 8 x 8.)
+// needed 20 registers more, which kept a third of them off the chip: the 4 x 4
+// fields of a mixed batch 99 -> 55 us, its 8 x 8 field 23 -> 14 us, with the
+// changes above.)
 struct RGBMultiArgs {
   const RGBArgs *lfs;      // [n_lf], every one of block size B
   const int32_t *first;    // [n_lf + 1] first work item of each light field (items = strips x parts)
   int n_lf;
 };
 
-template <int B, bool KEYS>
-__global__ __launch_bounds__(kLFThreads, B <= 4 ? 6 : 1) void k_decode_rgb_multi(RGBMultiArgs m) {
+template <int B>
+__global__ __launch_bounds__(kLFThreads, B <= 4 ? 6 : 4) void k_decode_rgb_multi(RGBMultiArgs m) {
   extern __shared__ uint32_t smem[];
   const uniform_i32 first = as_uniform(m.first);
   const int item = blockIdx.x;
@@ -1839,7 +1837,7 @@ __global__ __launch_bounds__(kLFThreads, B <= 4 ? 6 : 1) void k_decode_rgb_multi
   while (lf + 1 < m.n_lf && first[lf + 1] <= item) lf++;
   const RGBArgs a = m.lfs[lf];
   const int local = item - first[lf];
-  rgb_strip<B, KEYS>(a, local, smem);
+  rgb_strip<B>(a, local, smem);
 }
 
 // Novel views from fully decoded 8-bit RGB source views ([nv][hp][wp]): one
@@ -2195,6 +2193,12 @@ lfc_status decode_images(const lfc_lf *lf, int16_t *out, hipStream_t s, int64_t 
   return launched("lfc_decode_blocks");
 }
 
+// Key views whose rows a workgroup of the colour decode holds in LDS: all, or
+// those of one chunk (read from global memory in the gather, they would wait for
+// the wave's stores: 289 views of 256 x 256 in two levels 108 -> 31 us, 64 key
+// views of 128 x 128 95 -> 9 us).
+int rgb_key_views(const lfc_lf *lf) { return std::min(lf->geo.n_top, lfc::rgb_key_roots(lf->geo.B)); }
+
 // Every view (or those whose bit is set in vneed) as 8-bit RGB words
 // [nv][hp][wp], inverse YCoCg-R and clamp applied to the decoded samples.
 template <int B>
@@ -2204,13 +2208,12 @@ lfc_status decode_rgb(const lfc_lf *lf, uint32_t *out, const uint32_t *vneed, hi
   constexpr int NBLK = 64 / B;
   if ((uint64_t)g.nv() * g.hp * g.wp >= ((uint64_t)1 << 32))
     return fail(LFC_E_UNSUPPORTED, std::string(who) + ": light field too large for 32-bit pixel indices");
-  const int64_t kw = (int64_t)3 * g.n_top * B * 32;
-  const int key_words = kw <= kRGBKeyWordsMax ? (int)kw : 0;
+  const int key_views = rgb_key_views(lf);
   // a view mask longer than the kernel's LDS copy of it: every view is decoded
   if (g.nv() > 32 * kRGBNeedWords) vneed = nullptr, views = nullptr;
   const int need_words = vneed || (views && nviews > 0) ? (g.nv() + 31) / 32 : 0;
   const size_t lds = 4 * ((size_t)rgb_head_words(need_words, lf->rgb_tab_cap, lf->rgb_run_cap) +
-                          (size_t)lf_tile_words(lf->tile_cap_rgb, B * B) + (size_t)key_words);
+                          (size_t)lf_tile_words(lf->tile_cap_rgb, B * B) + (size_t)key_views * lfc::rgb_key_words(B));
   if (lds > (size_t)max_lds_bytes())
     return fail(LFC_E_UNSUPPORTED, std::string(who) + ": tree too large for the colour whole-field kernel");
   const int nsx = (g.nbx + NBLK - 1) / NBLK, nstrips = g.nby * nsx;
@@ -2218,7 +2221,7 @@ lfc_status decode_rgb(const lfc_lf *lf, uint32_t *out, const uint32_t *vneed, hi
   // workgroups (about three per compute unit), at most the strips' chunk count
   int parts = std::max(1, std::min(lf->rgb_max_chunks, (3 * 3 * device_cus() + nstrips - 1) / nstrips));
   RGBArgs a{lf->d_rkv, lf->d_off, lf->d_srv, lf->d_sched_rgb, lf->d_order_rgb, lf->d_batch,
-            vneed, out, g.nbx, nsx, g.L, g.q, g.wp, g.hp, g.nb, lf->n_batch, g.nv(), g.n_top, key_words,
+            vneed, out, g.nbx, nsx, g.L, g.q, g.wp, g.hp, g.nb, lf->n_batch, g.nv(), g.n_top, key_views,
             lf->tile_cap_rgb, parts, need_words, lf->rgb_tab_cap, lf->rgb_run_cap};
   if (!vneed && views && nviews > 0) {
     a.views = views;
@@ -2227,10 +2230,7 @@ lfc_status decode_rgb(const lfc_lf *lf, uint32_t *out, const uint32_t *vneed, hi
     a.V = g.V;
   }
   const dim3 grid((unsigned)(nstrips * parts));
-  if (key_words)
-    hipLaunchKernelGGL((k_decode_rgb<B, true>), grid, dim3(kLFThreads), lds, s, a);
-  else
-    hipLaunchKernelGGL((k_decode_rgb<B, false>), grid, dim3(kLFThreads), lds, s, a);
+  hipLaunchKernelGGL(k_decode_rgb<B>, grid, dim3(kLFThreads), lds, s, a);
   return launched(who);
 }
 
@@ -2757,13 +2757,6 @@ lfc_status render_req_fill(const lfc_lf *lf, const lfc_view &v, int wo, int ho, 
 
 namespace {
 
-// LDS words of the key-view rows of a colour strip, or 0 when they exceed the
-// kernel's staging budget (then read from global memory)
-int rgb_key_words(const lfc::Geometry &g) {
-  const int64_t kw = (int64_t)3 * g.n_top * g.B * 32;
-  return kw <= kRGBKeyWordsMax ? (int)kw : 0;
-}
-
 int rgb_parts(const lfc_lf *lf) {
   const lfc::Geometry &g = lf->geo;
   const int nblk = 64 / g.B, nstrips = g.nby * ((g.nbx + nblk - 1) / nblk);
@@ -2775,7 +2768,7 @@ int rgb_parts(const lfc_lf *lf) {
 bool lf_rgb_batchable(const lfc_lf *lf, double out_pixels) {
   const Geometry &g = lf->geo;
   const size_t lds = 4 * ((size_t)rgb_head_words((g.nv() + 31) / 32, lf->rgb_tab_cap, lf->rgb_run_cap) +
-                          (size_t)lf_tile_words(lf->tile_cap_rgb, g.B * g.B) + (size_t)rgb_key_words(g));
+                          (size_t)lf_tile_words(lf->tile_cap_rgb, g.B * g.B) + (size_t)rgb_key_views(lf) * lfc::rgb_key_words(g.B));
   return (uint64_t)g.nv() * g.hp * g.wp * 4 < ((uint64_t)1 << 32) && g.nv() <= 32 * kRGBNeedWords &&
          lds <= (size_t)max_lds_bytes() && 20.0 * out_pixels >= (double)g.nv() * g.hp * g.wp;
 }
@@ -2792,23 +2785,21 @@ int lf_views(const lfc_lf *lf) { return lf->geo.nv(); }
 
 size_t rgb_args_bytes() { return sizeof(RGBArgs); }
 
-void rgb_args_fill(const lfc_lf *lf, bool keys, uint32_t *d_rgb, const uint32_t *d_mask, void *dst) {
+void rgb_args_fill(const lfc_lf *lf, uint32_t *d_rgb, const uint32_t *d_mask, void *dst) {
   const Geometry &g = lf->geo;
   const int nblk = 64 / g.B;
   RGBArgs a{lf->d_rkv, lf->d_off, lf->d_srv, lf->d_sched_rgb, lf->d_order_rgb, lf->d_batch,
             d_mask, d_rgb, g.nbx, (g.nbx + nblk - 1) / nblk, g.L, g.q, g.wp, g.hp, g.nb, lf->n_batch, g.nv(),
-            g.n_top, keys ? rgb_key_words(g) : 0, lf->tile_cap_rgb, rgb_parts(lf), (g.nv() + 31) / 32, lf->rgb_tab_cap,
+            g.n_top, rgb_key_views(lf), lf->tile_cap_rgb, rgb_parts(lf), (g.nv() + 31) / 32, lf->rgb_tab_cap,
             lf->rgb_run_cap};
   std::memcpy(dst, &a, sizeof a);
 }
 
-size_t rgb_lds_bytes(const lfc_lf *lf, bool keys) {
+size_t rgb_lds_bytes(const lfc_lf *lf) {
   const Geometry &g = lf->geo;
   return 4 * ((size_t)rgb_head_words((g.nv() + 31) / 32, lf->rgb_tab_cap, lf->rgb_run_cap) +
-              (size_t)lf_tile_words(lf->tile_cap_rgb, g.B * g.B) + (size_t)(keys ? rgb_key_words(g) : 0));
+              (size_t)lf_tile_words(lf->tile_cap_rgb, g.B * g.B) + (size_t)rgb_key_views(lf) * lfc::rgb_key_words(g.B));
 }
-
-bool rgb_keys_fit(const lfc_lf *lf) { return rgb_key_words(lf->geo) > 0; }
 
 void need_mask_host(const lfc_lf *lf, const lfc_view &v, uint32_t *mask) {
   const Geometry &g = lf->geo;
@@ -2843,7 +2834,7 @@ void interp_req_fill(const lfc_lf *lf, const uint32_t *d_rgb, const lfc_view &v,
   std::memcpy(dst, &r, sizeof r);
 }
 
-lfc_status rgb_multi_launch(int block, bool keys, const void *d_args, const int32_t *d_first, int n_lf, int n_items,
+lfc_status rgb_multi_launch(int block, const void *d_args, const int32_t *d_first, int n_lf, int n_items,
                             size_t lds, hipStream_t s) {
   if (n_items <= 0) return LFC_OK;
   RGBMultiArgs m{static_cast<const RGBArgs *>(d_args), d_first, n_lf};
@@ -2851,13 +2842,10 @@ lfc_status rgb_multi_launch(int block, bool keys, const void *d_args, const int3
     hipLaunchKernelGGL(kern, dim3((unsigned)n_items), dim3(kLFThreads), lds, s, m);
     return launched("lfc_batch_render");
   };
-  switch (block * 2 + (keys ? 1 : 0)) {
-    case 5: return launch(k_decode_rgb_multi<2, true>);
-    case 4: return launch(k_decode_rgb_multi<2, false>);
-    case 9: return launch(k_decode_rgb_multi<4, true>);
-    case 8: return launch(k_decode_rgb_multi<4, false>);
-    case 17: return launch(k_decode_rgb_multi<8, true>);
-    default: return launch(k_decode_rgb_multi<8, false>);
+  switch (block) {
+    case 2: return launch(k_decode_rgb_multi<2>);
+    case 4: return launch(k_decode_rgb_multi<4>);
+    default: return launch(k_decode_rgb_multi<8>);
   }
 }
 

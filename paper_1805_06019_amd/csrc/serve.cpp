@@ -185,7 +185,6 @@ struct BatchLayout {
     size_t lds = 0;
     size_t at_tiles = 0;
     std::vector<int> lf;            // colour-decoded light fields of this block size
-    bool keys = true;
     size_t rgb_lds = 0;
     int items = 0;
     size_t at_args = 0, at_first = 0;
@@ -276,8 +275,7 @@ lfc_status plan_batch(lfc_batch *b, const lfc_lf *const *lfs, int32_t n_lf, cons
   for (int block : {2, 4, 8}) {
     BatchLayout::Group &gp = L.grp[block];
     if (gp.lf.empty()) continue;
-    for (int l : gp.lf) gp.keys = gp.keys && lfc::rgb_keys_fit(lfs[l]);
-    for (int l : gp.lf) gp.rgb_lds = std::max(gp.rgb_lds, lfc::rgb_lds_bytes(lfs[l], gp.keys));
+    for (int l : gp.lf) gp.rgb_lds = std::max(gp.rgb_lds, lfc::rgb_lds_bytes(lfs[l]));
     for (int l : gp.lf) gp.items += lfc::lf_rgb_items(lfs[l]);
     gp.at_args = at;
     at = align16(at + gp.lf.size() * ab);
@@ -308,7 +306,7 @@ void fill_batch(const BatchLayout &L, const lfc_lf *const *lfs, int32_t n_lf, co
     int items = 0;
     for (size_t k = 0; k < gp.lf.size(); k++) {
       const int l = gp.lf[k];
-      lfc::rgb_args_fill(lfs[l], gp.keys, static_cast<uint32_t *>(L.scr[(size_t)l]->buf),
+      lfc::rgb_args_fill(lfs[l], static_cast<uint32_t *>(L.scr[(size_t)l]->buf),
                          reinterpret_cast<const uint32_t *>(dev + L.at_mask[(size_t)l]), host + gp.at_args + k * ab);
       first[k] = items;
       items += lfc::lf_rgb_items(lfs[l]);
@@ -341,7 +339,7 @@ lfc_status launch_batch(const BatchLayout &L, const char *dev, hipStream_t s) {
   for (int block : {2, 4, 8}) {
     const BatchLayout::Group &gp = L.grp[block];
     if (gp.lf.empty() || st != LFC_OK) continue;
-    st = lfc::rgb_multi_launch(block, gp.keys, dev + gp.at_args, reinterpret_cast<const int32_t *>(dev + gp.at_first),
+    st = lfc::rgb_multi_launch(block, dev + gp.at_args, reinterpret_cast<const int32_t *>(dev + gp.at_first),
                                (int)gp.lf.size(), gp.items, gp.rgb_lds, s);
   }
   if (st == LFC_OK && L.n_interp) st = lfc::interp_multi_launch(dev + L.at_interp, L.n_interp, L.max_wo, L.max_ho, s);

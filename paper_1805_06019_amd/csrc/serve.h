@@ -57,14 +57,13 @@ size_t lf_rgb_bytes(const lfc_lf *lf);
 int lf_rgb_items(const lfc_lf *lf);
 int lf_views(const lfc_lf *lf);
 size_t rgb_args_bytes();
-void rgb_args_fill(const lfc_lf *lf, bool keys, uint32_t *d_rgb, const uint32_t *d_mask, void *dst);
-size_t rgb_lds_bytes(const lfc_lf *lf, bool keys);
-bool rgb_keys_fit(const lfc_lf *lf);
+void rgb_args_fill(const lfc_lf *lf, uint32_t *d_rgb, const uint32_t *d_mask, void *dst);
+size_t rgb_lds_bytes(const lfc_lf *lf);
 void need_mask_host(const lfc_lf *lf, const lfc_view &v, uint32_t *mask);
 size_t interp_req_bytes();
 void interp_req_fill(const lfc_lf *lf, const uint32_t *d_rgb, const lfc_view &v, int wo, int ho, float *out,
                      uint64_t call_bytes, void *dst);   // call_bytes: decoded views and outputs of the whole call
-lfc_status rgb_multi_launch(int block, bool keys, const void *d_args, const int32_t *d_first, int n_lf, int n_items,
+lfc_status rgb_multi_launch(int block, const void *d_args, const int32_t *d_first, int n_lf, int n_items,
                             size_t lds, hipStream_t s);
 lfc_status interp_multi_launch(const void *d_reqs, int n, int max_wo, int max_ho, hipStream_t s);
 
