@@ -58,9 +58,10 @@ def kernel_source_hash() -> str:
 
 
 def short_name(name: str) -> str:
-    """A kernel's name with its template arguments (k_decode_lf<4>,
-    k_decode_rgb<4, true>, k_interp_rgb<false>), else the first 60 characters."""
-    m = re.search(r"(k_\w+)ILi(\d)E", name)
+    """A kernel's name with its template arguments (k_decode_rgb<4>,
+    k_interp_rgb<false, 4>; the whole-field kernel's forms all as k_decode_lf<4>),
+    else the first 60 characters."""
+    m = re.search(r"(k_\w+)ILi(\d)E", name) or re.search(r"(k_decode_lf)<(\d)", name)
     if m:
         return f"{m.group(1)}<{m.group(2)}>"
     m = re.search(r"(k_\w+)(<[^()]*>)?", name)
