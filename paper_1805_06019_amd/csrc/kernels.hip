@@ -76,7 +76,6 @@ constexpr uint32_t lut_value(int t) {
   }
   return v;
 }
-__device__ __forceinline__ uint16_t lut_entry(int t) { return (uint16_t)lut_value(t); }
 
 // The LUT, two entries per word, as a table in device memory (the
 // whole-field kernel copies it into LDS instead of computing it).
@@ -325,7 +324,8 @@ struct LFArgs {
 };
 
 // A whole block of a known kind (0 plain bits, 1 trit, 2 quint) decoded by one
-// lane: d holds the B*B residuals as packed int16 pairs, row-major.  With the
+// lane, row by row from memory (8 x 8 blocks, and plain ones too wide for a
+// window): d holds the B*B residuals as packed int16 pairs, row-major.  With the
 // kind and the row fixed at compile time, every field position except the
 // m-dependent low-bit offsets is a constant.
 template <int B, int KIND>
@@ -339,40 +339,6 @@ __device__ __forceinline__ void decode_block_k(const uint32_t *gw, uint32_t e, i
   const uint32_t code = e & 31u, rel = e >> 5;
   const uint32_t m = KIND == 0 ? code + 1u : (KIND == 1 ? code - 12u : code - 19u);
   const uint32_t lmask = (1u << m) - 1u;
-  if constexpr (B <= 4 && KIND != 0) {
-    // Trits and quints at B <= 4: a row's low bits (B*m <= 24) lie in one
-    // 32-bit window of two words, and the digit plane (at most 38 bits) is
-    // read once, in two or three words, and expanded field by field: every
-    // field is looked up once instead of once per row that shares it.
-    constexpr uint32_t DPG = KIND == 1 ? 5u : 3u;   // digits per field
-    constexpr int NG = (int)((S + DPG - 1) / DPG);
-    using AllDigits = std::conditional_t<(KIND == 2 && S > 10), uint64_t, uint32_t>;
-    const uint32_t *qd = gw + (rel >> 5);
-    const uint32_t sh = rel & 31u;
-    uint64_t plane = __builtin_amdgcn_alignbit(qd[1], qd[0], sh);
-    if constexpr (HDR > 32) plane |= (uint64_t)__builtin_amdgcn_alignbit(qd[2], qd[1], sh) << 32;
-    AllDigits D = 0;
-#pragma unroll
-    for (int g = 0; g < NG; g++) {
-      const uint32_t off = (uint32_t)g * FW;
-      const uint32_t wdt = HDR - off < FW ? HDR - off : FW;
-      D |= (AllDigits)lut[LB + ((uint32_t)(plane >> off) & ((1u << wdt) - 1u))] << (g * GB);
-    }
-#pragma unroll
-    for (int y = 0; y < B; y++) {
-      const uint32_t p = rel + HDR + (uint32_t)(y * B) * m;
-      const uint32_t *qr = gw + (p >> 5);
-      const uint32_t lo = __builtin_amdgcn_alignbit(qr[1], qr[0], p & 31u);
-      uint32_t u[B];
-#pragma unroll
-      for (int k = 0; k < B; k++)
-        u[k] = __builtin_amdgcn_ubfe(lo, (uint32_t)k * m, m) |
-               ((((uint32_t)(D >> ((y * B + k) * DB))) & DMASK) << m);
-#pragma unroll
-      for (int i = 0; i < B / 2; i++) d[y * (B / 2) + i] = unzigzag_pk(u[2 * i] | (u[2 * i + 1] << 16), q);
-    }
-    return;
-  }
 #pragma unroll
   for (int y = 0; y < B; y++) {
     uint32_t u[B];
@@ -570,10 +536,10 @@ __device__ __forceinline__ void decode_fetched(const Window<B> &s, const uint32_
       return;
     }
   }
-  decode_block_k<B, KIND>(words + base, e, q, lut, d);
+  if constexpr (B == 8 || KIND == 0) decode_block_k<B, KIND>(words + base, e, q, lut, d);
 }
 
-// A whole block of any kind decoded by one lane, with the generic row
+// A whole 8 x 8 block of any kind decoded by one lane, with the generic row
 // decoder (one code for the three kinds, the row plans constant).
 template <int B>
 __device__ __forceinline__ void decode_block(const uint32_t *gw, uint32_t e, int q, const uint16_t *lut,
@@ -949,7 +915,8 @@ __global__ __launch_bounds__(kLFThreads, B <= 4 ? 6 : 1) void k_decode_lf(LFArgs
       // stores)
 #pragma unroll
       for (int k = 0; k < 2; k++) {
-        if (wave * 64 + k * kLFThreads < n) decode_to_tile(min((uint32_t)tid + k * kLFThreads, n - 1), w[k], a.srv, s_o0[t[k] & 31u], e[k], t[k]);
+        if ((uint32_t)(wave * 64 + k * kLFThreads) < n)
+          decode_to_tile(min((uint32_t)(tid + k * kLFThreads), n - 1), w[k], a.srv, s_o0[t[k] & 31u], e[k], t[k]);
         e[k] = f[k], t[k] = u[k];
         if (hn.n) fetch(e[k], t[k], w[k]);
       }
@@ -1125,7 +1092,7 @@ __device__ __forceinline__ void load_lut(uint32_t *lut) {
 }
 
 // Request r = (vi, b) by its lanes, of which this one is sub: the block, or zeros
-// and the error flag if the request is out of range; out16: out is aligned to 16
+// and the error flag if the request is out of range; wide: out is aligned to 16
 // bytes (8 at B = 2).
 template <int B>
 __device__ __forceinline__ void serve_request(const RAArgs &ra, bool valid, int vi, int b, int64_t r, int sub, int stop,
@@ -1722,7 +1689,7 @@ struct RGBArgs {
 // of 317 x 521: 92 -> 49 us.
 template <int B>
 __device__ __forceinline__ void rgb_strip(const RGBArgs &a, int wg, uint32_t *smem) {
-  constexpr int S = B * B, NBLK = 64 / B, H = B / 2, HR = B;   // HR rows per lane
+  constexpr int S = B * B, NBLK = 64 / B, HR = B;   // HR rows per lane
   const uint16_t *lut = reinterpret_cast<const uint16_t *>(smem);   // 384 x u16 = 192 words
   uint32_t *s_o0 = smem + 192;                          // [3][NBLK] group start words
   uint32_t *s_nlist = smem + 288;                       // [0] listed pairs of the chunk
