@@ -2209,10 +2209,18 @@ struct InterpGrid {
     view = j % per / pieces;
   }
   // (a grid dimension holds fewer than 2^32 threads; bands past the last exit)
+  static constexpr uint32_t kRow = 1u << 23;   // most workgroups in a row of the grid
   dim3 grid(int bands) const {
     const uint64_t blocks = (uint64_t)8 * ((bands + 7) / 8) * pieces * n;
-    const uint32_t x = (uint32_t)std::min<uint64_t>(blocks, 1u << 23);
+    const uint32_t x = (uint32_t)std::min<uint64_t>(blocks, kRow);
     return dim3(x, (uint32_t)((blocks + x - 1) / x));
+  }
+  // Most views of one launch: its workgroups' numbers fit 32 bits, the last
+  // row's padding included.  (Views of one size never come near, 2^32
+  // workgroups of them would not fit the memory; a batch's grid is that of its
+  // largest output for every request.)
+  static int most_views(int bands, int pieces) {
+    return (int)((((uint64_t)1 << 32) - kRow) / ((uint64_t)8 * ((bands + 7) / 8) * pieces));
   }
 };
 
@@ -3088,10 +3096,15 @@ lfc_status rgb_multi_launch(int block, const void *d_args, const int32_t *d_firs
 lfc_status interp_multi_launch(const void *d_reqs, int n, int max_wo, int max_ho, hipStream_t s) {
   if (n <= 0) return LFC_OK;
   if (n > 65535) return fail(LFC_E_INVALID, "lfc_batch_render: at most 65535 interpolated requests per batch");
-  const InterpGrid gr{(max_wo + kThreads - 1) / kThreads, n};
-  hipLaunchKernelGGL(k_interp_multi, gr.grid((max_ho + kInterpRows - 1) / kInterpRows), dim3(kThreads), 0, s,
-                     static_cast<const InterpReq *>(d_reqs), gr);
-  return launched("lfc_batch_render");
+  const int pieces = (max_wo + kThreads - 1) / kThreads, bands = (max_ho + kInterpRows - 1) / kInterpRows;
+  const int most = InterpGrid::most_views(bands, pieces);   // (16,352 or more)
+  lfc_status st = LFC_OK;
+  for (int at = 0; at < n && st == LFC_OK; at += most) {
+    const InterpGrid gr{pieces, std::min(most, n - at)};
+    hipLaunchKernelGGL(k_interp_multi, gr.grid(bands), dim3(kThreads), 0, s, static_cast<const InterpReq *>(d_reqs) + at, gr);
+    st = launched("lfc_batch_render");
+  }
+  return st;
 }
 
 lfc_status render_multi_launch(int block, const void *d_reqs, int n, int max_tiles, size_t lds, hipStream_t s) {

@@ -1,0 +1,115 @@
+"""The library's host side at sizes and on paths that need no GPU: what it
+launches, how it sizes LDS and what it waits for, seen by a HIP runtime that
+runs nothing (stand_in_hip.c).  Each case runs in a process of its own, which
+loads that runtime before the library.
+"""
+import ctypes as C
+import os
+import shutil
+import subprocess
+import sys
+
+import numpy as np
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+sys.path.insert(0, os.path.dirname(HERE))
+from paper_1805_06019_amd import lfc  # noqa: E402
+
+MIB = 1 << 20
+DEVICE = 1 << 44    # an address of the stand-in's device memory
+CASES = {}
+
+
+def case(f):
+    CASES[f.__name__] = f
+    return f
+
+
+@pytest.fixture(scope="session")
+def stand_in(tmp_path_factory):
+    if not shutil.which("gcc") or not os.path.exists("/opt/rocm/include/hip/hip_runtime_api.h"):
+        pytest.skip("needs gcc and the HIP headers")
+    so = str(tmp_path_factory.mktemp("hip") / "stand_in_hip.so")
+    subprocess.run(["gcc", "-std=c11", "-O1", "-shared", "-fPIC", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
+                    os.path.join(HERE, "stand_in_hip.c"), "-o", so], check=True, timeout=120)
+    return so
+
+
+class Watch:
+    """The launches (kernel, grid, threads, LDS bytes, reader of the arguments) and events the stand-in saw."""
+
+    def __init__(self, so):
+        self.launches, self.events, self.fail = [], [], None
+        hip = C.CDLL(so, C.RTLD_GLOBAL)
+        launch_t = C.CFUNCTYPE(C.c_int, C.c_char_p, C.POINTER(C.c_uint32), C.c_uint32, C.c_size_t, C.POINTER(C.c_void_p))
+        event_t = C.CFUNCTYPE(None, C.c_char_p, C.c_void_p, C.c_size_t)
+        self.keep = launch_t(self.on_launch), event_t(self.on_event)
+        hip.stand_in_watch(*self.keep)
+
+    def on_launch(self, name, grid, threads, lds, args):
+        g = tuple(grid[i] for i in range(3))
+        words = C.cast(args[1], C.POINTER(C.c_int32)) if b"interp" in name else None
+        self.launches.append((name.decode(), g, threads, lds, (C.cast(args[0], C.POINTER(C.c_uint64))[0], words[0], words[1])
+                              if words else None))
+        self.events.append(("launch", name.decode(), 0))
+        return 1 if self.fail and self.fail in name.decode() else 0
+
+    def on_event(self, what, src, n):
+        self.events.append((what.decode(), src, n))
+
+
+def opened(U, V, W, H, block, levels, tile=0, threshold=1 << 20, seed=1):
+    """An opened light field; the default threshold leaves it no residuals."""
+    rgb = np.random.default_rng(seed).integers(0, 256, (V, U, H, W, 3), dtype=np.uint8)
+    p = lfc.Params(U, V, W, H, block, levels, (2,) * (levels - 1), blk_threshold=threshold)
+    s = np.frombuffer(lfc.lfc_encode(rgb, p), np.uint8)
+    h = C.c_void_p()
+    lfc._check(lfc.load().lfc_open_ex(s.ctypes.data, s.size, C.byref(lfc.c_open_config(tile)), None, C.byref(h)))
+    return h
+
+
+# ---------------------------------------------------------------------------
+
+@case
+def batch_of_many_requests_and_one_large(w):
+    """Every band of output rows, piece of a row and request of a batch has a
+    workgroup, whose number the kernel forms in 32 bits."""
+    lib, lf = lfc.load(), opened(3, 3, 24, 16, 4, 2)
+    b = C.c_void_p()
+    lfc._check(lib.lfc_batch_create(C.byref(b)))
+    for n, big_w, big_h in ((20000, 16384, 16384), (65535, 16384, 16384), (65535, 4097, 16381), (16384, 16384, 16384),
+                            (16383, 16384, 16384), (70, 300, 200)):
+        reqs = lfc._requests([(0, big_w if i == 7 else 1 + i % 5, big_h if i == 7 else 1 + i % 3, (1.0, 1.0, 0.0, 0.0))
+                              for i in range(n)])
+        outs = (C.c_void_p * n)(*([DEVICE] * n))
+        w.launches.clear()
+        lfc._check(lib.lfc_batch_render(b, (C.c_void_p * 1)(lf), 1, reqs, n, outs, None))
+        interp = [x for x in w.launches if "interp" in x[0]]
+        assert interp
+        pieces, bands, served = -(-big_w // 256), -(-big_h // 4), 0
+        at, record = interp[0][4][0], 0
+        if len(interp) > 1:
+            record = (interp[1][4][0] - at) // interp[0][4][2]
+        for _, g, threads, _, (first, gp, gn) in interp:
+            blocks = g[0] * g[1] * g[2]
+            assert threads == 256 and gp == pieces and g[0] * threads < 1 << 32 and g[1] <= 65535 and g[2] == 1
+            assert blocks <= 1 << 32, (n, big_w, big_h, g)   # the numbers 0 .. blocks - 1 fit
+            assert blocks >= 8 * -(-bands // 8) * pieces * gn
+            assert first == at + served * record
+            served += gn
+        assert served == n
+    print("done")
+
+
+# ---------------------------------------------------------------------------
+
+@pytest.mark.parametrize("name", CASES)
+def test_host_side(stand_in, name):
+    r = subprocess.run([sys.executable, __file__, name, stand_in], stdout=subprocess.PIPE, stderr=subprocess.STDOUT,
+                       text=True, timeout=300)
+    assert r.returncode == 0 and r.stdout.endswith("done\n"), r.stdout[-4000:]
+
+
+if __name__ == "__main__":
+    CASES[sys.argv[1]](Watch(sys.argv[2]))
