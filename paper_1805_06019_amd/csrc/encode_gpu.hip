@@ -534,6 +534,17 @@ struct Scratch {
   }
 };
 
+// Waits for the stream at the end of its scope: declared after host memory that a
+// copy on it reads, so that a return before the call's own wait does not free
+// that memory under the copy.
+struct WaitOnReturn {
+  hipStream_t s;
+  bool pending = true;
+  ~WaitOnReturn() {
+    if (pending) (void)hipStreamSynchronize(s);
+  }
+};
+
 // Parts of one allocation, 256-byte aligned.
 struct Parts {
   size_t bytes = 0;
@@ -628,6 +639,7 @@ lfc_status encode_gpu(const uint8_t *d_rgb, const lfc_params *p, void **stream_o
       serial[l] = reinterpret_cast<const int32_t *>(base + p_host + at);
     }
   }
+  WaitOnReturn tables{s};
   if (hipMemcpyAsync(base + p_host, host.data(), host.size(), hipMemcpyHostToDevice, s) != hipSuccess)
     return fail(LFC_E_HIP, "lfc_encode_gpu: copy of the tables");
   const RangeTab *d_rt = reinterpret_cast<const RangeTab *>(base + p_host);
@@ -693,6 +705,7 @@ lfc_status encode_gpu(const uint8_t *d_rgb, const lfc_params *p, void **stream_o
   if (hipMemcpyAsync(hs.data(), small, 8 * n_small, hipMemcpyDeviceToHost, s) != hipSuccess ||
       hipStreamSynchronize(s) != hipSuccess)
     return fail(LFC_E_HIP, "lfc_encode_gpu: synchronize");
+  tables.pending = false;
   const int32_t herr = (int32_t)hs[at_err];
   if (herr & 1) return fail(LFC_E_RANGE, "lfc_encode_gpu: a residual block needs a BISE range the mask does not allow");
   if (herr & 2) return fail(LFC_E_RANGE, "lfc_encode_gpu: a reconstructed sample leaves int16");

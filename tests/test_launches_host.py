@@ -102,6 +102,21 @@ def batch_of_many_requests_and_one_large(w):
     print("done")
 
 
+@case
+def gpu_encoder_fails_while_its_tables_are_copied(w):
+    """A failed launch returns only after the copy of the host's tables, which the call frees, has been waited for."""
+    p = lfc.Params(5, 4, 40, 24, 4, 3, (2, 2)).to_c()
+    for kernel in ("k_enc_level0", "k_enc_filter", "k_enc_residual", "k_enc_group_words", "k_enc_offsets"):
+        w.fail = kernel
+        w.events.clear()
+        out, n = C.c_void_p(), C.c_size_t()
+        assert lfc.load().lfc_encode_gpu(DEVICE, C.byref(p), C.byref(out), C.byref(n), None, None) == -4
+        what = [e[0] for e in w.events]
+        assert any(e[0] == "launch" and kernel in e[1] for e in w.events)
+        assert "wait" in what[what.index("copy in"):], (kernel, what)
+    print("done")
+
+
 # ---------------------------------------------------------------------------
 
 @pytest.mark.parametrize("name", CASES)
