@@ -413,7 +413,8 @@ __global__ __launch_bounds__(kT) void k_enc_pack(const int8_t *code_tab, const u
                                                  uint32_t *off_out, uint32_t *srv, EncGeo g) {
   constexpr int S = B * B;
   __shared__ PackLds<S> lds[kT / 64];
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, gi = blockIdx.x * (kT / 64) + wv;
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int gi = (int)(blockIdx.y * gridDim.x + blockIdx.x) * (kT / 64) + wv;   // (at most 2^30 groups)
   if (gi >= g.ng) {
     if (gi == g.ng && lane < 2) srv[offsets[g.ng] + lane] = 0;   // the section's spare words
     if (gi == g.ng && lane == 0) off_out[gi] = offsets[gi];
@@ -733,8 +734,10 @@ lfc_status encode_gpu(const uint8_t *d_rgb, const lfc_params *p, void **stream_o
   char *stream = static_cast<char *>(ds.p);
   by_block([&](auto n) {
     constexpr int B = decltype(n)::value;
-    // (one wave more than groups: it writes the last offset and the section's two spare words)
-    hipLaunchKernelGGL(k_enc_pack<B>, dim3((unsigned)((geo.ng + kT / 64) / (kT / 64))), dim3(kT), 0, s,
+    // (one wave more than groups: it writes the last offset and the section's two
+    // spare words; a grid dimension holds fewer than 2^32 threads)
+    const unsigned wgs = (unsigned)((geo.ng + kT / 64) / (kT / 64)), row = std::min(wgs, 1u << 22);
+    hipLaunchKernelGGL(k_enc_pack<B>, dim3(row, (wgs + row - 1) / row), dim3(kT), 0, s,
                        (const int8_t *)code_tab, (const uint16_t *)zv, (const uint32_t *)d_off,
                        reinterpret_cast<uint32_t *>(stream + off_off), reinterpret_cast<uint32_t *>(stream + srv_off), g);
     const int64_t rows = (int64_t)geo.n_top * geo.nb * 3 * B;

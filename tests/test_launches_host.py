@@ -117,6 +117,24 @@ def gpu_encoder_fails_while_its_tables_are_copied(w):
     print("done")
 
 
+@case
+def gpu_encoder_of_large_views(w):
+    """A dimension of a launch holds fewer than 2^32 threads, whatever size of view the encoder takes; every
+    group, and the wave after the last one, has a wave of the packing kernel."""
+    for W, H, block in ((65536, 1364, 2), (65536, 1366, 2), (65534, 21842, 2), (65536, 5464, 4), (640, 480, 4)):
+        p = lfc.Params(2, 2, W, H, block, 2, (2,)).to_c()
+        out, n = C.c_void_p(), C.c_size_t()
+        w.launches.clear()
+        lfc._check(lfc.load().lfc_encode_gpu(DEVICE, C.byref(p), C.byref(out), C.byref(n), None, None))
+        lfc.load().lfc_free(out)
+        groups = 3 * -(-W // block) * -(-H // block)
+        for name, g, threads, _, _ in w.launches:
+            assert g[0] * threads < 1 << 32 and g[1] <= 65535 and g[2] <= 65535, (W, H, block, name, g)
+            if "k_enc_pack" in name:
+                assert groups + 1 <= g[0] * g[1] * threads // 64 < 1 << 31
+    print("done")
+
+
 # ---------------------------------------------------------------------------
 
 @pytest.mark.parametrize("name", CASES)
