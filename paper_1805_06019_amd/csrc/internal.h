@@ -54,8 +54,13 @@ constexpr int order_words(int B) { return 4 + 2 * (64 / B); }
 // first slots, per run three words of node positions and five of its record)
 // in the whole-field kernel's schedule, beyond its first run's: the kernel
 // keeps them in LDS.
-// (beside a tile of more than 64 KB, fewer)
-constexpr size_t lf_tab_limit(int B, int tile_cap) { return tile_cap * B * B / 2 > 16384 ? 1024 : 1280; }
+// (beside a tile of more than 64 KB, fewer: the kernel holds two such tables, and
+// past 128 KB two of 512 words take no more than the 1,024 that the largest
+// accepted tiles, of 8 x 8 blocks, leave in the workgroup's 160 KB)
+constexpr size_t lf_tab_limit(int B, int tile_cap) {
+  const int words = tile_cap * B * B / 2;
+  return words > 32768 ? 512 : (words > 16384 ? 1024 : 1280);
+}
 // Range codes whose 2 x 2 and 4 x 4 blocks the whole-field kernels decode from
 // one window of words: all but plain ones of more than 7 bits.
 constexpr bool window_code(uint32_t code) { return code < 7u || code >= 12u; }

@@ -135,6 +135,26 @@ def gpu_encoder_of_large_views(w):
     print("done")
 
 
+@case
+def whole_field_decode_with_the_largest_tiles(w):
+    """A tile that leaves room for 1,024 words of gather tables beside it, the LUT and extents and the key-view
+    rows is decoded; a larger one is refused."""
+    # sparse fields of large trees, as many runs in a chunk as its tables allow: 25 key views (not staged), one
+    # and 16 (the most that are staged: 16 KB)
+    for levels, grid, most in ((3, 17, 1232), (6, 17, 1224), (4, 32, 1104)):
+        for block, tile in ((2, 2048), (4, 2048), (8, 512), (8, 520), (8, 1024), (8, 1032), (8, 1072), (8, 1080),
+                            (8, 1104), (8, 1168), (8, most), (8, most + 8)):
+            h = opened(grid, grid, 16, 8, block, levels, tile)
+            w.launches.clear()
+            st = lfc.load().lfc_decode_blocks(h, None, grid * grid, 1, DEVICE, None)
+            fits = block < 8 or tile <= most
+            assert st == (0 if fits else -6), (block, tile, levels, st)
+            if fits:
+                assert w.launches[0][3] <= 160 * 1024
+            lfc.load().lfc_close(h)
+    print("done")
+
+
 # ---------------------------------------------------------------------------
 
 @pytest.mark.parametrize("name", CASES)
