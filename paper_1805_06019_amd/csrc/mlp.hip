@@ -167,8 +167,9 @@ __global__ __launch_bounds__(64 * kMfmaWaves, kMfmaWgs) void k_mlp_infer_mfma(In
   };
   // bias, ReLU, rounding to bf16, and the next layer's operand of each K
   // step.  The ReLU takes a NaN to 0.  FAST clamps the rounded pairs as signed
-  // 16-bit numbers instead, which keeps a positive NaN: it makes every logit of
-  // its row NaN, and the tile is then done again without FAST.
+  // 16-bit numbers instead, which keeps a positive NaN: it makes every sum of its
+  // row in the next layer NaN, of whatever sign, so each layer's sums are tested
+  // before they are clamped, and the tile is then done again without FAST.
   auto next_operand = [&](auto fast, const f32x16 (&d)[2], const float *b, bf16x8 (&o)[4]) {
     constexpr bool FAST = decltype(fast)::value;
     typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
@@ -220,6 +221,7 @@ __global__ __launch_bounds__(64 * kMfmaWaves, kMfmaWgs) void k_mlp_infer_mfma(In
   for (; tile < tiles; tile += stride) {
     request(tile + stride);
     f32x16 d[2];
+    bool nan2 = false;   // a sum of layer 2 is NaN (all of its row are, if a NaN was kept)
     auto layers = [&](auto fast) {
       // (the biases are read anew for each tile: kept in registers, their 160
       // values would halve the waves per SIMD)
@@ -231,6 +233,7 @@ __global__ __launch_bounds__(64 * kMfmaWaves, kMfmaWgs) void k_mlp_infer_mfma(In
       for (int t = 0; t < 2; t++) d[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w1[t], x, f32x16{}, 0, 0, 0);
       next_operand(fast, d, bias, o);
       products(w2, o, d);
+      if constexpr (decltype(fast)::value) nan2 = d[0][0] != d[0][0];
       next_operand(fast, d, bias + kH, o);
       products(w3, o, d);
 #pragma unroll
@@ -241,7 +244,7 @@ __global__ __launch_bounds__(64 * kMfmaWaves, kMfmaWgs) void k_mlp_infer_mfma(In
       }
     };
     layers(std::true_type{});
-    if (__builtin_expect(__any(d[0][0] != d[0][0]), 0)) layers(std::false_type{});
+    if (__builtin_expect(__any(nan2 || d[0][0] != d[0][0]), 0)) layers(std::false_type{});
     // this lane's logits of its row: units 8 g + 4 h + j (d[0][4 g + j]), g = 0..3, and 32 + 4 h + j
     const int64_t r0 = tile * 32;
     const int rows = (int)min((int64_t)32, a.n - r0);
