@@ -267,19 +267,30 @@ lfc_status lfc_mlp_adam(float *d_master, uint16_t *d_w, float *d_m, float *d_v, 
 /*
  * lfc_encode_ex on the GPU (the global thresholds of the parameters):
  * level 0, the key-view filters, the closed-loop residual levels and the
- * packing of every group run as kernels on stream s; the host turns the
- * group sizes into offsets and assembles the stream.  The stream and the
+ * packing of every group run as kernels on stream s, which lay the stream
+ * out on the device; it is copied to the host once.  The stream and the
  * statistics equal lfc_encode_ex's byte for byte.
  *  d_rgb  device uint8 [grid_v][grid_u][height][width][3] (as lfc_encode).
- * Blocks until done.  Device memory for the tree's levels and tables is
- * allocated and freed by the call.
+ * Blocks until done.  Device memory for the tree's levels, the tables and
+ * the stream comes from the memory pool that lfc_render_views takes its
+ * scratch from and goes back to it: up to 1 GiB of what the two free stays
+ * with the library until the process ends.  The stream's host memory:
+ * lfc_free.
  * Errors: as lfc_encode, plus LFC_E_INVALID (d_rgb not device memory of that
  * size), LFC_E_NOMEM (device), LFC_E_HIP.
  */
 lfc_status lfc_encode_gpu(const uint8_t *d_rgb, const lfc_params *p, void **stream_out, size_t *bytes_out,
                           lfc_encode_stats *stats, hipStream_t s);
 
-/* Frees a buffer returned by lfc_encode.  NULL is ignored. */
+/*
+ * Frees a stream returned by lfc_encode, lfc_encode_ex, lfc_encode_ctl or
+ * lfc_encode_gpu (of any thread).  NULL is ignored.  Of the streams of 1 MiB
+ * and more the library keeps the memory of the largest one freed, up to
+ * 128 MiB, for the next of at least half that size: its pages are already
+ * there.  That memory goes back to the system when a larger freed stream
+ * takes its place, after four streams of 1 MiB and more in a row that were
+ * too small for it, or when the process ends.
+ */
 void lfc_free(void *ptr);
 
 /*

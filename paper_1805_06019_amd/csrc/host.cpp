@@ -53,10 +53,12 @@ static std::string fmt(const char *f, ...) {
 // A fresh large allocation costs a page fault per 4 KB at its first writing
 // (several ms for a stream of 25 MB, more than encoding it on the GPU), so
 // streams of at least kStreamBig bytes come from memory advised to use huge
-// pages, and the last one freed, up to kStreamKeep bytes, is kept for the next
-// (it goes back when a larger one takes its place, else when the process
-// ends).  Every thread may allocate and free.
+// pages, and the largest one freed, up to kStreamKeep bytes, is kept for the next
+// of at least half its size.  It goes back when a larger one takes its place,
+// when kStreamPasses streams in a row were too small for it, else when the
+// process ends.  Every thread may allocate and free.
 constexpr size_t kStreamBig = (size_t)1 << 20, kStreamKeep = (size_t)128 << 20, kHugePage = (size_t)2 << 20;
+constexpr int kStreamPasses = 4;
 
 namespace {
 struct StreamMemory {
@@ -64,6 +66,7 @@ struct StreamMemory {
   std::unordered_map<void *, size_t> big;   // sizes of the large allocations in use
   void *kept = nullptr;
   size_t kept_bytes = 0;
+  int passes = 0;                           // streams in a row too small for the kept one
 };
 StreamMemory &stream_memory() {
   static StreamMemory *m = new StreamMemory;   // (outlives every static destructor that frees a stream)
@@ -75,20 +78,30 @@ void *stream_alloc(size_t bytes) noexcept {
   if (bytes < kStreamBig) return std::malloc(std::max<size_t>(bytes, 1));
   try {
     StreamMemory &m = stream_memory();
-    const size_t need = (bytes + kHugePage - 1) / kHugePage * kHugePage;
-    void *p = nullptr;
+    // whole huge pages from where they add at most an eighth
+    const size_t unit = bytes >= 8 * kHugePage ? kHugePage : 4096;
+    const size_t need = (bytes + unit - 1) / unit * unit;
+    void *p = nullptr, *back = nullptr;
     size_t have = need;
     {
       std::lock_guard<std::mutex> lock(m.mu);
       if (m.kept && m.kept_bytes >= need) {
-        p = m.kept;
-        have = m.kept_bytes;
-        m.kept = nullptr;
+        const bool fits = need >= m.kept_bytes / 2;
+        if (fits) {
+          p = m.kept;
+          have = m.kept_bytes;
+        } else if (++m.passes == kStreamPasses) {
+          back = m.kept;
+        }
+        if (p || back) {
+          m.kept = nullptr;
+          m.passes = 0;
+        }
       }
     }
+    std::free(back);
     if (!p) {
-      p = std::aligned_alloc(kHugePage, need);
-      if (!p) return nullptr;
+      if (posix_memalign(&p, kHugePage, need) != 0) return nullptr;
       (void)madvise(p, need, MADV_HUGEPAGE);
     }
     std::lock_guard<std::mutex> lock(m.mu);
@@ -116,6 +129,7 @@ void stream_free(void *p) noexcept {
       if (bytes <= kStreamKeep && (!m.kept || bytes > m.kept_bytes)) {
         std::swap(m.kept, p);
         m.kept_bytes = bytes;
+        m.passes = 0;
       }
     }
   }
