@@ -485,7 +485,8 @@ lfc_status lfc_render_views(const lfc_lf *lf, const lfc_view *d_views, int32_t n
  * Launch shape of a render (results are the same bytes for every shape).
  *  LFC_RENDER_AUTO     the library's choice (decode-then-interpolate when the
  *                      batch's pixels are at least 1/20 of the light field's
- *                      samples, else tiles of up to 64 x 16 pixels).
+ *                      samples, else tiles of up to 64 x 16 pixels, of the
+ *                      size that takes the fewest passes over the footprints).
  *  LFC_RENDER_TILES    one workgroup per output tile of tile_w x tile_h
  *                      pixels decodes the tile's source footprint (0 x 0:
  *                      64 x 16, shrunk until the footprint fits 64 KB).
@@ -538,8 +539,9 @@ lfc_status lfc_render_views_noalloc(const lfc_lf *lf, const lfc_view *d_views, i
 
 /*
  * Measured tuning of the render's launch shape for one (light field, batch
- * size, output size): the decoded path and each tile shape of 32 x 8 up to
- * 256 x 8 pixels whose footprint fits are run once, then timed over `reps`
+ * size, output size): the decoded path, the tile of the automatic choice and
+ * each tile shape of 32 x 8 up to 256 x 8 pixels whose footprint fits are run
+ * once, then timed over `reps`
  * launches with events on stream s, on the caller's views (the output is
  * overwritten).  Blocks until the timing is done.  res->cfg[res->best] is
  * the fastest.  Allocates (and frees) the decoded path's scratch; when that

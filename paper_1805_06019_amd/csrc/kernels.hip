@@ -2774,10 +2774,9 @@ extern "C" lfc_status lfc_render_views_noalloc(const lfc_lf *lf, const lfc_view 
       return fail(LFC_E_RANGE, std::string(who) + ": the decoded views need " + std::to_string(need) +
                                    " bytes; the static scratch holds " + std::to_string(LFC_NOALLOC_SCRATCH_BYTES));
     // the automatic choice falls back to the tile path, which needs no scratch
-    RenderChoice tiles = rc;
-    lfc_render_config tc{LFC_RENDER_TILES, 0, 0, rc.disp};
-    if (lfc_status st = choose_render(lf, n, out_w, out_h, &tc, tiles, who)) return st;
-    rc = tiles;
+    rc.decoded = false;
+    if (!best_plan(lf->geo, n, out_w, out_h, rc.pl))
+      return fail(LFC_E_UNSUPPORTED, std::string(who) + ": output too strongly minified for the tile footprint");
   }
   void *ws = nullptr;
   if (rc.decoded)
@@ -2797,8 +2796,11 @@ extern "C" lfc_status lfc_render_tune(const lfc_lf *lf, const lfc_view *d_views,
   static const int kShapes[][2] = {{32, 8}, {32, 16}, {64, 8}, {64, 16}, {64, 32}, {128, 8}, {128, 16}, {256, 8}};
   std::vector<lfc_render_config> cands;
   cands.push_back(lfc_render_config{LFC_RENDER_DECODED, 0, 0, 0.0f});
+  RenderPlan pl{};   // the automatic choice's tile first, so that no choice made here is slower than it
+  if (best_plan(lf->geo, n, out_w, out_h, pl)) cands.push_back(lfc_render_config{LFC_RENDER_TILES, pl.TX, pl.TY, 0.0f});
+  const int auto_w = pl.TX, auto_h = pl.TY;
   for (const auto &sh : kShapes) {
-    RenderPlan pl;
+    if (sh[0] == auto_w && sh[1] == auto_h) continue;
     if (plan_render(lf->geo, out_w, out_h, pl, sh[0], sh[1], false))
       cands.push_back(lfc_render_config{LFC_RENDER_TILES, sh[0], sh[1], 0.0f});
   }

@@ -155,6 +155,46 @@ def whole_field_decode_with_the_largest_tiles(w):
     print("done")
 
 
+def auto_tile(h, n, wo, ho):
+    """The tile that an automatic plan reports, or None if it takes the decoded path."""
+    plan, cfg, graph = C.c_void_p(), lfc.c_render_config(), C.c_int32()
+    lfc._check(lfc.load().lfc_render_plan_create(h, None, DEVICE, n, wo, ho, DEVICE, 0, C.byref(plan)))
+    lfc._check(lfc.load().lfc_render_plan_info(plan, C.byref(cfg), C.byref(graph)))
+    lfc.load().lfc_render_plan_destroy(plan)
+    return None if cfg.path == lfc.RENDER_DECODED else (cfg.tile_w, cfg.tile_h)
+
+
+@case
+def render_tuner_tries_the_automatic_tile(w):
+    """The tuner's candidates hold the tile of the automatic choice for its number and size of views, so its
+    result is no slower than plain renders, also where every other shape's footprint is too large."""
+    h = opened(5, 5, 640, 480, 4, 2)
+    for n, wo, ho in ((1, 512, 384), (1, 256, 256), (1, 80, 60), (2, 200, 150), (3, 90, 70), (1, 160, 60), (1, 640, 61)):
+        tile = auto_tile(h, n, wo, ho)
+        assert tile is not None
+        res = lfc.c_render_tuning()
+        lfc._check(lfc.load().lfc_render_tune(h, DEVICE, n, wo, ho, DEVICE, 2, C.byref(res), None))
+        tried = [(res.cfg[k].path, res.cfg[k].tile_w, res.cfg[k].tile_h) for k in range(res.n_tried)]
+        assert (lfc.RENDER_TILES, *tile) in tried and (lfc.RENDER_DECODED, 0, 0) in tried, (n, wo, ho, tile, tried)
+        assert len(set(tried)) == len(tried) <= 16
+    print("done")
+
+
+@case
+def renders_without_allocation_take_the_automatic_tile(w):
+    """Where the decoded views exceed the static scratch, the automatic choice of the entry point that allocates
+    nothing falls back to the tile of lfc_render_views (as that takes it for a view fewer)."""
+    h = opened(17, 17, 256, 256, 4, 2)
+    assert 17 * 17 * 256 * 256 * 4 > lfc.NOALLOC_SCRATCH_BYTES
+    n = 17 * 17 * 256 * 256 // (20 * 128 * 128)
+    tile = auto_tile(h, n, 128, 128)
+    assert tile is not None and auto_tile(h, n + 1, 128, 128) is None
+    w.launches.clear()
+    lfc._check(lfc.load().lfc_render_views_noalloc(h, DEVICE, n + 1, 128, 128, DEVICE, None, None))
+    assert [x[1] for x in w.launches] == [(-(-128 // tile[0]), -(-128 // tile[1]), n + 1)], (tile, w.launches)
+    print("done")
+
+
 # ---------------------------------------------------------------------------
 
 @pytest.mark.parametrize("name", CASES)
