@@ -2980,12 +2980,11 @@ lfc_status decode_multi_launch(int block, const void *d_lfs, int n_lf, const int
 
 int lf_device(const lfc_lf *lf) { return lf->device; }
 
-lfc_status render_req_fill(const lfc_lf *lf, const lfc_view &v, int wo, int ho, float *out, void *dst, int *block,
+lfc_status render_req_fill(const lfc_lf *lf, const lfc_view &v, int wo, int ho, int n, float *out, void *dst, int *block,
                            int *ntiles, size_t *lds) {
   const Geometry &g = lf->geo;
   RenderPlan pl;
-  // (as one of many renders: fewest passes in all)
-  if (!best_plan(g, 64, wo, ho, pl))
+  if (!best_plan(g, n, wo, ho, pl))
     return fail(LFC_E_UNSUPPORTED, "lfc_batch_render: output too strongly minified for the tile footprint");
   RenderReq r{};
   r.a = RenderArgs{ra_args(lf), nullptr, out, wo, ho, g.U, g.V, g.W, g.H, pl.TX, pl.TY, pl.fbx, pl.fby, 0.0f};

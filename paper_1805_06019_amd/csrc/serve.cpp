@@ -236,6 +236,8 @@ lfc_status plan_batch(lfc_batch *b, const lfc_lf *const *lfs, int32_t n_lf, cons
   const size_t rb = lfc::render_req_bytes(), ab = lfc::rgb_args_bytes(), ib = lfc::interp_req_bytes();
   std::vector<char> packed((size_t)n * rb);
   std::vector<int> bs(n, 0);
+  int n_tiled = 0;   // requests rendered by tiles, whose number the tile depends on
+  for (int i = 0; i < n; i++) n_tiled += !L.scr[(size_t)reqs[i].lf];
   for (int i = 0; i < n; i++) {
     const lfc_render_request &r = reqs[i];
     if (L.scr[(size_t)r.lf]) {
@@ -247,8 +249,8 @@ lfc_status plan_batch(lfc_batch *b, const lfc_lf *const *lfs, int32_t n_lf, cons
     }
     int block = 0, nt = 0;
     size_t lds = 0;
-    if (lfc_status st = lfc::render_req_fill(lfs[r.lf], r.view, r.out_w, r.out_h, d_outs[i], &packed[(size_t)i * rb],
-                                             &block, &nt, &lds))
+    if (lfc_status st = lfc::render_req_fill(lfs[r.lf], r.view, r.out_w, r.out_h, n_tiled, d_outs[i],
+                                             &packed[(size_t)i * rb], &block, &nt, &lds))
       return st;
     bs[i] = block;
     BatchLayout::Group &gp = L.grp[block];

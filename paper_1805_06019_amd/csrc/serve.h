@@ -24,9 +24,9 @@ lfc_status device_buffer(const void *p, size_t need, size_t align, const char *w
 lfc_status scratch_alloc(void **p, size_t bytes, hipStream_t s);
 
 // Packs request (view v of lf at wo x ho into out, [3][ho][wo] floats) into
-// dst; reports the light field's block size, the request's tile count and
-// the LDS bytes its tiles need.
-lfc_status render_req_fill(const lfc_lf *lf, const lfc_view &v, int wo, int ho, float *out, void *dst, int *block,
+// dst, as one of n that a launch renders by tiles; reports the light field's
+// block size, the request's tile count and the LDS bytes its tiles need.
+lfc_status render_req_fill(const lfc_lf *lf, const lfc_view &v, int wo, int ho, int n, float *out, void *dst, int *block,
                            int *ntiles, size_t *lds);
 
 // One launch over n packed requests already in device memory (all of block

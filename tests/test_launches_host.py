@@ -195,6 +195,21 @@ def renders_without_allocation_take_the_automatic_tile(w):
     print("done")
 
 
+@case
+def batch_tiles_follow_the_number_of_requests(w):
+    """The tile requests of a batch, of one size, take the tile of as many views of that size rendered at once."""
+    lib, h = lfc.load(), opened(5, 5, 640, 480, 4, 2)
+    b = C.c_void_p()
+    lfc._check(lib.lfc_batch_create(C.byref(b)))
+    for n, wo, ho in ((1, 512, 384), (1, 160, 100), (2, 160, 100), (6, 160, 100), (3, 200, 150), (1, 320, 240)):
+        tile = auto_tile(h, n, wo, ho)
+        reqs = lfc._requests([(0, wo, ho, (1.5, 2.0, 0.0, 0.0))] * n)
+        w.launches.clear()
+        lfc._check(lib.lfc_batch_render(b, (C.c_void_p * 1)(h), 1, reqs, n, (C.c_void_p * n)(*([DEVICE] * n)), None))
+        assert [x[1] for x in w.launches] == [(-(-wo // tile[0]) * -(-ho // tile[1]), n, 1)], (n, wo, ho, tile, w.launches)
+    print("done")
+
+
 # ---------------------------------------------------------------------------
 
 @pytest.mark.parametrize("name", CASES)
