@@ -13,7 +13,8 @@
 // blocks of one block row and channel; one lane decodes a whole stored
 // residual block into LDS, then each lane gathers and stores 16 bytes of an
 // output row (key view + ancestors + leaf).  Random access and rendering
-// give one lane one row of B samples of a block.  Samples travel as packed
+// give one lane one channel of a block (random access to 8 x 8 blocks: one
+// row of it).  Samples travel as packed
 // int16 pairs: the residual tail (zigzag undo, step 2^q, adding the parent)
 // runs on both halves of a register at once, and the sums wrap modulo 2^16
 // exactly as the final int16 store of a 32-bit sum would.
@@ -47,21 +48,11 @@ constexpr uint32_t kAbsent = 0xFFFFFFFFu;
 constexpr int kLutEntries = 384;  // 256 trit-field values, then 128 quint-field values
 constexpr int kThreads = 256;
 
-// Range code k: 0..11 bits (m = k+1), 12..18 trits (m = k-12), 19..25 quints (m = k-19).
-__device__ __forceinline__ uint32_t code_kind(uint32_t k) { return k < 12u ? 0u : (k < 19u ? 1u : 2u); }
-__device__ __forceinline__ uint32_t code_m(uint32_t k) { return k < 12u ? k + 1u : (k < 19u ? k - 12u : k - 19u); }
-
 template <int S>
 struct Planes {
   static constexpr uint32_t trit = (8 * S + 4) / 5;    // digit-plane bits, trit blocks
   static constexpr uint32_t quint = (7 * S + 2) / 3;   // digit-plane bits, quint blocks
 };
-
-template <int S>
-__device__ __forceinline__ uint32_t block_bits(uint32_t code) {
-  const uint32_t kind = code_kind(code), m = code_m(code);
-  return S * m + (kind == 0u ? 0u : (kind == 1u ? Planes<S>::trit : Planes<S>::quint));
-}
 
 // Digits of a trit field (entries 0..255: five 2-bit digits) or of a quint
 // field (entries 256..383: three 3-bit digits).  Out-of-range fields map to 0;
@@ -99,10 +90,6 @@ __device__ __forceinline__ uint64_t window64(const uint32_t *gw, uint32_t pos) {
   return ((uint64_t)hi << 32) | lo;
 }
 
-__device__ __forceinline__ uint64_t join64(const uint32_t v[3], uint32_t sh) {
-  return ((uint64_t)__builtin_amdgcn_alignbit(v[2], v[1], sh) << 32) | __builtin_amdgcn_alignbit(v[1], v[0], sh);
-}
-
 typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 typedef short i16x2 __attribute__((ext_vector_type(2)));
 
@@ -130,15 +117,14 @@ __device__ __forceinline__ uint32_t unzigzag_pk(uint32_t z, int q) {
   return t ^ ((z & 0x00010001u) * inv);
 }
 
-// Where the digits of row y (values y*B .. y*B+B-1) sit in a trit or quint
+// Where the digits of row y (values 8 y .. 8 y + 7) sit in a trit or quint 8 x 8
 // block: bits 0..7 the bit offset of the row's first digit field in the
 // digit plane, bits 8..15 the offset of the row's first digit in the
 // concatenated digits of those fields, bits 16+4i the width of the row's i-th
 // field (the last group of a block can be short; 0 = no such field).
 // Computed once per lane.
-template <int B>
 __device__ __forceinline__ uint32_t digit_plan(int y, bool trit) {
-  constexpr int S = B * B;
+  constexpr int B = 8, S = B * B;
   const int glen = trit ? 5 : 3, fw = trit ? 8 : 7, dbits = trit ? 2 : 3;
   const int rem = S % glen, last = S / glen;
   const int pw = trit ? (8 * rem + 4) / 5 : (7 * rem + 2) / 3;
@@ -149,91 +135,39 @@ __device__ __forceinline__ uint32_t digit_plan(int y, bool trit) {
   return plan;
 }
 
-// Words of one row's BISE fields, read before any of them is used so that the
-// reads of several blocks can be in flight together.
-template <int B>
-struct RowWords {
-  uint32_t l[3];     // low-bit plane from value i0
-  uint32_t l2[3];    // low-bit plane from value i0+4 (B == 8)
-  uint32_t dg[2];    // the row's digit fields
-};
-
-template <int B>
-__device__ __forceinline__ void fetch_row(const uint32_t *gw, uint32_t e, uint32_t plan_t, uint32_t plan_q, int y,
-                                          RowWords<B> &w) {
-  constexpr int S = B * B;
+// Row y of an 8 x 8 block of any kind: its BISE fields read (digit << m | low
+// bits), zigzag undone, times 2^q; d holds the residuals as packed int16 pairs.
+__device__ __forceinline__ void decode_row(const uint32_t *gw, uint32_t e, uint32_t plan_t, uint32_t plan_q, int y,
+                                           int q, const uint16_t *lut, uint32_t d[4]) {
+  constexpr int B = 8, S = B * B;
   const uint32_t code = e & 31u, rel = e >> 5;
   const bool is_bits = code < 12u, is_trit = code - 12u < 7u;
   const uint32_t m = is_bits ? code + 1u : (is_trit ? code - 12u : code - 19u);
   const uint32_t hdr = is_bits ? 0u : (is_trit ? Planes<S>::trit : Planes<S>::quint);
-  const uint32_t p = rel + hdr + (uint32_t)(y * B) * m;
-  const uint32_t *q = gw + (p >> 5);
-  w.l[0] = q[0];
-  w.l[1] = q[1];
-  w.l[2] = q[2];
-  if constexpr (B > 4) {
-    const uint32_t *q2 = gw + ((p + 4u * m) >> 5);
-    w.l2[0] = q2[0];
-    w.l2[1] = q2[1];
-    w.l2[2] = q2[2];
-  }
-  const uint32_t pd = rel + (is_bits ? 0u : ((is_trit ? plan_t : plan_q) & 0xffu));
+  const uint32_t p = rel + hdr + (uint32_t)(y * B) * m, lmask = (1u << m) - 1u;
+  const uint32_t plan = is_trit ? plan_t : plan_q, pd = rel + (is_bits ? 0u : (plan & 0xffu));
   const uint32_t *qd = gw + (pd >> 5);
-  w.dg[0] = qd[0];
-  w.dg[1] = qd[1];
-}
-
-// BISE unpack of the row (digit << m | low bits), zigzag undo, times 2^q:
-// d holds the B residuals as B/2 packed int16 pairs.
-template <int B>
-__device__ __forceinline__ void finish_row(const RowWords<B> &w, uint32_t e, uint32_t plan_t, uint32_t plan_q, int y,
-                                           int q, const uint16_t *lut, uint32_t d[B / 2]) {
-  constexpr int S = B * B, NF = B == 8 ? 4 : 2;
-  using DigitWord = std::conditional_t<B == 8, uint64_t, uint32_t>;
-  const uint32_t code = e & 31u, rel = e >> 5;
-  const bool is_bits = code < 12u, is_trit = code - 12u < 7u;
-  const uint32_t m = is_bits ? code + 1u : (is_trit ? code - 12u : code - 19u);
-  const uint32_t hdr = is_bits ? 0u : (is_trit ? Planes<S>::trit : Planes<S>::quint);
-  const uint32_t p = rel + hdr + (uint32_t)(y * B) * m;
-  const uint32_t lmask = (1u << m) - 1u;
-  uint32_t low[B];
-  {
-    const uint64_t v = join64(w.l, p & 31u);
-#pragma unroll
-    for (int k = 0; k < (B < 4 ? B : 4); k++) low[k] = (uint32_t)(v >> (k * m)) & lmask;
-    if constexpr (B > 4) {
-      const uint64_t v2 = join64(w.l2, (p + 4u * m) & 31u);
-#pragma unroll
-      for (int k = 4; k < B; k++) low[k] = (uint32_t)(v2 >> ((k - 4) * m)) & lmask;
-    }
-  }
+  const uint64_t v = window64(gw, p), v2 = window64(gw, p + 4u * m);   // low bits of values 0..3, 4..7
+  const uint32_t win = __builtin_amdgcn_alignbit(qd[1], qd[0], pd & 31u);
   // the row's digit fields through the LUT, concatenated, then one digit per value
-  const uint32_t plan = is_trit ? plan_t : plan_q;
-  const uint32_t pd = rel + (is_bits ? 0u : (plan & 0xffu));
-  const uint32_t win = __builtin_amdgcn_alignbit(w.dg[1], w.dg[0], pd & 31u);
   const uint32_t fw = is_trit ? 8u : 7u, gb = is_trit ? 10u : 9u, db = is_trit ? 2u : 3u;
   const uint32_t lb = is_trit ? 0u : 256u;
-  DigitWord D = 0;
+  uint64_t D = 0;
 #pragma unroll
-  for (int i = 0; i < NF; i++) {
+  for (int i = 0; i < 4; i++) {
     const uint32_t f = __builtin_amdgcn_ubfe(win, i * fw, (plan >> (16 + 4 * i)) & 15u);
-    D |= (DigitWord)lut[lb + f] << (i * gb);
+    D |= (uint64_t)lut[lb + f] << (i * gb);
   }
-  const DigitWord rowd = D >> ((plan >> 8) & 0xffu);
+  const uint64_t rowd = D >> ((plan >> 8) & 0xffu);
   const uint32_t dmask = is_bits ? 0u : (is_trit ? 3u : 7u);
   uint32_t u[B];
 #pragma unroll
-  for (int k = 0; k < B; k++) u[k] = ((((uint32_t)(rowd >> (k * db))) & dmask) << m) | low[k];
+  for (int k = 0; k < B; k++) {
+    const uint32_t low = (uint32_t)((k < 4 ? v : v2) >> ((k & 3) * m)) & lmask;
+    u[k] = ((((uint32_t)(rowd >> (k * db))) & dmask) << m) | low;
+  }
 #pragma unroll
   for (int i = 0; i < B / 2; i++) d[i] = unzigzag_pk(u[2 * i] | (u[2 * i + 1] << 16), q);
-}
-
-template <int B>
-__device__ __forceinline__ void decode_row(const uint32_t *gw, uint32_t e, uint32_t plan_t, uint32_t plan_q, int y,
-                                           int q, const uint16_t *lut, uint32_t d[B / 2]) {
-  RowWords<B> w;
-  fetch_row<B>(gw, e, plan_t, plan_q, y, w);
-  finish_row<B>(w, e, plan_t, plan_q, y, q, lut, d);
 }
 
 // a row of B int16 samples as B/2 packed words
@@ -335,7 +269,7 @@ __device__ __forceinline__ void decode_block_k(const uint32_t *gw, uint32_t e, i
   constexpr uint32_t HDR = KIND == 0 ? 0u : (KIND == 1 ? Planes<S>::trit : Planes<S>::quint);
   constexpr uint32_t FW = KIND == 1 ? 8u : 7u, GB = KIND == 1 ? 10u : 9u, DB = KIND == 1 ? 2u : 3u;
   constexpr uint32_t LB = KIND == 1 ? 0u : 256u, DMASK = KIND == 1 ? 3u : 7u;
-  using DigitWord = std::conditional_t<B == 8, uint64_t, uint32_t>;
+  static_assert(B == 8 || KIND == 0);
   const uint32_t code = e & 31u, rel = e >> 5;
   const uint32_t m = KIND == 0 ? code + 1u : (KIND == 1 ? code - 12u : code - 19u);
   const uint32_t lmask = (1u << m) - 1u;
@@ -354,17 +288,17 @@ __device__ __forceinline__ void decode_block_k(const uint32_t *gw, uint32_t e, i
       }
     }
     if constexpr (KIND != 0) {
-      const uint32_t plan = digit_plan<B>(y, KIND == 1);   // a constant once unrolled
+      const uint32_t plan = digit_plan(y, KIND == 1);   // a constant once unrolled
       const uint32_t pd = rel + (plan & 0xffu);
       const uint32_t *qd = gw + (pd >> 5);
       const uint32_t win = __builtin_amdgcn_alignbit(qd[1], qd[0], pd & 31u);
-      DigitWord D = 0;
+      uint64_t D = 0;
 #pragma unroll
-      for (int i = 0; i < (B == 8 ? 4 : 2); i++) {
+      for (int i = 0; i < 4; i++) {
         const uint32_t wdt = (plan >> (16 + 4 * i)) & 15u;
-        if (wdt) D |= (DigitWord)lut[LB + ((win >> (i * FW)) & ((1u << wdt) - 1u))] << (i * GB);
+        if (wdt) D |= (uint64_t)lut[LB + ((win >> (i * FW)) & ((1u << wdt) - 1u))] << (i * GB);
       }
-      const DigitWord rowd = D >> ((plan >> 8) & 0xffu);
+      const uint64_t rowd = D >> ((plan >> 8) & 0xffu);
 #pragma unroll
       for (int k = 0; k < B; k++) u[k] |= (((uint32_t)(rowd >> (k * DB))) & DMASK) << m;
     }
@@ -539,14 +473,11 @@ __device__ __forceinline__ void decode_fetched(const Window<B> &s, const uint32_
   if constexpr (B == 8 || KIND == 0) decode_block_k<B, KIND>(words + base, e, q, lut, d);
 }
 
-// A whole 8 x 8 block of any kind decoded by one lane, with the generic row
-// decoder (one code for the three kinds, the row plans constant).
-template <int B>
-__device__ __forceinline__ void decode_block(const uint32_t *gw, uint32_t e, int q, const uint16_t *lut,
-                                             uint32_t d[B * B / 2]) {
+// A whole 8 x 8 block of any kind decoded by one lane, row by row (one code for
+// the three kinds, the row plans constant).
+__device__ __forceinline__ void decode_block(const uint32_t *gw, uint32_t e, int q, const uint16_t *lut, uint32_t d[32]) {
 #pragma unroll
-  for (int y = 0; y < B; y++)
-    decode_row<B>(gw, e, digit_plan<B>(y, true), digit_plan<B>(y, false), y, q, lut, d + y * (B / 2));
+  for (int y = 0; y < 8; y++) decode_row(gw, e, digit_plan(y, true), digit_plan(y, false), y, q, lut, d + 4 * y);
 }
 
 // n words from global memory into LDS, without a round trip through
@@ -987,22 +918,20 @@ struct RAArgs {
   const int16_t *rkv;
   const uint32_t *off;
   const uint32_t *srv;
-  const uint32_t *dbase;
   const uint32_t *poff;
   const int32_t *path;
   const int32_t *root;
   int nb, nbx, nv, nbw, L, q;
-  const uint32_t *dir2;   // [nb][nbw][3] (bitmap word, dbase entry) pairs
+  const uint32_t *dir2;   // [nb][nbw][3] (bitmap word, directory index of its first stored node) pairs
 };
 
-// Row y of block b, channel c, of view vi (Alg. 2): key-view row plus the
+// Row y of 8 x 8 block b, channel c, of view vi (Alg. 2): key-view row plus the
 // residual rows of the view's ancestors on levels L-2 down to stop (0: the
-// view itself; a higher stop is progressive decompression, Sec. 3.6), as B/2
+// view itself; a higher stop is progressive decompression, Sec. 3.6), as
 // packed int16 pairs.
-template <int B>
 __device__ __forceinline__ void gather_row(const RAArgs &a, int vi, int b, int c, int y, int stop, uint32_t plan_t,
-                                           uint32_t plan_q, const uint16_t *lut, uint32_t x[B / 2]) {
-  constexpr int S = B * B;
+                                           uint32_t plan_q, const uint16_t *lut, uint32_t x[4]) {
+  constexpr int B = 8, S = B * B;
   const int root = a.root[vi];
   load_row<B>(a.rkv + ((size_t)(root * a.nb + b) * 3 + c) * S + y * B, x);
   const int g = 3 * b + c;
@@ -1019,7 +948,7 @@ __device__ __forceinline__ void gather_row(const RAArgs &a, int vi, int b, int c
     if ((bm >> bit) & 1u) {
       const uint32_t idx = bd.y + __popc(bm & ((1u << bit) - 1u));
       uint32_t d[B / 2];
-      decode_row<B>(gw, a.poff[idx], plan_t, plan_q, y, a.q, lut, d);
+      decode_row(gw, a.poff[idx], plan_t, plan_q, y, a.q, lut, d);
 #pragma unroll
       for (int i = 0; i < B / 2; i++) x[i] = add_pk(x[i], d[i]);
     }
@@ -1092,11 +1021,10 @@ __device__ __forceinline__ void load_lut(uint32_t *lut) {
 }
 
 // Request r = (vi, b) by its lanes, of which this one is sub: the block, or zeros
-// and the error flag if the request is out of range; wide: out is aligned to 16
-// bytes (8 at B = 2).
+// and the error flag if the request is out of range (out is aligned to 16 bytes).
 template <int B>
 __device__ __forceinline__ void serve_request(const RAArgs &ra, bool valid, int vi, int b, int64_t r, int sub, int stop,
-                                              const uint16_t *lut, int16_t *out, bool wide, int32_t *err) {
+                                              const uint16_t *lut, int16_t *out, int32_t *err) {
   constexpr int S = B * B;
   if (!valid && sub == 0) atomicOr(err, 1);
   if constexpr (B <= 4) {
@@ -1104,21 +1032,15 @@ __device__ __forceinline__ void serve_request(const RAArgs &ra, bool valid, int 
     if (valid) gather_block<B>(ra, vi, b, sub, stop, lut, x);
     int16_t *dst = out + ((size_t)r * 3 + sub) * S;
     if constexpr (B == 4) {
-      if (wide) {
-        *reinterpret_cast<uint4 *>(dst) = make_uint4(x[0], x[1], x[2], x[3]);
-        *reinterpret_cast<uint4 *>(dst + 8) = make_uint4(x[4], x[5], x[6], x[7]);
-        return;
-      }
-    } else if (wide) {
+      *reinterpret_cast<uint4 *>(dst) = make_uint4(x[0], x[1], x[2], x[3]);
+      *reinterpret_cast<uint4 *>(dst + 8) = make_uint4(x[4], x[5], x[6], x[7]);
+    } else {
       *reinterpret_cast<uint2 *>(dst) = make_uint2(x[0], x[1]);
-      return;
     }
-#pragma unroll
-    for (int y = 0; y < B; y++) store_row<B>(dst + y * B, x + y * (B / 2));
   } else {
     const int c = sub / B, y = sub % B;
     uint32_t x[B / 2] = {};
-    if (valid) gather_row<B>(ra, vi, b, c, y, stop, digit_plan<B>(y, true), digit_plan<B>(y, false), lut, x);
+    if (valid) gather_row(ra, vi, b, c, y, stop, digit_plan(y, true), digit_plan(y, false), lut, x);
     store_row<B>(out + ((size_t)r * 3 + c) * S + y * B, x);
   }
 }
@@ -1130,7 +1052,6 @@ struct BlocksArgs {
   int32_t *err;
   int64_t n;
   int stop;            // lowest tree level whose residuals are added
-  int wide;            // out takes wide stores
 };
 
 template <int B>
@@ -1153,7 +1074,7 @@ __global__ __launch_bounds__(kThreads) void k_decode_blocks(BlocksArgs a) {
     b = (int)(r % a.ra.nb);
   }
   const bool valid = vi >= 0 && vi < a.ra.nv && b >= 0 && b < a.ra.nb;
-  serve_request<B>(a.ra, valid, vi, b, r, sub, a.stop, reinterpret_cast<const uint16_t *>(lut), a.out, a.wide, a.err);
+  serve_request<B>(a.ra, valid, vi, b, r, sub, a.stop, reinterpret_cast<const uint16_t *>(lut), a.out, a.err);
 }
 
 // The same for a long list over a light field whose tables exceed an L2 several
@@ -1220,8 +1141,7 @@ __global__ __launch_bounds__(kThreads) void k_decode_banded(BlocksArgs a) {
     const int k = crowded ? mine * SHARE + i : (int)s_at[i];
     const int vi = req[2 * k], b = req[2 * k + 1];
     const bool valid = vi >= 0 && vi < a.ra.nv && b >= 0 && b < a.ra.nb;
-    serve_request<B>(a.ra, valid, vi, b, r0 + k, sub, a.stop, reinterpret_cast<const uint16_t *>(lut), a.out, a.wide,
-                     a.err);
+    serve_request<B>(a.ra, valid, vi, b, r0 + k, sub, a.stop, reinterpret_cast<const uint16_t *>(lut), a.out, a.err);
   }
 }
 
@@ -1235,7 +1155,6 @@ struct MultiArgs {
   int16_t *out;        // [n][3][S]
   int32_t *err;
   int64_t n;
-  int wide;
 };
 
 template <int B>
@@ -1254,7 +1173,7 @@ __global__ __launch_bounds__(kThreads) void k_decode_multi(MultiArgs a) {
   RAArgs la{};
   if (known) la = a.lfs[li];   // the light field's record, read once
   const bool valid = known && vi >= 0 && vi < la.nv && b >= 0 && b < la.nb;
-  serve_request<B>(la, valid, vi, b, r, sub, 0, reinterpret_cast<const uint16_t *>(lut), a.out, a.wide, a.err);
+  serve_request<B>(la, valid, vi, b, r, sub, 0, reinterpret_cast<const uint16_t *>(lut), a.out, a.err);
 }
 
 // ---------------------------------------------------------------------------
@@ -1544,7 +1463,7 @@ __device__ __forceinline__ void render_tile(const RenderArgs &a, const lfc_view 
         const uint32_t e = locate(a.ra, 3 * b + c, node[k], &gw);
         if (e == kAbsent) continue;
         uint32_t d[S / 2];
-        decode_block<B>(gw, e, a.ra.q, lut, d);
+        decode_block(gw, e, a.ra.q, lut, d);
 #pragma unroll
         for (int k2 = 0; k2 < 4; k2++) {
           if (owner[k2] != k) continue;
@@ -2286,7 +2205,7 @@ lfc_status check_buffer(const void *p, size_t need, size_t align, const char *wh
 
 RAArgs ra_args(const lfc_lf *lf) {
   const lfc::Geometry &g = lf->geo;
-  return RAArgs{lf->d_rkv, lf->d_off, lf->d_srv, lf->d_dbase, lf->d_poff, lf->d_path, lf->d_root,
+  return RAArgs{lf->d_rkv, lf->d_off, lf->d_srv, lf->d_poff, lf->d_path, lf->d_root,
                 g.nb, g.nbx, g.nv(), g.nbw, g.L, g.q, lf->d_dir2};
 }
 
@@ -2438,13 +2357,10 @@ lfc_status decode_rgb(const lfc_lf *lf, uint32_t *out, const uint32_t *vneed, hi
   return launched(who);
 }
 
-// whether the blocks of a list may be stored wide (see serve_request)
-int wide_blocks(const int16_t *out, int B) { return reinterpret_cast<uintptr_t>(out) % (B == 2 ? 8 : 16) == 0; }
-
 template <int B>
 lfc_status decode_list(const lfc_lf *lf, const int32_t *req, int64_t n, int16_t *out, hipStream_t s, int stop = 0) {
   constexpr int RPW = 64 / request_lanes<B>();
-  BlocksArgs a{ra_args(lf), req, out, lf->d_err, n, stop, wide_blocks(out, B)};
+  BlocksArgs a{ra_args(lf), req, out, lf->d_err, n, stop};
   const int64_t waves = (n + RPW - 1) / RPW;
   const int64_t blocks = (waves + kThreads / 64 - 1) / (kThreads / 64);
   if (blocks > 0x7FFFFFFF) return fail(LFC_E_INVALID, "lfc_decode_blocks: too many requests");
@@ -2965,7 +2881,7 @@ void lf_table_fill(const lfc_lf *lf, void *dst) {
 lfc_status decode_multi_launch(int block, const void *d_lfs, int n_lf, const int32_t *d_req, int64_t n, int16_t *out,
                                int32_t *err, hipStream_t s) {
   if (n <= 0) return LFC_OK;
-  MultiArgs a{static_cast<const RAArgs *>(d_lfs), n_lf, d_req, out, err, n, wide_blocks(out, block)};
+  MultiArgs a{static_cast<const RAArgs *>(d_lfs), n_lf, d_req, out, err, n};
   const int rpw = 64 / (block == 2 ? request_lanes<2>() : (block == 4 ? request_lanes<4>() : request_lanes<8>()));
   const int64_t waves = (n + rpw - 1) / rpw;
   const int64_t blocks = (waves + kThreads / 64 - 1) / (kThreads / 64);
