@@ -579,7 +579,8 @@ lfc_status encode_gpu(const uint8_t *d_rgb, const lfc_params *p, void **stream_o
       return fail(LFC_E_INVALID, "lfc_encode_gpu: d_rgb is not device memory of [V][U][H][W][3] bytes");
     }
   }
-  // grid limits of the launches below (second and third grid dimensions)
+  // views and the nodes of a level are a grid dimension of launches below; the
+  // bounds of three rows and three views to one are the entry point's own
   bool fits = 3 * geo.hp <= 65535 && nv * 3 <= 65535;
   for (int l = 0; l < L; l++) fits &= geo.lu[l] * geo.lv[l] <= 65535;
   if (!fits) return fail(LFC_E_UNSUPPORTED, "lfc_encode_gpu: light field too large for the GPU encoder's grids");

@@ -315,7 +315,7 @@ void build_tree_tables(const Geometry &g, TreeTables &t) {
 // Per strip (channel c, block row by, strip sx of 64/B blocks) the runs of
 // sibling leaves are cut into chunks whose stored blocks fit the kernel's
 // compact residual tile (cap blocks, stored blocks only) and whose gather
-// table (masks, first slots, run records) fits kLFTabWords words; per
+// table and run records fit lf_tab_limit words; per
 // chunk: its runs, its nodes (leaves first, then ancestors), per node a mask
 // of the stored blocks and the tile slot of the first one (slots follow node
 // order, then mask order), per run the positions of its first leaf and of

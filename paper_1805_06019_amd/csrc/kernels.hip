@@ -2366,9 +2366,11 @@ lfc_status decode_list(const lfc_lf *lf, const int32_t *req, int64_t n, int16_t 
   if (blocks > 0x7FFFFFFF) return fail(LFC_E_INVALID, "lfc_decode_blocks: too many requests");
   if constexpr (B <= 4) {
     // By bands if the list and the tables are long (what is requested of higher
-    // levels only is little): 0.75 to 1.1 times as fast with tables of 5 to 10
-    // MB, 1.02 to 1.6 times from 11 MB on; 0.75 to 0.95 times for lists of
-    // 30,000 to 60,000.
+    // levels only is little).  Random lists of 131,072 to 10^6 of 17 x 17 views:
+    // 0.76 to 0.94 times as fast with tables of 2 to 4 MB, 0.96 to 1.17 of 5 to 7,
+    // 1.1 to 1.3 of 9 to 11, 1.1 to 1.75 from 13 MB on; shorter ones 0.9 to 1.1
+    // (30,000) and 0.8 to 1.2 (60,000).  Lists sorted by block lose with any
+    // table, 0.65 to 0.9 times, so the line lies where random ones gain more.
     const lfc::Geometry &g = lf->geo;
     const int64_t tables = (int64_t)lf->stream_bytes + 4 * (int64_t)lf->present + 8 * (int64_t)g.ng * g.nbw;
     const int64_t pieces = (n + 2 * kThreads - 1) / (2 * kThreads);
