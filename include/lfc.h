@@ -277,7 +277,8 @@ lfc_status lfc_mlp_adam(float *d_master, uint16_t *d_w, float *d_m, float *d_v, 
  * with the library until the process ends.  The stream's host memory:
  * lfc_free.
  * Errors: as lfc_encode, plus LFC_E_INVALID (d_rgb not device memory of that
- * size), LFC_E_NOMEM (device), LFC_E_HIP.
+ * size), LFC_E_UNSUPPORTED (3 x the padded height, 3 x the views or the nodes
+ * of a level above 65,535), LFC_E_NOMEM (device), LFC_E_HIP.
  */
 lfc_status lfc_encode_gpu(const uint8_t *d_rgb, const lfc_params *p, void **stream_out, size_t *bytes_out,
                           lfc_encode_stats *stats, hipStream_t s);

@@ -1010,7 +1010,7 @@ __device__ __forceinline__ void gather_block(const RAArgs &a, int vi, int b, int
 // chain of reads (request - path - directory - offset - window) and by the lines
 // they read past L2, about eight; with three lanes a request four times as many
 // are in flight as with one per row, and the levels' chains run side by side.
-// 10^6 blocks of 289 views of 512 x 512: 167 -> 134 us, sorted by block 142 -> 54.
+// 10^6 blocks of 289 views of 512 x 512: 167 -> 135 us, sorted by block 142 -> 47.
 template <int B>
 constexpr int request_lanes() { return B <= 4 ? 3 : 3 * B; }
 
@@ -1084,8 +1084,8 @@ __global__ __launch_bounds__(kThreads) void k_decode_blocks(BlocksArgs a) {
 // workgroup reads a piece of 512 requests, picks its band's, 64 or so, and serves
 // them.  Where a piece's requests crowd into few bands (one holds twice its
 // share), its workgroups take equal parts of it instead; all of them see the same
-// piece and decide alike.  10^6 random blocks of 289 views of 512 x 512: 134 ->
-// 104 us (sorted by block, which no list here need be, 54 -> 69).
+// piece and decide alike.  10^6 random blocks of 289 views of 512 x 512: 135 ->
+// 97 us (sorted by block, which no list here need be, 47 -> 64).
 constexpr int64_t kBandRequests = 1 << 17, kBandBytes = (int64_t)13 << 20;
 
 template <int B>

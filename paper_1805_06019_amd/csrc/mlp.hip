@@ -64,7 +64,7 @@ struct InferArgs {
 // tile's features are requested before this tile's layers.  (The bias as a
 // product with one, in an fp32 MFMA, costs more than the additions: those
 // share the vector unit.)
-// Measured over 18.2 M rows: 456 us, 2.8 TB/s of rows (936 us with each layer's
+// Measured over 18.2 M rows: 466 us, 2.7 TB/s of rows (936 us with each layer's
 // output exchanged through LDS and the heads on half of the lanes); four waves
 // per SIMD with part of the weights in LDS 504 us, two 490 us.
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
