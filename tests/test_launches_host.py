@@ -16,7 +16,6 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, os.path.dirname(HERE))
 from paper_1805_06019_amd import lfc  # noqa: E402
 
-MIB = 1 << 20
 DEVICE = 1 << 44    # an address of the stand-in's device memory
 CASES = {}
 
@@ -37,7 +36,8 @@ def stand_in(tmp_path_factory):
 
 
 class Watch:
-    """The launches (kernel, grid, threads, LDS bytes, reader of the arguments) and events the stand-in saw."""
+    """The launches the stand-in saw (kernel, grid, threads, LDS bytes; of a batch's interpolation also its first
+    record, pieces of a row and requests), and the order of its launches, copies and waits."""
 
     def __init__(self, so):
         self.launches, self.events, self.fail = [], [], None
@@ -49,9 +49,11 @@ class Watch:
 
     def on_launch(self, name, grid, threads, lds, args):
         g = tuple(grid[i] for i in range(3))
-        words = C.cast(args[1], C.POINTER(C.c_int32)) if b"interp" in name else None
-        self.launches.append((name.decode(), g, threads, lds, (C.cast(args[0], C.POINTER(C.c_uint64))[0], words[0], words[1])
-                              if words else None))
+        more = None
+        if b"interp" in name:   # (records, grid)
+            pieces_n = C.cast(args[1], C.POINTER(C.c_int32))
+            more = (C.cast(args[0], C.POINTER(C.c_uint64))[0], pieces_n[0], pieces_n[1])
+        self.launches.append((name.decode(), g, threads, lds, more))
         self.events.append(("launch", name.decode(), 0))
         return 1 if self.fail and self.fail in name.decode() else 0
 
